@@ -53,7 +53,8 @@ def kernel_source_hash():
     counters; any code change does)."""
     import re
     h = hashlib.sha256()
-    for f in ("kernels.hip", "internal.h", "sbim_api.cpp"):
+    for f in ("kernels.hip", "quads.hip", "pairs.hip", "step_items.h", "internal.h",
+              "sbim_api.cpp"):
         with open(os.path.join(ROOT, "paper_2102_08756_amd", "csrc", f)) as fh:
             for line in fh:
                 code = re.sub(r"//.*", "", line).rstrip()

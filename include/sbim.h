@@ -115,25 +115,28 @@ typedef struct {
   long long step;              /* pushes since init / reset */
   long long backward_step;     /* sbim_backward calls since the last reset */
   int material_groups;         /* planes sharing (c_s, c_p) share one table and one pass */
-  int sweep_depth;             /* steps served by one pass over a block's history: 32 on
-                                  the matrix cores (below); otherwise 6 when the mean
-                                  window is under 64 lags, else 12 (float64, compensated,
-                                  and float32 from a mean window of 1500 lags) or 8
-                                  (float32 below that); the environment variable
-                                  SBIM_SWEEP_DEPTH (1, 2, 4, 6, 8, 12 or 16; 16 or 32 on
-                                  the matrix cores) overrides it at sbim_init, for tuning */
-  int sweep_matrix_cores;      /* 1: the history sweep runs as 16x16x4 float32 matrix-core
-                                  products (float32 forms, one window for every mode, two
-                                  planes of one material, mean window of 64 lags or more);
+  int sweep_depth;             /* steps served by one pass over a block's history: on the
+                                  matrix cores (below) 32, or 64 with one plane per group
+                                  on grids where mostly only +-m1 share a wavenumber;
+                                  otherwise 6 when the mean window is under 64 lags, else
+                                  12 (float64, compensated, and float32 from a mean window
+                                  of 1500 lags) or 8 (float32 below that); the environment
+                                  variable SBIM_SWEEP_DEPTH (1, 2, 4, 6, 8, 12 or 16; 16 on
+                                  the matrix cores with two planes per group) overrides it
+                                  at sbim_init, for tuning */
+  int sweep_matrix_cores;      /* 1: the history sweep runs as 16x16x4 matrix-core products
+                                  (one window for every mode, of 64 lags or more; and
+                                  either a float32 form with two planes of one material or
+                                  more than 2^18 modes x lags per plane); float32 handles
+                                  that drive a fault or a strip sum their lags in order,
+                                  with two planes of one material on the matrix cores too;
                                   SBIM_SWEEP_KIND=valu or mfma overrides it, for tuning */
-  int sweep_lag_chunks;        /* matrix-core sweep: wavefronts per group of four modes,
-                                  each summing a range of lags (1, 2 or 4; 0 otherwise);
-                                  SBIM_SWEEP_CHUNKS overrides it, for tuning */
-  int sweep_quads;             /* matrix-core sweep: groups of four modes per work-group
-                                  (1, 2 or 4, at most 4 / sweep_lag_chunks; 0 otherwise):
-                                  2 for the compensated form (two lag ranges), 1 for
-                                  plain float32 (four); SBIM_SWEEP_QUADS overrides it,
-                                  for tuning */
+  int sweep_lag_chunks;        /* matrix-core sweep: wavefronts per group of modes that
+                                  share a kernel row, each summing a range of lags (1, 2
+                                  or 4; 0 otherwise); SBIM_SWEEP_CHUNKS overrides it, for
+                                  tuning */
+  int sweep_quads;             /* matrix-core sweep: such groups per work-group (1, 2 or 4;
+                                  0 otherwise); SBIM_SWEEP_QUADS overrides it, for tuning */
 } sbim_info;
 
 /*
@@ -292,9 +295,10 @@ int sbim_load_running_state(sbim_handle *h, const void *src_device);
  * n-1 of the modes whose block sweeps for steps n+1 .. n+sweep_depth, phase
  * (n+1) mod sweep_depth; the kernel rows of each distinct row class in those
  * blocks; their row/window indices and block descriptors; the sweep_depth
- * pending sums written per mode and plane) and the mode items (spectrum
- * gathered, float64 state read and written, ring slot written, pending sum
- * read, newest lags and their kernel rows read, traction spectrum written,
+ * pending sums written per mode and plane; on the matrix cores also the sums over
+ * the entries since a block's last sweep, formed every 8 steps) and the mode items
+ * (spectrum gathered, float64 state read and written, ring slot written, pending
+ * sums read, newest lags and their kernel rows read, traction spectrum written,
  * per-mode indices and geometry).
  */
 int sbim_step_work(const sbim_handle *h, long long n, double *mode_lags, double *conv_bytes);
@@ -386,7 +390,9 @@ typedef struct {
 /*
  * sbim_fault_create: a fault on handle h (planes as described above, handle at
  * step 0).  The parameter arrays are copied (the caller may free them
- * afterwards) and checked on the device; synchronises the stream.
+ * afterwards) and checked on the device; synchronises the stream.  A float32
+ * handle whose sweep would sum its lags out of order on the matrix cores is planned
+ * again with the sums in order (sbim_get_info and the snapshot sizes follow): the stick/slip history depends on their rounding.
  * SBIM_E_INVALID names the first offending cell (non-finite value, d_c <= 0,
  * mu_k < 0 or mu_s < mu_k).  A cell can be locked (a bonded interface) by a
  * static coefficient that no traction reaches.

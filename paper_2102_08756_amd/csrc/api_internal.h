@@ -38,6 +38,8 @@ long long out_spec_bytes(const sbim_handle *h);
 hipError_t fft_forward(sbim_handle *h, const void *field, void *spec);
 hipError_t fft_inverse(sbim_handle *h, const void *spec, void *scratch, void *field,
                        const void *add);
+// Plan a float32 handle at step 0 with its history sums in lag order (fault, strip).
+int keep_sum_order(sbim_handle *h);
 // One forward step: transform u (and v for VEL_INPUT), then the step launch of
 // every material group with the given rule for the damping term's velocity.
 int push_fields(sbim_handle *h, const void *u, const void *v, int vel_rule);

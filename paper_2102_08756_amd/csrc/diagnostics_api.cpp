@@ -220,6 +220,7 @@ int sbim_step_work(const sbim_handle *h, long long n, double *mode_lags, double 
     // class/window indices and block descriptors, and write S pending sums per
     // mode and plane
     for (long long b = (n + 1) % S; b < g.nblocks; b += S) {
+      if (g.h_blk_cap[b] <= sbim::kDirectLags) continue;
       const long long last = std::min<long long>(g.h_blk_cap[b] - 1, n + 1);
       int last_cls = -1;
       for (long long s = b * sbim::kLanes; s < std::min(g.M, (b + 1) * sbim::kLanes); ++s) {
@@ -234,6 +235,24 @@ int sbim_step_work(const sbim_handle *h, long long n, double *mode_lags, double 
       }
       bytes += 16.0;
     }
+    // time-tiled form, the middle level's blocks of this launch: the entries since their
+    // last sweep, their kernel rows, and kMidPeriod sums written per mode and plane
+    const int P = sbim::kMidPeriod;
+    for (long long b = (n + 1) % P; h->tiled && b < g.nblocks; b += P) {
+      const long long d = ((n + 1 - b) % S + S) % S;
+      if (d == 0) continue;
+      int last_cls = -1;
+      for (long long s = b * sbim::kLanes; s < std::min(g.M, (b + 1) * sbim::kLanes); ++s) {
+        if (g.h_nat[s] < 0 || g.h_win[s] == 0) continue;
+        const long long entries =
+            std::max(0LL, std::min<long long>({d, g.h_win[s] - 2LL, static_cast<long long>(n)}));
+        bytes += entries * g.np * 3.0 * 2.0 * r + 12.0 + P * g.np * 10.0 * r;
+        if (g.h_cls[s] != last_cls) {
+          last_cls = g.h_cls[s];
+          bytes += std::max(0LL, std::min<long long>(g.h_win[s] - 2LL, d + P - 1)) * 4.0 * r;
+        }
+      }
+    }
     // the mode items of step n (same launch), per mode and plane: the three
     // float64 spectrum values, the float64 state read and written, the ring
     // slot written, the pending sum read, the newest lags (history from the
@@ -243,10 +262,18 @@ int sbim_step_work(const sbim_handle *h, long long n, double *mode_lags, double 
       if (g.h_nat[s] < 0) continue;
       const long long b = s / sbim::kLanes;
       const int phi = static_cast<int>(b % S);
-      const bool swept = n >= (phi == 0 ? S : phi);
-      const long long fresh = std::min<long long>(g.h_win[s], swept ? (n - phi) % S + 2 : n + 1);
+      const long long since = ((n - phi) % S + S) % S;
+      const bool swept = n - since >= 1 && g.h_blk_cap[b] > sbim::kDirectLags;
+      long long newest = swept ? since + 2 : n + 1;
       double per_plane = 3.0 * 16.0 + 3.0 * 32.0 + 3.0 * 2.0 * r + 3.0 * 2.0 * r;
       if (swept) per_plane += 10.0 * r;
+      if (h->tiled) {  // middle level's sum, the step's entry written again with its tile
+        const long long e = since % P;
+        if (n - e >= 1) newest = e + 2;
+        if (n - e >= 1 && since >= P) per_plane += 10.0 * r;
+        per_plane += 3.0 * 2.0 * r;
+      }
+      const long long fresh = std::min<long long>(g.h_win[s], newest);
       per_plane += std::max(0LL, fresh - 1) * 3.0 * 2.0 * r + fresh * 4.0 * r;
       bytes += per_plane * g.np + 4.0 + 24.0 + 4.0 + 4.0 + (fresh > 0 ? 8.0 : 0.0);
     }

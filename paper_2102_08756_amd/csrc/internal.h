@@ -17,7 +17,10 @@ constexpr int kTwiddleN = 1 << kTwiddleLog;
 constexpr int kFftThreads = 256;
 constexpr int kFftPerThread = 16;     // transform points per thread in the LDS FFT kernels
 constexpr int kGaussN = 32;           // Gauss-Legendre points per quadrature panel
-constexpr int kMaxSweep = 8;          // deepest sweep: steps served by one pass over a history
+constexpr int kMidPeriod = 8;         // steps served by one middle-level sum (kernels.hip)
+constexpr int kRingTileBytes = 16;    // matrix-core form: consecutive steps of one real held together
+constexpr int kRecent = kMidPeriod + 1;  // matrix-core form: steps the mode items read again
+constexpr int kDirectLags = 2;        // blocks of at most this capacity have no lags to sweep
 
 // How the push forms the velocity of the damping term.
 enum VelRule : int {
@@ -48,7 +51,7 @@ struct Group {
   long long table_rows = 0;       // sum over classes of W + 1
   // device
   int *nat = nullptr;             // [M] sorted position -> spectrum bin i3 * n1 + i1
-  int *cls = nullptr;             // [M] sorted position -> class
+  long long *row0 = nullptr;      // [M] first kernel row of each position's class
   int *win = nullptr;             // [M] W(q) per sorted position
   double *geom = nullptr;         // [M][4] q, kh1, kh3, 0 per sorted position
   long long *blk_off = nullptr;   // [nblocks] first ring record of the block
@@ -58,9 +61,11 @@ struct Group {
   double *cls_q = nullptr;        // [nclasses]
   int *cls_w = nullptr;           // [nclasses]
   void *table = nullptr;          // [table_rows] x 4 reals (w11, w12, w22, w33)
-  void *ring = nullptr;           // [ring_records][np][3][64] complex
+  void *ring = nullptr;           // [ring_records][np][3][64] complex (matrix-core form: in
+                                  // tiles, then the recent ring [kRecent][nblocks][np][3][64])
   double *state = nullptr;        // [np][3][M] complex double (rotated frame, sorted)
-  void *pending = nullptr;        // [depth+1][np][10][M] real_t: history sums of coming steps
+  void *pending = nullptr;        // [depth+1][np][5][M] complex: history sums of coming steps,
+                                  // then [kMidPeriod+1][np][5][M]: the middle level's, if any
   // adjoint (allocated on first use)
   void *ring_adj = nullptr;
   void *pending_adj = nullptr;
@@ -85,10 +90,13 @@ struct sbim_handle {
   long long nh = 0;               // n1 * h3
   int ngroups = 0;
   sbim::Group g[SBIM_MAX_PLANES];
+  bool ready = false;             // the groups hold their buffers
   long long step = 0;             // pushes done
   long long bstep = 0;            // backward calls done
   int depth = 1;                  // sweep depth: steps served by one pass over a block's history
   bool mfma = false;              // history sweep on the matrix cores (quads of one class)
+  bool tiled = false;             // ... in the time-tiled form (quads.hip), else in lag order (pairs.hip)
+  int quad_modes = 4;             // time-tiled form: sorted positions that share a kernel row (2 or 4)
   int lag_chunks = 1;             // matrix-core sweep: wavefronts per quad, each a lag range
   int sweep_quads = 1;            // matrix-core sweep: quads per work-group (1, 2 or 4)
   void *twiddle = nullptr;        // [4096] complex real_t, exp(-2 pi i m / 4096)
@@ -150,17 +158,17 @@ hipError_t launch_step(const sbim_handle *h, const Group &g, const StepLaunch &w
 // Kernel arguments (device pointers) of the two item kinds of that launch.
 struct ModeArgs {
   const void *spec, *spec_v;
-  void *ring;
+  void *ring, *recent;
   double2 *state;
-  const void *pending, *table;
-  const long long *cls_off;
-  const int *cls, *win, *nat;
+  const void *pending, *mid, *table;
+  const long long *row0;
+  const int *win, *nat;
   const double *geom;
   const long long *blk_off;
   const int *blk_cap, *blk_stride;
   double2 *lam;
   void *out_a, *out_b;
-  long long M, nh, step;
+  long long M, nh, step, nblocks;
   int np, depth;
   double inv_dt;
   int vel_rule, state_rule;
@@ -168,16 +176,22 @@ struct ModeArgs {
 };
 struct SweepArgs {
   const void *ring, *table;
-  void *pending;
-  const int *cls, *win;
+  void *pending, *mid;
+  const long long *row0;
+  const int *win;
   const long long *blk_off;
   const int *blk_cap, *blk_stride;
-  const long long *cls_off;
   int cls_w0;             // rows of class 0 (its zero row follows them)
   long long M, step;
   int np;
   long long nphase;       // blocks of this launch's sweep phase
 };
+
+// The step launches of the matrix-core forms (quads.hip, pairs.hip), as launch_step.
+hipError_t launch_step_quads(const sbim_handle *h, const Group &g, const SweepArgs &sa,
+                             const ModeArgs &ma, hipEvent_t ev0, hipEvent_t ev1);
+hipError_t launch_step_pairs(const sbim_handle *h, const Group &g, const SweepArgs &sa,
+                             const ModeArgs &ma, hipEvent_t ev0, hipEvent_t ev1);
 
 // fault.hip: interface solve of a frictional fault between the two sides.
 // Fields are [component][cell] with cell = i1 * n3 + i3; u, v hold the upper

@@ -78,6 +78,12 @@ void gauss_legendre(int n, std::vector<double> &x, std::vector<double> &w) {
   }
 }
 
+// The matrix-core sweep needs windows of at least 4 lags (its ring steps), and
+// outside the two-plane float32 form enough work: more than this many modes x lags
+// per plane.
+constexpr int kQuadMinWindow = 4;
+constexpr double kQuadMinLags = 262144.0;
+
 struct ModeKey {
   int w;
   double q;
@@ -91,7 +97,7 @@ hipError_t dev_alloc_bytes(void **p, size_t bytes) {
 }
 
 void free_group(Group &g) {
-  void *ptrs[] = {g.nat,   g.cls,   g.win,   g.geom,      g.blk_off,   g.blk_cap, g.blk_stride, g.cls_off,
+  void *ptrs[] = {g.nat,   g.row0,  g.win,   g.geom,      g.blk_off,   g.blk_cap, g.blk_stride, g.cls_off,
                   g.cls_q, g.cls_w, g.table, g.ring,      g.state,     g.pending,
                   g.ring_adj, g.state_adj, g.lam_adj, g.pending_adj};
   for (void *p : ptrs)
@@ -113,14 +119,16 @@ void free_handle(sbim_handle *h) {
 }
 
 long long ring_bytes(const sbim_handle *h, const Group &g) {
-  return g.ring_records * g.np * 3LL * sbim::kLanes * 2 * static_cast<long long>(h->rsize);
+  return (g.ring_records + (h->tiled ? sbim::kRecent * g.nblocks : 0)) * g.np * 3LL * sbim::kLanes * 2 *
+         static_cast<long long>(h->rsize);
 }
 long long table_bytes(const sbim_handle *h, const Group &g) {
   return g.table_rows * 4LL * static_cast<long long>(h->rsize);
 }
 long long state_bytes_g(const Group &g) { return g.np * 3LL * g.M * 16; }
 long long pending_bytes(const sbim_handle *h, const Group &g) {
-  return (h->depth + 1LL) * g.np * 10LL * g.M * static_cast<long long>(h->rsize);
+  return (h->depth + 1LL + (h->tiled ? sbim::kMidPeriod + 1 : 0)) * g.np * 10LL * g.M *
+         static_cast<long long>(h->rsize);
 }
 long long out_spec_bytes(const sbim_handle *h) {
   return static_cast<long long>(h->cfg.nplanes) * 3 * h->nh * 2 * static_cast<long long>(h->rsize);
@@ -182,12 +190,96 @@ double mean_window(const sbim_config &c, double cs) {
   return sum / (static_cast<double>(n1) * h3);
 }
 
+// Sorted positions per kernel row of the matrix-core sweep: 4 where the classes
+// (modes of bitwise equal q, formed as plan_group forms it) pad to multiples of 4
+// with little waste, as on square grids ((+-m1, m3) and (+-m3, m1)); 2 where mostly
+// only +-m1 share q.
+int quad_modes(const sbim_config &c) {
+  const int n1 = c.n1, h3 = c.n3 / 2 + 1;
+  const double two_pi = 2.0 * M_PI;
+  std::vector<double> q(static_cast<size_t>(n1) * h3);
+  for (int i1 = 0; i1 < n1; ++i1) {
+    const int m1 = i1 < n1 / 2 ? i1 : i1 - n1;
+    const double k1 = (two_pi * m1) / (n1 * c.dx1);
+    for (int i3 = 0; i3 < h3; ++i3) {
+      const double k3 = (two_pi * i3) / (c.n3 * c.dx3);
+      q[static_cast<size_t>(i1) * h3 + i3] = std::sqrt(k1 * k1 + k3 * k3);
+    }
+  }
+  std::sort(q.begin(), q.end());
+  long long by4 = 0, by2 = 0;  // padded positions
+  for (size_t s0 = 0; s0 < q.size();) {
+    size_t s1 = s0;
+    while (s1 < q.size() && q[s1] == q[s0]) ++s1;
+    by4 += (s1 - s0 + 3) / 4 * 4;
+    by2 += (s1 - s0 + 1) / 2 * 2;
+    s0 = s1;
+  }
+  return 4 * by4 <= 5 * by2 ? 4 : 2;
+}
+
+// Order of the time-tiled form's positions.  `keys` come sorted by (W desc, q asc,
+// bin); each run of equal (W, q) is cut into quads of `quad` modes (padding: nat = -1),
+// and the quads, whose order is free where every window is the same, are put so that
+// a block's spectrum gathers and traction scatters are runs of neighbouring bins:
+// with quads of 4, (+-m1, m3) and (+-m3, m1), along a Z curve over 4 x 4 tiles of
+// (max, min) of the two indices (a block of 64 positions is one tile and touches
+// four 4 x 4 patches of the spectrum); with quads of 2, +-m1, in spectrum order.
+// (Sorted by q they were single bins: 1024^2 x 2 planes, float32: the traction
+// scatter alone took 45 us of a step.)
+void quad_order(const sbim_config &c, int quad, std::vector<ModeKey> &keys) {
+  const int n1 = c.n1;
+  auto m1 = [n1](int nat) { const int i = nat % n1; return i < n1 - i ? i : n1 - i; };  // |m1|
+  auto m3 = [n1](int nat) { return nat / n1; };
+  struct Quad { int w; unsigned long long key; size_t first; int count; };
+  std::vector<Quad> quads;
+  quads.reserve(keys.size() / quad + keys.size() / 8 + 1);
+  auto spread = [](unsigned v) {  // bits of v to the even places
+    unsigned long long r = 0;
+    for (int i = 0; i < 16; ++i) r |= static_cast<unsigned long long>((v >> i) & 1u) << (2 * i);
+    return r;
+  };
+  for (size_t s0 = 0; s0 < keys.size();) {
+    size_t s1 = s0;
+    while (s1 < keys.size() && keys[s1].w == keys[s0].w && keys[s1].q == keys[s0].q) ++s1;
+    // modes of one orbit (equal max and min of the indices) next to each other
+    auto lo = [&](int nat) { return std::min(m1(nat), m3(nat)); };
+    auto hi = [&](int nat) { return std::max(m1(nat), m3(nat)); };
+    if (quad == 4)
+      std::sort(keys.begin() + s0, keys.begin() + s1, [&](const ModeKey &x, const ModeKey &y) {
+        if (hi(x.nat) != hi(y.nat)) return hi(x.nat) < hi(y.nat);
+        return x.nat < y.nat;
+      });
+    for (size_t s = s0; s < s1; s += quad) {
+      const int nat = keys[s].nat;
+      const unsigned a = quad == 4 ? hi(nat) : m1(nat), b = quad == 4 ? lo(nat) : m3(nat);
+      const unsigned long long key = quad == 4
+          ? ((spread(a >> 2) | spread(b >> 2) << 1) << 4 | (b & 3) << 2 | (a & 3))
+          : static_cast<unsigned long long>(b) << 32 | a;
+      quads.push_back(Quad{keys[s].w, key, s, static_cast<int>(std::min<size_t>(quad, s1 - s))});
+    }
+    s0 = s1;
+  }
+  std::sort(quads.begin(), quads.end(), [](const Quad &x, const Quad &y) {
+    if (x.w != y.w) return x.w > y.w;
+    if (x.key != y.key) return x.key < y.key;
+    return x.first < y.first;
+  });
+  std::vector<ModeKey> out;
+  out.reserve(quads.size() * quad);
+  for (const Quad &z : quads)
+    for (int i = 0; i < quad; ++i)
+      out.push_back(i < z.count ? keys[z.first + i] : ModeKey{z.w, keys[z.first].q, -1});
+  keys.swap(out);
+}
+
 // Mode geometry, windows, ordering and classes of one material group (host).
-// With `quads` (the matrix-core sweep) every class starts at a multiple of 4
-// sorted positions and is padded to a multiple of 4 with positions that hold
-// no mode (bin -1, window 0, the class's row set), so each aligned group of
-// four lanes shares one kernel row.
-void plan_group(const sbim_config &c, int depth, bool quads, Group &g, std::vector<double> &geom,
+// With `quad` > 0 (the matrix-core sweeps: 2 or 4) every class is padded to a
+// multiple of `quad` sorted positions with positions that hold no mode (bin -1,
+// window 0, the class's row set), so each aligned group of `quad` lanes shares one
+// kernel row; `tiled` also orders those groups (quad_order) and lays the rings out
+// in time tiles.
+void plan_group(const sbim_config &c, int depth, int quad, bool tiled, Group &g, std::vector<double> &geom,
                 std::vector<long long> &blk_off, std::vector<int> &blk_cap,
                 std::vector<int> &blk_stride, std::vector<double> &cls_q) {
   const int n1 = c.n1, h3 = c.n3 / 2 + 1;
@@ -230,8 +322,10 @@ void plan_group(const sbim_config &c, int depth, bool quads, Group &g, std::vect
     if (by_q && a.q != b.q) return a.q < b.q;
     return a.nat < b.nat;
   });
-  if (quads) {
-    // pad each run of equal (W, q) (a class, sorted together) to a multiple of 4;
+  cls_q.clear();
+  g.h_cls_w.clear();
+  if (quad && !tiled) {
+    // pad each run of equal (W, q) (a class, sorted together) to a multiple of `quad`;
     // a padding position carries nat = -1
     std::vector<ModeKey> padded;
     padded.reserve(M + M / 2);
@@ -239,11 +333,19 @@ void plan_group(const sbim_config &c, int depth, bool quads, Group &g, std::vect
       long long s1 = s0;
       while (s1 < M && keys[s1].w == keys[s0].w && keys[s1].q == keys[s0].q) ++s1;
       for (long long s = s0; s < s1; ++s) padded.push_back(keys[s]);
-      for (long long r = (s1 - s0) % 4; r != 0 && r < 4; ++r)
+      for (long long r = (s1 - s0) % quad; r != 0 && r < quad; ++r)
         padded.push_back(ModeKey{keys[s0].w, keys[s0].q, -1});
       s0 = s1;
     }
     keys.swap(padded);
+  }
+  if (tiled) {
+    for (const ModeKey &k : keys)
+      if (k.w > 0 && (cls_q.empty() || cls_q.back() != k.q)) {
+        cls_q.push_back(k.q);
+        g.h_cls_w.push_back(k.w);
+      }
+    quad_order(c, quad, keys);
   }
   const long long Ms = static_cast<long long>(keys.size());  // sorted positions
   g.M = Ms;
@@ -252,8 +354,6 @@ void plan_group(const sbim_config &c, int depth, bool quads, Group &g, std::vect
   g.h_cls.resize(Ms);
   g.h_win.resize(Ms);
   geom.assign(4 * Ms, 0.0);
-  cls_q.clear();
-  g.h_cls_w.clear();
   // a class per distinct (W, q): kernel rows are shared whatever the order
   std::map<std::pair<int, double>, int> class_of;
   for (long long s = 0; s < Ms; ++s) {
@@ -265,7 +365,9 @@ void plan_group(const sbim_config &c, int depth, bool quads, Group &g, std::vect
       continue;
     }
     int cls = 0;
-    if (k.w > 0) {
+    if (k.w > 0 && tiled) {          // numbered in order of q
+      cls = static_cast<int>(std::lower_bound(cls_q.begin(), cls_q.end(), k.q) - cls_q.begin());
+    } else if (k.w > 0) {
       bool known = false;
       if (by_q) {                    // sorted by (W, q): equal keys are neighbours
         known = s > 0 && k.w == keys[s - 1].w && k.q == keys[s - 1].q;
@@ -301,14 +403,21 @@ void plan_group(const sbim_config &c, int depth, bool quads, Group &g, std::vect
       cap = std::max(cap, g.h_win[s]);
     blk_cap[b] = cap;
   }
+  if (tiled) {  // whole tiles of the time-tiled ring, at least four
+    const int ts = sbim::kRingTileBytes / (c.precision == SBIM_FP64 ? 8 : 4);
+    for (int &cap : blk_cap)
+      if (cap > 0) cap = std::max((cap + ts - 1) / ts * ts, 4 * ts);
+  }
   g.h_blk_cap = blk_cap;
   // Blocks of one sweep phase (b mod depth) are stored together; within a
   // phase, runs of consecutive blocks with equal capacity are stored slot-major.
+  // The time-tiled form addresses a block's tiles with 32-bit offsets, so there
+  // every block's ring is contiguous (a run of one; measured equal on gfx950).
   long long rec = 0;
   for (int ph = 0; ph < depth; ++ph) {
     for (long long b0 = ph; b0 < g.nblocks;) {
       long long b1 = b0, len = 0;
-      while (b1 < g.nblocks && blk_cap[b1] == blk_cap[b0]) {
+      while (b1 < g.nblocks && blk_cap[b1] == blk_cap[b0] && !(tiled && len > 0)) {
         b1 += depth;
         ++len;
       }
@@ -431,9 +540,295 @@ int step_group(sbim_handle *h, Group &g, const sbim::StepLaunch &w, bool timed) 
   return SBIM_OK;
 }
 
+// Groups of planes with equal (c_s, c_p), which share kernel tables and one pass.
+void make_groups(sbim_handle *h) {
+  const sbim_config *cfg = &h->cfg;
+  h->ngroups = 0;
+  for (int p = 0; p < cfg->nplanes; ++p) {
+    const sbim_plane &pl = cfg->plane[p];
+    int gi = -1;
+    for (int i = 0; i < h->ngroups; ++i)
+      if (h->g[i].cs == pl.cs && h->g[i].cp == pl.cp) gi = i;
+    if (gi < 0) {
+      gi = h->ngroups++;
+      h->g[gi] = Group();
+      h->g[gi].cs = pl.cs;
+      h->g[gi].cp = pl.cp;
+      h->g[gi].eta = pl.cp / pl.cs;
+    }
+    Group &g = h->g[gi];
+    g.pl[g.np++] = sbim::PlaneParams{pl.mu, pl.cs, pl.cp / pl.cs, pl.side, p};
+  }
+}
+
+// The plan of a handle's material groups (sweep form, mode order) and their device
+// memory, tables and cleared state; `extra` more bytes are needed beside them.  With
+// `in_order` the float32 history sums keep the lag order of the vector and in-order
+// forms.  `tables` (or null): kernel tables of an earlier plan of the same fixed
+// windows, whose classes and rows are the same; the groups take them over.  Errors are
+// reported on `eh` (null: for sbim_last_error(NULL)); the caller frees the groups then.
+int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, void **tables = nullptr) {
+  const sbim_config &c = h->cfg;
+  hipError_t e;
+  h->ready = false;
+  make_groups(h);
+  struct HostPlan {
+    std::vector<double> geom, cls_q;
+    std::vector<long long> blk_off, row0;
+    std::vector<int> blk_cap, blk_stride;
+  };
+  // Sweep depth: steps served by one pass over a block's history.  Deeper
+  // sweeps divide the history traffic, but the newest lags of each step (up
+  // to depth + 1 of them) are summed by the mode items.  A lane holds the 10
+  // sums of up to 8 steps (float32) or 6 (float64 and the compensated form,
+  // whose sums take two registers each); depths 12 and 16 give each mode two
+  // lanes, one per half of the steps.  Measured on gfx950 (two planes,
+  // 512^2 at W = 1000, 1024^2 at W = 2000, 2048^2 with per-mode windows of
+  // mean 18 lags): with long windows float64 and the compensated form run
+  // fastest at 12; float32 at 8 for W = 1000 (by 5%) and at 12 for W = 2000
+  // (by 7%); with mean windows under 64 lags every form runs fastest at 6.
+  double wbar = 0;
+  for (int p = 0; p < c.nplanes; ++p)
+    wbar = std::max(wbar, mean_window(c, c.plane[p].cs));
+  // Matrix-core sweep: one window for every mode (modes of a class then share
+  // their kernel rows), windows of 64 lags or more so that the deep sweep pays, and
+  // (outside the two-plane float32 forms) more than kQuadMinLags modes x lags per
+  // plane: measured on gfx950 against the vector sweep, us per step, 128 x 64
+  // two-material float64 W = 150: 45 against 86; 512 x 128 two-material float32
+  // W = 250: 58 against 103; 512^2 x 2 float64 W = 1000: 207 against 352; one plane
+  // 256^2 float32 W = 300, forward and adjoint: 33 against 38.
+  const int np0 = h->g[0].np;  // (planes per group: the same for every group)
+  const bool pair32 = !h->fp64 && np0 == 2;
+  // (and a block's ring within the 32-bit byte offsets of the sweep's buffer loads)
+  const bool able = c.window_mode == SBIM_W_FIXED && (in_order ? pair32 : c.window_cap >= kQuadMinWindow) &&
+                    c.window_cap * (np0 * 3.0 * sbim::kLanes * 2) * static_cast<double>(h->rsize) < 4.29e9;
+  h->mfma = able && wbar >= 64 &&
+            (pair32 || static_cast<double>(h->nh) * c.window_cap > kQuadMinLags);
+  if (const char *env = std::getenv("SBIM_SWEEP_KIND")) {  // tuning override
+    if (std::strcmp(env, "valu") == 0) h->mfma = false;
+    if (std::strcmp(env, "mfma") == 0) h->mfma = able;
+  }
+  int want_depth = 0;
+  if (const char *env = std::getenv("SBIM_SWEEP_DEPTH")) want_depth = std::atoi(env);  // tuning override
+  const auto vector_depth = [&]() {
+    if (want_depth == 1 || want_depth == 2 || want_depth == 4 || want_depth == 6 ||
+        want_depth == 8 || want_depth == 12 || want_depth == 16)
+      return want_depth;
+    return wbar < 64 ? 6 : (h->comp || h->fp64 || wbar >= 1500 ? 12 : 8);
+  };
+  h->tiled = h->mfma && !in_order;
+  h->quad_modes = 4;
+  if (h->tiled && !(np0 == 2 && want_depth == 16)) h->quad_modes = quad_modes(c);
+  if (!h->mfma)
+    h->depth = vector_depth();
+  else if (np0 == 2 && want_depth == 16)
+    h->depth = 16;
+  else
+    h->depth = h->quad_modes == 2 && np0 == 1 ? 64 : 32;
+  std::vector<HostPlan> plan(h->ngroups);
+  auto plan_groups = [&]() {
+    for (int i = 0; i < h->ngroups; ++i)
+      plan_group(c, h->depth, h->mfma ? h->quad_modes : 0, h->tiled, h->g[i], plan[i].geom,
+                 plan[i].blk_off, plan[i].blk_cap, plan[i].blk_stride, plan[i].cls_q);
+  };
+  plan_groups();
+  if (h->mfma && !h->tiled) {
+    // The in-order form addresses a block's history with 32-bit byte offsets from
+    // its slot 0: every block's capacity times its slot stride must stay below 2^30
+    // floats, else the vector sweep plans the group instead.
+    for (long long b = 0; b < h->g[0].nblocks && h->mfma; ++b)
+      if (static_cast<long long>(plan[0].blk_cap[b]) * plan[0].blk_stride[b] * 2 * 3 * sbim::kLanes * 2 >=
+          (1LL << 30))
+        h->mfma = false;
+    if (!h->mfma) {
+      h->depth = wbar < 64 ? 6 : (h->comp || wbar >= 1500 ? 12 : 8);
+      plan_groups();
+    }
+  }
+  if (h->mfma) {
+    if (h->tiled) {
+      // Lag ranges per quad, one wavefront each: one for fewer than 4 rounds of 32 lags,
+      // two for fewer than 16, else four (measured on gfx950, us per pass at 1 / 2 / 4
+      // ranges: W = 150 float64 rupture 128 x 64 238 / 222 / 232; W = 250 float32
+      // 512 x 128 65 / 59 / 60; W = 1000 float64 512^2 with the sweep spread among the
+      // other work - / 219 / 211, compensated - / 136 / 133; eight are slower there).
+      const int rounds = (c.window_cap + 31) / 32;
+      h->lag_chunks = rounds < 4 ? 1 : rounds < 16 ? 2 : 4;
+    } else {
+      // in-order form: as many as fit at least 16 blocks of 4 lags, up to two for the
+      // compensated form (its registers allow three wavefronts per SIMD), four for
+      // plain float32
+      const int nblk = (std::max(0, h->g[0].wmax - 2) + 3) / 4;
+      const int want = h->comp ? 2 : 4;
+      h->lag_chunks = 1;
+      while (h->lag_chunks < want && nblk >= 16 * 2 * h->lag_chunks) h->lag_chunks *= 2;
+    }
+    if (const char *env = std::getenv("SBIM_SWEEP_CHUNKS")) {  // tuning override
+      const int v = std::atoi(env);
+      if (v == 1 || v == 2 || v == 4 || (v == 8 && h->tiled)) h->lag_chunks = v;
+    }
+    // Quads per work-group.  Time-tiled form: one, its history tiles are whole cache
+    // lines (two quads measured within 2%, either way).  In-order form: two for the
+    // compensated form, whose neighbouring quads share the cache lines of their history
+    // (1024^2 at W = 2000: 5% faster), one for plain float32.
+    h->sweep_quads = !h->tiled && h->comp && h->lag_chunks <= 2 ? 2 : 1;
+    if (const char *env = std::getenv("SBIM_SWEEP_QUADS")) {  // tuning override
+      const int v = std::atoi(env);
+      if ((v == 1 || v == 2 || v == 4) && v * h->lag_chunks <= (h->tiled ? 8 : 4))
+        h->sweep_quads = v;
+    }
+  }
+  size_t need = extra;
+  for (int i = 0; i < h->ngroups; ++i) {
+    const Group &g = h->g[i];
+    need += ring_bytes(h, g) + state_bytes_g(g) + pending_bytes(h, g);
+    if (!(tables && tables[i])) need += table_bytes(h, g);
+    need += g.M * (4 * 2 + 8 + 32) + g.nblocks * 16 + g.nclasses * 20;
+  }
+  size_t free_b = 0, total_b = 0;
+  e = hipMemGetInfo(&free_b, &total_b);
+  if (e != hipSuccess) return fail(eh, SBIM_E_DEVICE, "hipMemGetInfo: %s", hipGetErrorString(e));
+  if (h->tiled) {
+    // The time-tiled form holds more sums per mode (and again for the adjoint): where
+    // both would not fit, plan the forms that hold less.
+    size_t adjoint = 0;
+    for (int i = 0; i < h->ngroups; ++i)
+      adjoint += ring_bytes(h, h->g[i]) + 2 * state_bytes_g(h->g[i]) + pending_bytes(h, h->g[i]);
+    if (need + adjoint + out_spec_bytes(h) > free_b) {
+      for (int i = 0; i < h->ngroups; ++i) free_group(h->g[i]);
+      return plan_handle(h, true, extra, eh);
+    }
+  }
+  if (need > free_b)
+    return fail(eh, SBIM_E_OOM, "needs %zu bytes of device memory, %zu free", need, free_b);
+
+  std::vector<double> glx, glw;
+  gauss_legendre(sbim::kGaussN, glx, glw);
+  double *d_glx = nullptr, *d_glw = nullptr;
+
+#define TRY(expr)                                         \
+  do {                                                    \
+    e = (expr);                                           \
+    if (e != hipSuccess) {                                \
+      const int code = (e == hipErrorOutOfMemory) ? SBIM_E_OOM : SBIM_E_DEVICE; \
+      (void)hipStreamSynchronize(h->stream);              \
+      if (d_glx) (void)hipFree(d_glx);                    \
+      if (d_glw) (void)hipFree(d_glw);                    \
+      return fail(eh, code, "%s: %s", #expr, hipGetErrorString(e)); \
+    }                                                     \
+  } while (0)
+
+  TRY(dev_alloc(&d_glx, glx.size()));
+  TRY(dev_alloc(&d_glw, glw.size()));
+  TRY(upload(d_glx, glx.data(), glx.size() * sizeof(double), h->stream));
+  TRY(upload(d_glw, glw.data(), glw.size() * sizeof(double), h->stream));
+  for (int i = 0; i < h->ngroups; ++i) {
+    Group &g = h->g[i];
+    HostPlan &hp = plan[i];
+    hp.row0.resize(g.M);
+    for (long long s = 0; s < g.M; ++s) hp.row0[s] = g.nclasses ? g.h_cls_off[g.h_cls[s]] : 0;
+    TRY(dev_alloc(&g.nat, g.M));
+    TRY(dev_alloc(&g.row0, g.M));
+    TRY(dev_alloc(&g.win, g.M));
+    TRY(dev_alloc(&g.geom, 4 * g.M));
+    TRY(dev_alloc(&g.blk_off, g.nblocks));
+    TRY(dev_alloc(&g.blk_cap, g.nblocks));
+    TRY(dev_alloc(&g.blk_stride, g.nblocks));
+    TRY(dev_alloc(&g.cls_off, g.nclasses));
+    TRY(dev_alloc(&g.cls_q, g.nclasses));
+    TRY(dev_alloc(&g.cls_w, g.nclasses));
+    const bool kept = tables && tables[i];
+    if (kept) {
+      g.table = tables[i];
+      tables[i] = nullptr;
+    } else {
+      TRY(dev_alloc_bytes(&g.table, table_bytes(h, g)));
+    }
+    TRY(dev_alloc_bytes(&g.ring, ring_bytes(h, g)));
+    TRY(dev_alloc(&g.state, state_bytes_g(g) / 8));
+    TRY(dev_alloc_bytes(&g.pending, pending_bytes(h, g)));
+    TRY(upload(g.nat, g.h_nat.data(), g.M * sizeof(int), h->stream));
+    TRY(upload(g.row0, hp.row0.data(), g.M * sizeof(long long), h->stream));
+    TRY(upload(g.win, g.h_win.data(), g.M * sizeof(int), h->stream));
+    TRY(upload(g.geom, hp.geom.data(), hp.geom.size() * sizeof(double), h->stream));
+    TRY(upload(g.blk_off, hp.blk_off.data(), hp.blk_off.size() * sizeof(long long), h->stream));
+    TRY(upload(g.blk_cap, hp.blk_cap.data(), hp.blk_cap.size() * sizeof(int), h->stream));
+    TRY(upload(g.blk_stride, hp.blk_stride.data(), hp.blk_stride.size() * sizeof(int), h->stream));
+    TRY(upload(g.cls_off, g.h_cls_off.data(), g.h_cls_off.size() * sizeof(long long), h->stream));
+    TRY(upload(g.cls_q, hp.cls_q.data(), hp.cls_q.size() * sizeof(double), h->stream));
+    TRY(upload(g.cls_w, g.h_cls_w.data(), g.h_cls_w.size() * sizeof(int), h->stream));
+    if (ring_bytes(h, g)) TRY(hipMemsetAsync(g.ring, 0, ring_bytes(h, g), h->stream));
+    TRY(hipMemsetAsync(g.state, 0, state_bytes_g(g), h->stream));
+    TRY(hipMemsetAsync(g.pending, 0, pending_bytes(h, g), h->stream));
+    if (c.window_mode == SBIM_W_STATIC) {
+      // one row per class: the static integrals G_ab(infinity) of the kernels,
+      // i.e. the static surface stiffness K_ab(0) less the instantaneous L-N
+      // coupling, (w11, w12, w22, w33); then the zero row
+      const double e2 = g.eta * g.eta;
+      const double row[4] = {2.0 * e2 / (e2 + 1.0), -2.0 / (e2 + 1.0) - (g.eta - 2.0),
+                             2.0 * e2 / (e2 + 1.0), 1.0};
+      std::vector<double> t64(static_cast<size_t>(g.table_rows) * 4, 0.0);
+      for (long long c = 0; c < g.nclasses; ++c)
+        for (int k = 0; k < 4; ++k) t64[static_cast<size_t>(g.h_cls_off[c]) * 4 + k] = row[k];
+      if (h->fp64) {
+        TRY(upload(g.table, t64.data(), t64.size() * sizeof(double), h->stream));
+        TRY(hipStreamSynchronize(h->stream));
+      } else {
+        std::vector<float> t32(t64.begin(), t64.end());
+        TRY(upload(g.table, t32.data(), t32.size() * sizeof(float), h->stream));
+        TRY(hipStreamSynchronize(h->stream));
+      }
+    } else if (!kept) {
+      TRY(sbim::launch_tabulate(h->fp64, g, c.dt, d_glx, d_glw, h->stream));
+    }
+    // the host vectors must outlive the asynchronous copies
+    TRY(hipStreamSynchronize(h->stream));
+  }
+  TRY(hipStreamSynchronize(h->stream));
+#undef TRY
+  (void)hipFree(d_glx);
+  (void)hipFree(d_glw);
+  h->ready = true;
+  return SBIM_OK;
+}
+
+
+// The in-order form for a float32 handle that will drive a fault or a strip: the
+// stick/slip state follows the rounding of the history sums from step to step, so the
+// order of the sums is part of those results.  The handle is at step 0: it is planned
+// again, all but its kernel tables.  Handles whose adjoint has been used
+// (their adjoint history would be lost) keep the form they have.
+int keep_sum_order(sbim_handle *h) {
+  if (h->fp64 || !h->tiled) return SBIM_OK;
+  for (int i = 0; i < h->ngroups; ++i)
+    if (h->g[i].state_adj) return SBIM_OK;
+  hipError_t e = hipStreamSynchronize(h->stream);
+  if (e != hipSuccess) return hip_fail(h, e, "planning the history sums in order");
+  // (fixed windows: classes are the distinct q in ascending order in every form, so the
+  // kernel tables stay)
+  auto plan = [&](bool in_order) {
+    void *tables[SBIM_MAX_PLANES] = {};
+    for (int i = 0; i < h->ngroups; ++i) {
+      std::swap(tables[i], h->g[i].table);
+      free_group(h->g[i]);
+    }
+    const int code = plan_handle(h, in_order, 0, h, tables);
+    for (void *t : tables)
+      if (t) (void)hipFree(t);
+    return code;
+  };
+  const int rc = plan(true);
+  if (rc == SBIM_OK) return rc;
+  const std::string why = h->err;
+  (void)plan(false);  // back to what it was; without memory for either the handle is not ready
+  h->err = why;
+  return rc;
+}
+
 // One forward step: transform u (and v for VEL_INPUT), then the step launch of
 // every material group with the given rule for the damping term's velocity.
 int push_fields(sbim_handle *h, const void *u, const void *v, int vel_rule) {
+  if (!h->ready) return fail(h, SBIM_E_STATE, "the handle has no history buffers");
   hipError_t e = fft_forward(h, u, h->spec);
   if (e != hipSuccess) return hip_fail(h, e, "forward FFT of u");
   if (vel_rule == sbim::VEL_INPUT) {
@@ -499,158 +894,24 @@ int sbim_init(const sbim_config *cfg, sbim_handle **out) {
                 h->device, hipGetErrorString(e));
   }
 
-  // material groups: planes with equal (c_s, c_p) share kernel tables and one pass
-  for (int p = 0; p < cfg->nplanes; ++p) {
-    const sbim_plane &pl = cfg->plane[p];
-    int gi = -1;
-    for (int i = 0; i < h->ngroups; ++i)
-      if (h->g[i].cs == pl.cs && h->g[i].cp == pl.cp) gi = i;
-    if (gi < 0) {
-      gi = h->ngroups++;
-      h->g[gi].cs = pl.cs;
-      h->g[gi].cp = pl.cp;
-      h->g[gi].eta = pl.cp / pl.cs;
-    }
-    Group &g = h->g[gi];
-    g.pl[g.np++] = sbim::PlaneParams{pl.mu, pl.cs, pl.cp / pl.cs, pl.side, p};
-  }
-
-  struct HostPlan {
-    std::vector<double> geom, cls_q;
-    std::vector<long long> blk_off;
-    std::vector<int> blk_cap, blk_stride;
-  };
-  // Sweep depth: steps served by one pass over a block's history.  Deeper
-  // sweeps divide the history traffic, but the newest lags of each step (up
-  // to depth + 1 of them) are summed by the mode items.  A lane holds the 10
-  // sums of up to 8 steps (float32) or 6 (float64 and the compensated form,
-  // whose sums take two registers each); depths 12 and 16 give each mode two
-  // lanes, one per half of the steps.  Measured on gfx950 (two planes,
-  // 512^2 at W = 1000, 1024^2 at W = 2000, 2048^2 with per-mode windows of
-  // mean 18 lags): with long windows float64 and the compensated form run
-  // fastest at 12; float32 at 8 for W = 1000 (by 5%) and at 12 for W = 2000
-  // (by 7%); with mean windows under 64 lags every form runs fastest at 6.
-  double wbar = 0;
-  for (int p = 0; p < cfg->nplanes; ++p)
-    wbar = std::max(wbar, mean_window(*cfg, cfg->plane[p].cs));
-  h->depth = wbar < 64 ? 6 : (h->comp || h->fp64 || wbar >= 1500 ? 12 : 8);
-  // Matrix-core sweep: float32 history, one window for every mode, both planes
-  // in one material group (their kernel rows shared), windows long enough for
-  // the deep sweep to pay.  Its depth is 16 or 32 (one or two 16-step groups of
-  // the 16x16x4 products); measured on gfx950 (two planes 512^2 at W = 1000,
-  // 1024^2 at W = 2000): 32 for both float32 forms.
-  const bool mfma_able = !h->fp64 && cfg->window_mode == SBIM_W_FIXED && h->ngroups == 1 &&
-                         h->g[0].np == 2;
-  h->mfma = mfma_able && wbar >= 64;
-  if (const char *env = std::getenv("SBIM_SWEEP_KIND")) {  // tuning override
-    if (std::strcmp(env, "valu") == 0) h->mfma = false;
-    if (std::strcmp(env, "mfma") == 0) h->mfma = mfma_able;
-  }
-  if (h->mfma) h->depth = 32;
-  if (const char *env = std::getenv("SBIM_SWEEP_DEPTH")) {  // tuning override
-    const int v = std::atoi(env);
-    if (h->mfma) {
-      if (v == 16 || v == 32) h->depth = v;
-    } else if (v == 1 || v == 2 || v == 4 || v == 6 || v == 8 || v == 12 || v == 16) {
-      h->depth = v;
-    }
-  }
-  std::vector<HostPlan> plan(h->ngroups);
-  size_t need = 0;
-  for (int i = 0; i < h->ngroups; ++i) {
-    Group &g = h->g[i];
-    plan_group(*cfg, h->depth, h->mfma, g, plan[i].geom, plan[i].blk_off, plan[i].blk_cap,
-               plan[i].blk_stride, plan[i].cls_q);
-    need += ring_bytes(h, g) + table_bytes(h, g) + state_bytes_g(g);
-    need += pending_bytes(h, g);
-    need += g.M * (4 * 3 + 32) + g.nblocks * 16 + g.nclasses * 20;
-  }
-  if (h->mfma) {
-    // The quad sweep addresses a block's history with 32-bit byte offsets from
-    // its slot 0: every block's capacity times its slot stride must stay below
-    // 2^30 floats, else the vector-unit sweep plans the group instead.
-    const Group &g0 = h->g[0];
-    bool fits = true;
-    for (long long b = 0; b < g0.nblocks; ++b)
-      if (static_cast<long long>(plan[0].blk_cap[b]) * plan[0].blk_stride[b] * 2 * 3 * sbim::kLanes * 2 >=
-          (1LL << 30))
-        fits = false;
-    if (!fits) {
-      h->mfma = false;
-      h->depth = wbar < 64 ? 6 : (h->comp || wbar >= 1500 ? 12 : 8);
-      need = 0;
-      Group &g = h->g[0];
-      const double cs = g.cs, cp = g.cp, eta = g.eta;
-      const int np = g.np;
-      sbim::PlaneParams pl[SBIM_MAX_PLANES] = {g.pl[0], g.pl[1]};
-      g = Group();
-      g.cs = cs, g.cp = cp, g.eta = eta, g.np = np;
-      for (int k = 0; k < np; ++k) g.pl[k] = pl[k];
-      plan[0] = HostPlan();
-      plan_group(*cfg, h->depth, false, g, plan[0].geom, plan[0].blk_off, plan[0].blk_cap,
-                 plan[0].blk_stride, plan[0].cls_q);
-      need += ring_bytes(h, g) + table_bytes(h, g) + state_bytes_g(g) + pending_bytes(h, g);
-      need += g.M * (4 * 3 + 32) + g.nblocks * 16 + g.nclasses * 20;
-    }
-  }
-  if (h->mfma) {
-    // Wavefronts per quad (lag ranges, each at least 16 blocks of 4 lags),
-    // measured on gfx950 (two planes 512^2 at W = 1000, 1024^2 at W = 2000):
-    // two for the compensated form (its registers allow three wavefronts per
-    // SIMD), four for plain float32.
-    const Group &g = h->g[0];
-    const int nblk = (std::max(0, g.wmax - 2) + 3) / 4;
-    const int want = h->comp ? 2 : 4;
-    h->lag_chunks = 1;
-    while (h->lag_chunks < want && nblk >= 16 * 2 * h->lag_chunks) h->lag_chunks *= 2;
-    if (const char *env = std::getenv("SBIM_SWEEP_CHUNKS")) {  // tuning override
-      const int v = std::atoi(env);
-      if (v == 1 || v == 2 || v == 4) h->lag_chunks = v;
-    }
-    // Quads per work-group: neighbouring quads of a block share the cache lines
-    // of their history (a line holds 4 quads' pieces), and in one work-group they
-    // stream them together.  Measured on gfx950: two for the compensated form
-    // (1024^2 at W = 2000: 5% faster; 512^2 at W = 1000: 1% faster since the
-    // mode items run XCD-contiguous, 1% slower before), one for plain float32 with
-    // its four lag ranges (two quads of two ranges: 6% slower at 512^2).
-    h->sweep_quads = (h->comp && h->lag_chunks <= 2) ? 2 : 1;
-    if (const char *env = std::getenv("SBIM_SWEEP_QUADS")) {  // tuning override
-      const int v = std::atoi(env);
-      if ((v == 1 || v == 2 || v == 4) && v * h->lag_chunks <= 4) h->sweep_quads = v;
-    }
-  }
-  // input spectra are float64 in every form; the traction spectrum is real_t
   const size_t spec_bytes = static_cast<size_t>(cfg->nplanes) * 3 * h->nh * 2 * sizeof(double);
   const size_t out_bytes = static_cast<size_t>(cfg->nplanes) * 3 * h->nh * 2 * h->rsize;
-  need += 2 * spec_bytes + out_bytes + sbim::kTwiddleN * 2 * (h->rsize + sizeof(double));
-  size_t free_b = 0, total_b = 0;
-  e = hipMemGetInfo(&free_b, &total_b);
-  if (e != hipSuccess) {
+  // input spectra are float64 in every form; the traction spectrum is real_t
+  rc = plan_handle(h, false, 2 * spec_bytes + out_bytes + sbim::kTwiddleN * 2 * (h->rsize + sizeof(double)),
+                   nullptr);
+  if (rc != SBIM_OK) {
     free_handle(h);
-    return fail(nullptr, SBIM_E_DEVICE, "hipMemGetInfo: %s", hipGetErrorString(e));
+    return rc;
   }
-  if (need > free_b) {
-    free_handle(h);
-    return fail(nullptr, SBIM_E_OOM, "needs %zu bytes of device memory, %zu free", need, free_b);
-  }
-
-
-  std::vector<double> glx, glw;
-  gauss_legendre(sbim::kGaussN, glx, glw);
-  double *d_glx = nullptr, *d_glw = nullptr;
-
 #define TRY(expr)                                         \
   do {                                                    \
     e = (expr);                                           \
     if (e != hipSuccess) {                                \
       const int code = (e == hipErrorOutOfMemory) ? SBIM_E_OOM : SBIM_E_DEVICE; \
-      if (d_glx) (void)hipFree(d_glx);                    \
-      if (d_glw) (void)hipFree(d_glw);                    \
       free_handle(h);                                     \
       return fail(nullptr, code, "%s: %s", #expr, hipGetErrorString(e)); \
     }                                                     \
   } while (0)
-
   TRY(dev_alloc_bytes(&h->twiddle, sbim::kTwiddleN * 2 * h->rsize));
   if (h->fp64) {
     h->twiddle64 = h->twiddle;
@@ -662,68 +923,8 @@ int sbim_init(const sbim_config *cfg, sbim_handle **out) {
   TRY(dev_alloc_bytes(&h->spec_v, spec_bytes));
   TRY(dev_alloc_bytes(&h->out_spec, out_bytes));
   TRY(sbim::upload_twiddles(h->fp64, h->twiddle, h->stream));
-  TRY(dev_alloc(&d_glx, glx.size()));
-  TRY(dev_alloc(&d_glw, glw.size()));
-  TRY(upload(d_glx, glx.data(), glx.size() * sizeof(double), h->stream));
-  TRY(upload(d_glw, glw.data(), glw.size() * sizeof(double), h->stream));
-  for (int i = 0; i < h->ngroups; ++i) {
-    Group &g = h->g[i];
-    HostPlan &hp = plan[i];
-    TRY(dev_alloc(&g.nat, g.M));
-    TRY(dev_alloc(&g.cls, g.M));
-    TRY(dev_alloc(&g.win, g.M));
-    TRY(dev_alloc(&g.geom, 4 * g.M));
-    TRY(dev_alloc(&g.blk_off, g.nblocks));
-    TRY(dev_alloc(&g.blk_cap, g.nblocks));
-    TRY(dev_alloc(&g.blk_stride, g.nblocks));
-    TRY(dev_alloc(&g.cls_off, g.nclasses));
-    TRY(dev_alloc(&g.cls_q, g.nclasses));
-    TRY(dev_alloc(&g.cls_w, g.nclasses));
-    TRY(dev_alloc_bytes(&g.table, table_bytes(h, g)));
-    TRY(dev_alloc_bytes(&g.ring, ring_bytes(h, g)));
-    TRY(dev_alloc(&g.state, state_bytes_g(g) / 8));
-    TRY(dev_alloc_bytes(&g.pending, pending_bytes(h, g)));
-    TRY(upload(g.nat, g.h_nat.data(), g.M * sizeof(int), h->stream));
-    TRY(upload(g.cls, g.h_cls.data(), g.M * sizeof(int), h->stream));
-    TRY(upload(g.win, g.h_win.data(), g.M * sizeof(int), h->stream));
-    TRY(upload(g.geom, hp.geom.data(), hp.geom.size() * sizeof(double), h->stream));
-    TRY(upload(g.blk_off, hp.blk_off.data(), hp.blk_off.size() * sizeof(long long), h->stream));
-    TRY(upload(g.blk_cap, hp.blk_cap.data(), hp.blk_cap.size() * sizeof(int), h->stream));
-    TRY(upload(g.blk_stride, hp.blk_stride.data(), hp.blk_stride.size() * sizeof(int), h->stream));
-    TRY(upload(g.cls_off, g.h_cls_off.data(), g.h_cls_off.size() * sizeof(long long), h->stream));
-    TRY(upload(g.cls_q, hp.cls_q.data(), hp.cls_q.size() * sizeof(double), h->stream));
-    TRY(upload(g.cls_w, g.h_cls_w.data(), g.h_cls_w.size() * sizeof(int), h->stream));
-    if (ring_bytes(h, g)) TRY(hipMemsetAsync(g.ring, 0, ring_bytes(h, g), h->stream));
-    TRY(hipMemsetAsync(g.state, 0, state_bytes_g(g), h->stream));
-    TRY(hipMemsetAsync(g.pending, 0, pending_bytes(h, g), h->stream));
-    if (cfg->window_mode == SBIM_W_STATIC) {
-      // one row per class: the static integrals G_ab(infinity) of the kernels,
-      // i.e. the static surface stiffness K_ab(0) less the instantaneous L-N
-      // coupling, (w11, w12, w22, w33); then the zero row
-      const double e2 = g.eta * g.eta;
-      const double row[4] = {2.0 * e2 / (e2 + 1.0), -2.0 / (e2 + 1.0) - (g.eta - 2.0),
-                             2.0 * e2 / (e2 + 1.0), 1.0};
-      std::vector<double> t64(static_cast<size_t>(g.table_rows) * 4, 0.0);
-      for (long long c = 0; c < g.nclasses; ++c)
-        for (int k = 0; k < 4; ++k) t64[static_cast<size_t>(g.h_cls_off[c]) * 4 + k] = row[k];
-      if (h->fp64) {
-        TRY(upload(g.table, t64.data(), t64.size() * sizeof(double), h->stream));
-        TRY(hipStreamSynchronize(h->stream));
-      } else {
-        std::vector<float> t32(t64.begin(), t64.end());
-        TRY(upload(g.table, t32.data(), t32.size() * sizeof(float), h->stream));
-        TRY(hipStreamSynchronize(h->stream));
-      }
-    } else {
-      TRY(sbim::launch_tabulate(h->fp64, g, cfg->dt, d_glx, d_glw, h->stream));
-    }
-    // the host vectors must outlive the asynchronous copies
-    TRY(hipStreamSynchronize(h->stream));
-  }
   TRY(hipStreamSynchronize(h->stream));
 #undef TRY
-  (void)hipFree(d_glx);
-  (void)hipFree(d_glw);
   *out = h;
   return SBIM_OK;
 }
@@ -754,6 +955,7 @@ int sbim_backward(sbim_handle *h, const void *g_tau, void *du, void *dv) {
   if (rc) return rc;
   rc = check_ptr(h, du, "dL_du");
   if (rc) return rc;
+  if (!h->ready) return fail(h, SBIM_E_STATE, "the handle has no history buffers");
   rc = ensure_adjoint(h);
   if (rc) return rc;
   hipError_t e = fft_forward(h, g_tau, h->spec);

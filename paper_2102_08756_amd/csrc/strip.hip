@@ -10,11 +10,10 @@
 // slipweak).
 //
 // Fields are float64 [component][node layer][x1][x3] (x3 fastest); one thread
-// per node in the predictor, per four nodes along x1 in each of three node
-// layers in the corrector, per fault cell for the split nodes.  The
-// stiffness is applied node by node as a 27-point stencil of 3x3 blocks, one
-// stencil per node layer (the element layers above and below it may differ),
-// precomputed on the host from the element stiffness.
+// per node in the predictor, per column of a few node layers in the corrector, per
+// fault cell for the split nodes.  The stiffness is applied node by node as a
+// 27-point stencil of 3x3 blocks, one stencil per node layer (the element layers
+// above and below it may differ), precomputed on the host from the element stiffness.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -27,66 +26,70 @@
 namespace sbim {
 namespace {
 
-constexpr int kStripThreads = 256;
-constexpr int kStripRows = 4;        // nodes along x1 per thread of the corrector (divides n1)
-constexpr int kStripLayers = 3;      // node layers per thread of the corrector
+// Pointers of known kind: device memory, and tables read through the scalar cache.
+using global_f64 = const __attribute__((address_space(1))) double *;
+using table_f64 = const __attribute__((address_space(4))) double *;
+
+constexpr int kStripThreads = 128;  // (1024^2, us a pass: 128 771, 256 781, 512 828)
 
 // The predictor of the next step from a node's new acceleration and velocity
 // (Eq. fepred and the displacement update), with the push inputs of S+ (plane
 // 0) or S- (plane 1) when the node lies on one of them.
 template <typename R>
-__device__ __forceinline__ void strip_predict(const StripArgs &a, long long k, int push_plane,
-                                              long long cell, int c, double vn, double acc) {
+__device__ __forceinline__ void strip_predict(const StripArgs &a, long long base, int push_plane,
+                                              unsigned cell, int c, double u, double vn, double acc) {
   const double dt = a.dt;
   const double vh = vn + 0.5 * dt * acc;        // v_{t+3/2}
-  const double un = a.u[k] + dt * vh;           // u_{t+2}
-  a.v[k] = vn;
-  a.vh[k] = vh;
-  a.u_next[k] = un;
+  const double un = u + dt * vh;                // u_{t+2}
+  (a.v + base)[cell] = vn;
+  (a.vh + base)[cell] = vh;
+  (a.u_next + base)[cell] = un;
   if (push_plane >= 0) {
     R *__restrict__ pu = static_cast<R *>(a.push_u);
     R *__restrict__ pv = static_cast<R *>(a.push_v);
-    const long long t = (push_plane * 3 + c) * a.cells + cell;
-    pu[t] = static_cast<R>(a.increment ? dt * vh : un);
-    pv[t] = static_cast<R>(vn + dt * acc);      // predicted velocity of Eq. fepred
+    const long long t = (push_plane * 3 + c) * a.cells;
+    (pu + t)[cell] = static_cast<R>(a.increment ? dt * vh : un);
+    (pv + t)[cell] = static_cast<R>(vn + dt * acc);  // predicted velocity of Eq. fepred
   }
 }
 
-// Everything after the stiffness forces for one node: the S+ (S-) traction,
+// Everything after the stiffness forces for one node (cell: its place in the layer; u: its u_{t+1}, vh: its
+// v_{t+1/2}): the S+ (S-) traction,
 // the fault solve on layer 0 of the one-sided strip, the corrector and the
 // fault outputs, then the predictor of the next step.
 template <typename R>
-__device__ __forceinline__ void strip_finish(const StripArgs &a, int layer, long long id,
-                                             long long cell, double r[3]) {
+__device__ __forceinline__ void strip_finish(const StripArgs &a, int layer, unsigned cell,
+                                             double r[3], const double u[3],
+                                             const double vh[3]) {
   const long long nodes = a.nodes, cells = a.cells;
   const double A = a.area;
   const R *__restrict__ ts = static_cast<const R *>(a.tau_sbi);
   if (layer == a.n2) {                           // S+: traction of the half-space above
 #pragma unroll
-    for (int p = 0; p < 3; ++p) r[p] += A * static_cast<double>(ts[p * cells + cell]);
+    for (int p = 0; p < 3; ++p) r[p] += A * static_cast<double>((ts + p * cells)[cell]);
   }
   const bool two = a.fault_lo >= 0;
   if (two && layer == 0) {                       // S-: outward normal -e2
 #pragma unroll
-    for (int p = 0; p < 3; ++p) r[p] -= A * static_cast<double>(ts[(3 + p) * cells + cell]);
+    for (int p = 0; p < 3; ++p) r[p] -= A * static_cast<double>((ts + (3 + p) * cells)[cell]);
   }
   if (two && (layer == a.fault_lo || layer == a.fault_lo + 1)) {
     // split fault nodes: the two copies are solved together by strip_fault2
     const int side = layer == a.fault_lo ? 1 : 0;
 #pragma unroll
-    for (int p = 0; p < 3; ++p) a.r_fault[(side * 3 + p) * cells + cell] = r[p];
+    for (int p = 0; p < 3; ++p) (a.r_fault + (side * 3 + p) * cells)[cell] = r[p];
     return;
   }
   const double M = a.mass[layer];
   const double dt = a.dt;
   if (!two && layer == 0) {                      // fault node: stick traction and strength
-    const double t00 = a.tau0[cell], t01 = a.tau0[cells + cell], t02 = a.tau0[2 * cells + cell];
-    const double vs0 = a.vh[id] + dt * r[0] / M;
-    const double vs2 = a.vh[2 * nodes + id] + dt * r[2] / M;
+    const double t00 = a.tau0[cell], t01 = (a.tau0 + cells)[cell], t02 = (a.tau0 + 2 * cells)[cell];
+    const double vs0 = vh[0] + dt * r[0] / M;
+    const double vs2 = vh[2] + dt * r[2] / M;
     const double st0 = t00 + M * vs0 / (dt * A);
     const double st2 = t02 + M * vs2 / (dt * A);
     const double mag = sqrt(st0 * st0 + st2 * st2);
-    const double s0 = 2.0 * a.u[id], s2 = 2.0 * a.u[2 * nodes + id];
+    const double s0 = 2.0 * u[0], s2 = 2.0 * u[2];
     const double delta = sqrt(s0 * s0 + s2 * s2);
     const double mus = a.mu_s[cell], muk = a.mu_k[cell], dc = a.d_c[cell];
     const double mu = delta < dc ? mus - (mus - muk) * delta / dc : muk;
@@ -101,117 +104,166 @@ __device__ __forceinline__ void strip_finish(const StripArgs &a, int layer, long
     r[0] -= A * (tau0 - t00);
     r[2] -= A * (tau2 - t02);
     a.tau[cell] = tau0;
-    a.tau[cells + cell] = t01;
-    a.tau[2 * cells + cell] = tau2;
+    (a.tau + cells)[cell] = t01;
+    (a.tau + 2 * cells)[cell] = tau2;
     a.slip[cell] = s0;
-    a.slip[cells + cell] = s2;
+    (a.slip + cells)[cell] = s2;
     a.sliding[cell] = sliding ? 1.0 : 0.0;
     if (a.tau_out) {
       a.tau_out[cell] = tau0;
-      a.tau_out[cells + cell] = t01;
-      a.tau_out[2 * cells + cell] = tau2;
+      (a.tau_out + cells)[cell] = t01;
+      (a.tau_out + 2 * cells)[cell] = tau2;
     }
   }
   const int push_plane = layer == a.n2 ? 0 : (two && layer == 0 ? 1 : -1);
   double vn[3];
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
-    const long long k = p * nodes + id;
     const double acc = r[p] / M;
-    vn[p] = a.vh[k] + 0.5 * dt * acc;            // v_{t+1} (Eqs. tintf, fecorr)
-    strip_predict<R>(a, k, push_plane, cell, p, vn[p], acc);
+    vn[p] = vh[p] + 0.5 * dt * acc;              // v_{t+1} (Eqs. tintf, fecorr)
+    strip_predict<R>(a, p * nodes + layer * cells, push_plane, cell, p, u[p], vn[p], acc);
   }
   if (!two && layer == 0) {
     a.rate[cell] = 2.0 * vn[0];
-    a.rate[cells + cell] = 2.0 * vn[2];
+    (a.rate + cells)[cell] = 2.0 * vn[2];
     if (a.rate_out) {
       a.rate_out[cell] = 2.0 * vn[0];
-      a.rate_out[cells + cell] = 2.0 * vn[2];
+      (a.rate_out + cells)[cell] = 2.0 * vn[2];
     }
   }
 }
 
-// One thread per kStripRows consecutive nodes along x1 (same x3) in each of
-// kStripLayers consecutive node layers: each row of u that the 27-point
-// stencils of those nodes need (node layers l0-1 .. l0+kStripLayers) is loaded
-// once and serves up to three of the thread's layers and three of its rows.
-// UNIFORM: every wavefront lies in one layer chunk, so the stencils are read
-// through the scalar cache once per wavefront.
+// The value of the lane before / after in the wavefront (`edge` at its ends).
+__device__ __forceinline__ double lane_shift(double v, double edge, bool left) {
+  const unsigned long long a = __builtin_bit_cast(unsigned long long, v);
+  const unsigned long long e = __builtin_bit_cast(unsigned long long, edge);
+  unsigned lo, hi;
+  if (left) {  // wave_shr:1
+    lo = __builtin_amdgcn_update_dpp(static_cast<int>(e), static_cast<int>(a), 0x138, 0xF, 0xF, false);
+    hi = __builtin_amdgcn_update_dpp(static_cast<int>(e >> 32), static_cast<int>(a >> 32), 0x138, 0xF, 0xF, false);
+  } else {     // wave_shl:1
+    lo = __builtin_amdgcn_update_dpp(static_cast<int>(e), static_cast<int>(a), 0x130, 0xF, 0xF, false);
+    hi = __builtin_amdgcn_update_dpp(static_cast<int>(e >> 32), static_cast<int>(a >> 32), 0x130, 0xF, 0xF, false);
+  }
+  return __builtin_bit_cast(double, static_cast<unsigned long long>(hi) << 32 | lo);
+}
+
+// One thread per (x1, x3) column of `depth` consecutive node layers.  It walks through
+// the node layers l0-1 .. l0+depth: a layer's displacement on the rows x1-1, x1, x1+1
+// comes from memory, its x3 neighbours from the lanes beside (lanes at the ends of a
+// wavefront or of the periodic grid load that neighbour's column themselves), and it is
+// added to the forces on the target layers l-1, l, l+1; the force on a layer is complete
+// one layer later, when its corrector and predictor follow.  Each force sums its terms
+// in the order offset in x2, x1, x3, component, whatever the depth.
+// UNIFORM: every wavefront lies in one run of layers, so the stencil comes through the
+// scalar cache (table_f64: after the loop's stores the compiler would read it through
+// vector memory otherwise).  Three wavefronts a SIMD hide the rows' latency; a prefetch
+// of the next layer costs the occupancy and more than it hides.
+// Bound by the small grid's latency and by memory on large ones: 48 B read and 72 B
+// written per node.  256^2 cells, two sides of 3 element layers: 49 us with one thread per
+// 4 x 3 nodes (x1, layers) and no lane exchange, 20.5 here; 1024^2, 2 element layers: 161
+// and 142 us (0.6 GB with the fault's and S+'s fields).
 template <typename R, bool UNIFORM>
-__global__ __launch_bounds__(kStripThreads) void strip_correct_kernel(StripArgs a) {
+__global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(3))) void
+strip_correct_kernel(StripArgs a, int depth) {
   const long long nodes = a.nodes, cells = a.cells;
   const int n1 = a.n1, n3 = a.n3, n2 = a.n2;
-  const long long tid = static_cast<long long>(blockIdx.x) * kStripThreads + threadIdx.x;
-  const long long per_chunk = cells / kStripRows;
-  const int nchunks = (n2 + kStripLayers) / kStripLayers;
-  if (tid >= per_chunk * nchunks) return;
-  const int chunk = UNIFORM ? __builtin_amdgcn_readfirstlane(static_cast<int>(tid / per_chunk))
-                            : static_cast<int>(tid / per_chunk);
-  const int l0 = chunk * kStripLayers;
-  const long long g = tid - chunk * per_chunk;
-  const int ib = static_cast<int>(g / n3);
-  const int i3 = static_cast<int>(g - static_cast<long long>(ib) * n3);
-  const int i10 = ib * kStripRows;
-  const int col[3] = {i3 == 0 ? n3 - 1 : i3 - 1, i3, i3 == n3 - 1 ? 0 : i3 + 1};
-
-  double r[kStripLayers][kStripRows][3];
+  // Work-groups go round-robin over the 8 XCDs; each XCD takes a contiguous eighth of
+  // them, so that a row's neighbours meet in its L2.
+  const long long wgs = (gridDim.x + 7LL) / 8;
+  const long long tid = ((blockIdx.x & 7) * wgs + (blockIdx.x >> 3)) * kStripThreads + threadIdx.x;
+  const int nruns = (n2 + depth) / depth;
+  if (tid >= cells * nruns) return;  // (a whole number of rows: a lane's neighbours in its row are active)
+  const int run = UNIFORM ? __builtin_amdgcn_readfirstlane(static_cast<int>(tid / cells))
+                          : static_cast<int>(tid / cells);
+  const int l0 = run * depth, l1 = min(l0 + depth, n2 + 1);  // target layers [l0, l1)
+  const unsigned cell = static_cast<unsigned>(tid - run * cells);
+  const int i1 = static_cast<int>(cell / n3), i3 = static_cast<int>(cell - static_cast<unsigned>(i1) * n3);
+  const int lane = threadIdx.x & 63;
+  const bool left_edge = lane == 0 || i3 == 0, right_edge = lane == 63 || i3 == n3 - 1;
+  // (never both: n3 >= 4 divides or is a multiple of 64)
+  const unsigned ecol = static_cast<unsigned>(left_edge ? (i3 == 0 ? n3 - 1 : i3 - 1)
+                                                        : (i3 == n3 - 1 ? 0 : i3 + 1));
+  const unsigned row[3] = {static_cast<unsigned>(i1 == 0 ? n1 - 1 : i1 - 1) * n3,
+                           static_cast<unsigned>(i1) * n3,
+                           static_cast<unsigned>(i1 == n1 - 1 ? 0 : i1 + 1) * n3};
+  double C[3][3], E[3][3];  // this column and the edge lanes' neighbour: [component][row]
+  auto load = [&](int l) {
+    const bool edge = left_edge || right_edge;
 #pragma unroll
-  for (int lo = 0; lo < kStripLayers; ++lo)
+    for (int c = 0; c < 3; ++c) {
+      global_f64 ul = (global_f64)(a.u + c * nodes + static_cast<long long>(l) * cells);
+      // (opaque: one base per component and 32-bit offsets, not a pointer per load
+      // kept through the loop)
+      if constexpr (UNIFORM)
+        asm volatile("" : "+s"(ul));
+      else
+        asm volatile("" : "+v"(ul));
 #pragma unroll
-    for (int k = 0; k < kStripRows; ++k) r[lo][k][0] = r[lo][k][1] = r[lo][k][2] = 0.0;
-#pragma unroll 1
-  for (int li = -1; li <= kStripLayers; ++li) {   // u of node layer l0 + li
-#pragma clang fp contract(fast)
-    const int l = l0 + li;
-    if (l < 0 || l > n2) continue;
-    const long long base = static_cast<long long>(l) * cells;
+      for (int q = 0; q < 3; ++q) C[c][q] = ul[row[q] + static_cast<unsigned>(i3)];
+      if (edge) {
 #pragma unroll
-    for (int q = 0; q < kStripRows + 2; ++q) {     // neighbour row i10 - 1 + q
-      int jr = i10 - 1 + q;
-      jr = jr < 0 ? jr + n1 : (jr >= n1 ? jr - n1 : jr);
-      const long long rb = base + static_cast<long long>(jr) * n3;
-      double u[3][3];
-#pragma unroll
-      for (int o3 = 0; o3 < 3; ++o3) {
-        const long long nb = rb + col[o3];
-        u[o3][0] = a.u[nb];
-        u[o3][1] = a.u[nodes + nb];
-        u[o3][2] = a.u[2 * nodes + nb];
-      }
-      // the row is the neighbour at offset o2 = li - lo of the thread's layer lo
-#pragma unroll
-      for (int lo = 0; lo < kStripLayers; ++lo) {
-        const int o2 = li - lo;
-        if (o2 < -1 || o2 > 1 || l0 + lo > n2) continue;
-        const double *__restrict__ Cl =
-            a.stencil + static_cast<long long>(l0 + lo) * 27 * 9 + 3 * (o2 + 1) * 9;
-        // row q is the neighbour at offset o1 = q - 1 - k of node k
-#pragma unroll
-        for (int k = 0; k < kStripRows; ++k) {
-          const int o1 = q - 1 - k;
-          if (o1 < -1 || o1 > 1) continue;
-#pragma unroll
-          for (int o3 = 0; o3 < 3; ++o3) {
-            const double *B = Cl + ((o1 + 1) + 9 * o3) * 9;
-#pragma unroll
-            for (int p = 0; p < 3; ++p) {
-              r[lo][k][p] -= B[3 * p] * u[o3][0];
-              r[lo][k][p] -= B[3 * p + 1] * u[o3][1];
-              r[lo][k][p] -= B[3 * p + 2] * u[o3][2];
-            }
-          }
-        }
+        for (int q = 0; q < 3; ++q) E[c][q] = ul[row[q] + ecol];
       }
     }
-  }
+  };
 #pragma unroll
-  for (int lo = 0; lo < kStripLayers; ++lo) {
-    const int layer = l0 + lo;
-    if (layer > n2) break;
+  for (int c = 0; c < 3; ++c) E[c][0] = E[c][1] = E[c][2] = 0.0;
+  // forces on the layers before, at and after the source layer
+  double f[3][3] = {};
+  double um[3] = {};   // u of the layer before
+  const int first = max(l0 - 1, 0);
+#pragma unroll 1
+  for (int l = first; l <= l1; ++l) {            // source layer (none above n2)
+    if (l <= n2) load(l);
+    double vh[3], uc[3];
+    // (opaque, so that the node's addresses are formed here from scalar bases and one
+    // offset, not kept as a pointer per array through the loop)
+    unsigned at = cell;
+    asm volatile("" : "+v"(at));
+    if (l > l0) {
 #pragma unroll
-    for (int k = 0; k < kStripRows; ++k) {
-      const long long cell = static_cast<long long>(i10 + k) * n3 + i3;
-      strip_finish<R>(a, layer, layer * cells + cell, cell, r[lo][k]);
+      for (int p = 0; p < 3; ++p) vh[p] = (a.vh + p * nodes + (l - 1LL) * cells)[at];
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) uc[c] = C[c][1];
+    if (l <= n2) {
+#pragma clang fp contract(fast)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {               // row at offset q - 1 in x1
+        double v[3][3];                           // [offset in x3][component]
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const double lo = lane_shift(C[c][q], E[c][q], true);
+          const double hi = lane_shift(C[c][q], E[c][q], false);
+          v[0][c] = left_edge ? E[c][q] : lo;
+          v[1][c] = C[c][q];
+          v[2][c] = right_edge ? E[c][q] : hi;
+        }
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {             // target layer l - 1 + t, which sees l at offset 1 - t
+          const int lt = l - 1 + t;
+          if (lt < l0 || lt >= l1) continue;
+          table_f64 B = (table_f64)a.stencil + (lt * 9 + (2 - t) * 3 + q) * 27;
+#pragma unroll
+          for (int o3 = 0; o3 < 3; ++o3)
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+#pragma unroll
+              for (int c = 0; c < 3; ++c) f[t][p] -= B[9 * o3 + 3 * p + c] * v[o3][c];
+        }
+        // (row by row: coefficients of all rows in flight would not fit the scalar registers)
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    // layer l - 1 has all its forces
+    if (l > l0) strip_finish<R>(a, l - 1, at, f[0], um, vh);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      um[c] = uc[c];
+      f[0][c] = f[1][c];
+      f[1][c] = f[2][c];
+      f[2][c] = 0.0;
     }
   }
 }
@@ -266,8 +318,8 @@ __global__ __launch_bounds__(kStripThreads) void strip_fault2_kernel(StripArgs a
     vp[p] = a.vh[p * nodes + ip] + 0.5 * dt * ap;
     vm[p] = a.vh[p * nodes + im] + 0.5 * dt * am;
     // the split copies lie on neither S+ nor S-
-    strip_predict<double>(a, p * nodes + ip, -1, cell, p, vp[p], ap);
-    strip_predict<double>(a, p * nodes + im, -1, cell, p, vm[p], am);
+    strip_predict<double>(a, p * nodes + ip - cell, -1, static_cast<unsigned>(cell), p, a.u[p * nodes + ip], vp[p], ap);
+    strip_predict<double>(a, p * nodes + im - cell, -1, static_cast<unsigned>(cell), p, a.u[p * nodes + im], vm[p], am);
     a.tau[p * cells + cell] = tau[p];
     if (a.tau_out) a.tau_out[p * cells + cell] = tau[p];
   }
@@ -338,22 +390,26 @@ hipError_t launch_strip_fault2(const StripArgs &a, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_strip_correct(bool fp64, const StripArgs &a, hipStream_t st) {
-  const long long threads = a.cells / kStripRows * ((a.n2 + kStripLayers) / kStripLayers);
-  const unsigned blocks = static_cast<unsigned>((threads + kStripThreads - 1) / kStripThreads);
-  const bool uniform = (a.cells / kStripRows) % 64 == 0;
-  if (fp64) {
-    if (uniform)
-      strip_correct_kernel<double, true><<<blocks, kStripThreads, 0, st>>>(a);
-    else
-      strip_correct_kernel<double, false><<<blocks, kStripThreads, 0, st>>>(a);
-  } else {
-    if (uniform)
-      strip_correct_kernel<float, true><<<blocks, kStripThreads, 0, st>>>(a);
-    else
-      strip_correct_kernel<float, false><<<blocks, kStripThreads, 0, st>>>(a);
-  }
+template <typename R>
+static hipError_t strip_correct(const StripArgs &a, int depth, hipStream_t st) {
+  const long long threads = a.cells * ((a.n2 + depth) / depth);
+  const unsigned blocks =
+      static_cast<unsigned>((threads + 8 * kStripThreads - 1) / (8 * kStripThreads) * 8);
+  if (a.cells % 64 == 0)
+    strip_correct_kernel<R, true><<<blocks, kStripThreads, 0, st>>>(a, depth);
+  else
+    strip_correct_kernel<R, false><<<blocks, kStripThreads, 0, st>>>(a, depth);
   return hipGetLastError();
+}
+
+// Layers per thread: four where that leaves four wavefronts to a SIMD (4096 in all), else
+// fewer: more layers a thread read fewer rows twice, but a small grid waits for the chain
+// of layers (us a pass, layers per thread 1 / 2 / 4: 1024^2 with 3 node layers, two steps,
+// 892 / 882 / 781; 256^2 with 8, three steps, 275 / 264 / 284).
+hipError_t launch_strip_correct(bool fp64, const StripArgs &a, hipStream_t st) {
+  int depth = 4;
+  while (depth > 1 && a.cells * ((a.n2 + depth) / depth) < 4096LL * 64) depth /= 2;
+  return fp64 ? strip_correct<double>(a, depth, st) : strip_correct<float>(a, depth, st);
 }
 
 }  // namespace sbim

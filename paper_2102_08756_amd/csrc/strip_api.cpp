@@ -202,7 +202,7 @@ int sbim_strip_create(sbim_handle *h, const sbim_strip_config *sc, const sbim_fa
           const int a = a1 + 2 * a2 + 4 * a3;
           for (int b = 0; b < 8; ++b) {
             const int o1 = (b & 1) - a1, o2 = ((b >> 1) & 1) - a2, o3 = ((b >> 2) & 1) - a3;
-            const int o = (o1 + 1) + 3 * (o2 + 1) + 9 * (o3 + 1);
+            const int o = 9 * (o2 + 1) + 3 * (o1 + 1) + (o3 + 1);
             double *blk = &st[(static_cast<size_t>(j) * 27 + o) * 9];
             for (int p = 0; p < 3; ++p)
               for (int q = 0; q < 3; ++q) blk[3 * p + q] += K[(3 * a + p) * 24 + 3 * b + q];

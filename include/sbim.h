@@ -264,7 +264,9 @@ int sbim_count_nonfinite_noalloc(sbim_handle *h, const void *field, long long *c
  * pending history sums of the coming steps, traction spectrum of the last
  * step, step counter) is sbim_state_bytes() bytes.  save/load
  * copy it to/from a caller-owned device buffer of at least that size,
- * asynchronously on the handle's stream.
+ * asynchronously on the handle's stream.  A snapshot fits handles that order their
+ * modes as the one that wrote it: same configuration and precision, same sweep form;
+ * one of another order is refused with SBIM_E_INVALID.
  */
 long long sbim_state_bytes(const sbim_handle *h);
 int sbim_save_state(sbim_handle *h, void *dst_device);
@@ -392,7 +394,8 @@ typedef struct {
  * step 0).  The parameter arrays are copied (the caller may free them
  * afterwards) and checked on the device; synchronises the stream.  A float32
  * handle whose sweep would sum its lags out of order on the matrix cores is planned
- * again with the sums in order (sbim_get_info and the snapshot sizes follow): the stick/slip history depends on their rounding.
+ * again with the sums in order (sbim_get_info and the snapshot sizes follow): the
+ * stick/slip history depends on their rounding.
  * SBIM_E_INVALID names the first offending cell (non-finite value, d_c <= 0,
  * mu_k < 0 or mu_s < mu_k).  A cell can be locked (a bonded interface) by a
  * static coefficient that no traction reaches.

@@ -87,6 +87,41 @@ int sbim_get_info(const sbim_handle *h, sbim_info *out) {
   return SBIM_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// A snapshot is the device memory as it lies, so its header tells the order of the modes.
+// Snapshots written before there was more than one order hold no mark: they are in lag order.
+struct SnapshotHeader {
+  long long step, layout;
+};
+constexpr long long kLagOrder = 0x5342494d4c414730, kTimeTiled = 0x5342494d54494c30;
+
+long long layout_of(const sbim_handle *h) {
+  return h->tiled ? kTimeTiled : kLagOrder;
+}
+
+bool layout_fits(const sbim_handle *h, const SnapshotHeader &hd) {
+  const bool marked = hd.layout == kLagOrder || hd.layout == kTimeTiled;
+  return (marked ? hd.layout : kLagOrder) == layout_of(h);
+}
+
+hipError_t save_header(const sbim_handle *h, void *dst) {
+  const SnapshotHeader hd{h->step, layout_of(h)};
+  const hipError_t e = hipMemcpyAsync(dst, &hd, sizeof hd, hipMemcpyHostToDevice, h->stream);
+  return e != hipSuccess ? e : hipStreamSynchronize(h->stream);  // hd goes with this frame
+}
+
+hipError_t load_header(const sbim_handle *h, const void *src, SnapshotHeader &hd) {
+  const hipError_t e = hipMemcpyAsync(&hd, src, sizeof hd, hipMemcpyDeviceToHost, h->stream);
+  return e != hipSuccess ? e : hipStreamSynchronize(h->stream);
+}
+
+}  // namespace
+
+extern "C" {
+
 long long sbim_state_bytes(const sbim_handle *h) {
   if (!h) return -1;
   long long b = 256 + out_spec_bytes(h);  // header (step counter), last traction spectrum
@@ -102,8 +137,7 @@ int sbim_save_state(sbim_handle *h, void *dst) {
   int rc = check_ptr(h, dst, "dst");
   if (rc) return rc;
   char *d = static_cast<char *>(dst);
-  hipError_t e = hipMemcpyAsync(d, &h->step, sizeof(long long), hipMemcpyHostToDevice, h->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(h->stream);  // &h->step may change after return
+  hipError_t e = save_header(h, d);
   d += 256;
   if (e == hipSuccess)
     e = hipMemcpyAsync(d, h->out_spec, out_spec_bytes(h), hipMemcpyDeviceToDevice, h->stream);
@@ -128,11 +162,12 @@ int sbim_load_state(sbim_handle *h, const void *src) {
   int rc = check_ptr(h, src, "src");
   if (rc) return rc;
   const char *s = static_cast<const char *>(src);
-  long long step = 0;
-  hipError_t e = hipMemcpyAsync(&step, s, sizeof(long long), hipMemcpyDeviceToHost, h->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+  SnapshotHeader hd{};
+  hipError_t e = load_header(h, s, hd);
   if (e != hipSuccess) return hip_fail(h, e, "sbim_load_state header");
-  if (step < 0) return fail(h, SBIM_E_INVALID, "snapshot header is corrupt");
+  if (hd.step < 0) return fail(h, SBIM_E_INVALID, "snapshot header is corrupt");
+  if (!layout_fits(h, hd))
+    return fail(h, SBIM_E_INVALID, "snapshot orders the modes in another way than this handle");
   s += 256;
   e = hipMemcpyAsync(h->out_spec, s, out_spec_bytes(h), hipMemcpyDeviceToDevice, h->stream);
   s += out_spec_bytes(h);
@@ -148,7 +183,7 @@ int sbim_load_state(sbim_handle *h, const void *src) {
     s += pb;
   }
   if (e != hipSuccess) return hip_fail(h, e, "sbim_load_state");
-  h->step = step;
+  h->step = hd.step;
   return SBIM_OK;
 }
 
@@ -164,8 +199,7 @@ int sbim_save_running_state(sbim_handle *h, void *dst) {
   int rc = check_ptr(h, dst, "dst");
   if (rc) return rc;
   char *d = static_cast<char *>(dst);
-  hipError_t e = hipMemcpyAsync(d, &h->step, sizeof(long long), hipMemcpyHostToDevice, h->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(h->stream);  // &h->step may change after return
+  hipError_t e = save_header(h, d);
   d += 256;
   for (int i = 0; i < h->ngroups && e == hipSuccess; ++i) {
     const Group &g = h->g[i];
@@ -181,11 +215,12 @@ int sbim_load_running_state(sbim_handle *h, const void *src) {
   int rc = check_ptr(h, src, "src");
   if (rc) return rc;
   const char *s = static_cast<const char *>(src);
-  long long step = 0;
-  hipError_t e = hipMemcpyAsync(&step, s, sizeof(long long), hipMemcpyDeviceToHost, h->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+  SnapshotHeader hd{};
+  hipError_t e = load_header(h, s, hd);
   if (e != hipSuccess) return hip_fail(h, e, "sbim_load_running_state header");
-  if (step < 0) return fail(h, SBIM_E_INVALID, "running-state snapshot header is corrupt");
+  if (hd.step < 0) return fail(h, SBIM_E_INVALID, "running-state snapshot header is corrupt");
+  if (!layout_fits(h, hd))
+    return fail(h, SBIM_E_INVALID, "running-state snapshot orders the modes in another way than this handle");
   s += 256;
   for (int i = 0; i < h->ngroups && e == hipSuccess; ++i) {
     Group &g = h->g[i];
@@ -197,7 +232,7 @@ int sbim_load_running_state(sbim_handle *h, const void *src) {
     if (e == hipSuccess) e = hipMemsetAsync(g.pending, 0, pending_bytes(h, g), h->stream);
   }
   if (e != hipSuccess) return hip_fail(h, e, "sbim_load_running_state");
-  h->step = step;
+  h->step = hd.step;
   return SBIM_OK;
 }
 

@@ -96,14 +96,16 @@ namespace {
 struct SnapshotHeader {
   long long step, layout;
 };
-constexpr long long kLagOrder = 0x5342494d4c414730, kTimeTiled = 0x5342494d54494c30;
+constexpr long long kLagOrder = 0x5342494d4c414730, kTimeTiled = 0x5342494d54494c30,
+                    kSpectrumOrder = 0x5342494d53504330;
 
 long long layout_of(const sbim_handle *h) {
-  return h->tiled ? kTimeTiled : kLagOrder;
+  if (h->tiled) return kTimeTiled;
+  return h->cfg.window_mode == SBIM_W_STATIC ? kSpectrumOrder : kLagOrder;
 }
 
 bool layout_fits(const sbim_handle *h, const SnapshotHeader &hd) {
-  const bool marked = hd.layout == kLagOrder || hd.layout == kTimeTiled;
+  const bool marked = hd.layout == kLagOrder || hd.layout == kTimeTiled || hd.layout == kSpectrumOrder;
   return (marked ? hd.layout : kLagOrder) == layout_of(h);
 }
 

@@ -40,11 +40,11 @@ __device__ __forceinline__ cplx<R> cconj(cplx<R> a) { return {a.x, -a.y}; }
 // r < L/4, copied from the global 4096-point table once per work-group, so that
 // no radix pass waits for memory.  load_quarter fills it (every thread calls it;
 // the caller synchronises before the first use).
-template <typename R>
+template <typename R, int NT = kFftThreads>
 __device__ __forceinline__ void load_quarter(cplx<R> *q, int logL, const cplx<R> *__restrict__ tw) {
   const int n = 1 << (logL - 2);
   const int stride = kTwiddleN >> logL;
-  for (int r = threadIdx.x; r < n; r += kFftThreads) q[r] = tw[r * stride];
+  for (int r = threadIdx.x; r < n; r += NT) q[r] = tw[r * stride];
 }
 // exp(dir 2 pi i j / 4096) for j a multiple of 4096 / L, from the quarter table:
 // with m = j L / 4096 = r + h L/4 (r < L/4), exp(-2 pi i m / L) = q[r] (-i)^h.
@@ -84,18 +84,22 @@ template <bool PAD>
 __device__ __forceinline__ int pad(int i) {
   return PAD ? i + (i >> 3) : i;
 }
+template <bool PAD> struct PadSlots {
+  __device__ __forceinline__ int operator()(int i) const { return pad<PAD>(i); }
+};
 __host__ __device__ constexpr int padded_points(int cnt, bool pad) {
   return pad ? cnt + (cnt + 7) / 8 : cnt;
 }
 
-// In-place FFT of nseq contiguous sequences of length N = 2^logN held in LDS
-// (point i at slot pad<PAD>(i)): Stockham autosort passes of radix 8 (then one
+// In-place FFT of nseq sequences of length N = 2^logN held in LDS (point i of
+// sequence b at slot(b N + i)): Stockham autosort passes of radix 8 (then one
 // of radix 4 or 2 for the remaining factor).  Every thread of the work-group
 // must call it.  Each pass stages its inputs in registers, synchronises, then
 // writes the outputs.
-template <typename R, int NT, int MAXV, bool PAD>
+template <typename R, int NT, int MAXV, typename Slot>
 __device__ __attribute__((always_inline)) void lds_fft(cplx<R> *buf, int N, int logN, int nseq,
-                                                       int dir, const cplx<R> *q, int logL) {
+                                                       int dir, const cplx<R> *q, int logL,
+                                                       const Slot &slot) {
   const int total = N * nseq;
   int logNs = 0;
   // Each pass reads the inputs of every butterfly of the thread from LDS,
@@ -114,7 +118,7 @@ __device__ __attribute__((always_inline)) void lds_fft(cplx<R> *buf, int N, int 
       const int g = min(static_cast<int>(threadIdx.x) + t * NT, nbf - 1);
       const int base = ((g >> (logN - 3)) << logN) + (g & (q8 - 1));
 #pragma unroll
-      for (int r = 0; r < 8; ++r) v[t][r] = buf[pad<PAD>(base + (r << (logN - 3)))];
+      for (int r = 0; r < 8; ++r) v[t][r] = buf[slot(base + (r << (logN - 3)))];
     }
     __syncthreads();
 #pragma unroll
@@ -156,18 +160,18 @@ __device__ __attribute__((always_inline)) void lds_fft(cplx<R> *buf, int N, int 
         {
           const cplx<R> t0 = cadd<R>(e[0], e[2]), t1 = csub<R>(e[0], e[2]);
           const cplx<R> t2 = cadd<R>(e[1], e[3]), t3 = rot4<R>(csub<R>(e[1], e[3]), dir);
-          buf[pad<PAD>(out)] = cadd<R>(t0, t2);
-          buf[pad<PAD>(out + (2 << logNs))] = cadd<R>(t1, t3);
-          buf[pad<PAD>(out + (4 << logNs))] = csub<R>(t0, t2);
-          buf[pad<PAD>(out + (6 << logNs))] = csub<R>(t1, t3);
+          buf[slot(out)] = cadd<R>(t0, t2);
+          buf[slot(out + (2 << logNs))] = cadd<R>(t1, t3);
+          buf[slot(out + (4 << logNs))] = csub<R>(t0, t2);
+          buf[slot(out + (6 << logNs))] = csub<R>(t1, t3);
         }
         {
           const cplx<R> t0 = cadd<R>(o[0], o[2]), t1 = csub<R>(o[0], o[2]);
           const cplx<R> t2 = cadd<R>(o[1], o[3]), t3 = rot4<R>(csub<R>(o[1], o[3]), dir);
-          buf[pad<PAD>(out + (1 << logNs))] = cadd<R>(t0, t2);
-          buf[pad<PAD>(out + (3 << logNs))] = cadd<R>(t1, t3);
-          buf[pad<PAD>(out + (5 << logNs))] = csub<R>(t0, t2);
-          buf[pad<PAD>(out + (7 << logNs))] = csub<R>(t1, t3);
+          buf[slot(out + (1 << logNs))] = cadd<R>(t0, t2);
+          buf[slot(out + (3 << logNs))] = cadd<R>(t1, t3);
+          buf[slot(out + (5 << logNs))] = csub<R>(t0, t2);
+          buf[slot(out + (7 << logNs))] = csub<R>(t1, t3);
         }
       }
     }
@@ -186,7 +190,7 @@ __device__ __attribute__((always_inline)) void lds_fft(cplx<R> *buf, int N, int 
       const int g = min(static_cast<int>(threadIdx.x) + t * NT, nbf - 1);
       const int base = ((g >> (logN - 2)) << logN) + (g & (q4 - 1));
 #pragma unroll
-      for (int r = 0; r < 4; ++r) v[t][r] = buf[pad<PAD>(base + (r << (logN - 2)))];
+      for (int r = 0; r < 4; ++r) v[t][r] = buf[slot(base + (r << (logN - 2)))];
     }
     __syncthreads();
 #pragma unroll
@@ -207,10 +211,10 @@ __device__ __attribute__((always_inline)) void lds_fft(cplx<R> *buf, int N, int 
         // dir * i * (a1 - a3): -i for the forward transform, +i for the inverse
         cplx<R> t3 = rot4<R>(csub<R>(a1, a3), dir);
         const int out = (b << logN) + ((j >> logNs) << (logNs + 2)) + k;
-        buf[pad<PAD>(out)] = cadd<R>(t0, t2);
-        buf[pad<PAD>(out + (1 << logNs))] = cadd<R>(t1, t3);
-        buf[pad<PAD>(out + (2 << logNs))] = csub<R>(t0, t2);
-        buf[pad<PAD>(out + (3 << logNs))] = csub<R>(t1, t3);
+        buf[slot(out)] = cadd<R>(t0, t2);
+        buf[slot(out + (1 << logNs))] = cadd<R>(t1, t3);
+        buf[slot(out + (2 << logNs))] = csub<R>(t0, t2);
+        buf[slot(out + (3 << logNs))] = csub<R>(t1, t3);
       }
     }
     __syncthreads();
@@ -229,8 +233,8 @@ __device__ __attribute__((always_inline)) void lds_fft(cplx<R> *buf, int N, int 
       const int g = min(static_cast<int>(threadIdx.x) + t * NT, nbf - 1);
       const int b = g >> (logN - 1);
       const int j = g & (h2 - 1);
-      v[t][0] = buf[pad<PAD>((b << logN) + j)];
-      v[t][1] = buf[pad<PAD>((b << logN) + j + h2)];
+      v[t][0] = buf[slot((b << logN) + j)];
+      v[t][1] = buf[slot((b << logN) + j + h2)];
     }
     __syncthreads();
 #pragma unroll
@@ -242,8 +246,8 @@ __device__ __attribute__((always_inline)) void lds_fft(cplx<R> *buf, int N, int 
         const int k = j & (Ns - 1);
         cplx<R> a1 = cmul<R>(v[t][1], twq<R>(q, k << lstep, logL, dir));
         const int out = (b << logN) + ((j >> logNs) << (logNs + 1)) + k;
-        buf[pad<PAD>(out)] = cadd<R>(v[t][0], a1);
-        buf[pad<PAD>(out + (1 << logNs))] = csub<R>(v[t][0], a1);
+        buf[slot(out)] = cadd<R>(v[t][0], a1);
+        buf[slot(out + (1 << logNs))] = csub<R>(v[t][0], a1);
       }
     }
     __syncthreads();
@@ -315,7 +319,7 @@ __global__ __launch_bounds__(kFftThreads) __attribute__((amdgpu_waves_per_eu(2))
     }
     __syncthreads();
     if (id + static_cast<int>(gridDim.x) < ntiles) load(id + gridDim.x);
-    lds_fft<R, kFftThreads, MAXV, PAD>(buf, Nh, logNh, rows, -1, q, logL);
+    lds_fft<R, kFftThreads, MAXV>(buf, Nh, logNh, rows, -1, q, logL, PadSlots<PAD>());
     cplx<R> *dst = spec + static_cast<long long>(f) * h3 * n1 + x0;
     for (int e = threadIdx.x; e < rows * h3; e += kFftThreads) {
       const int k = e >> logrows;
@@ -359,7 +363,7 @@ __global__ __launch_bounds__(kFftThreads) void cfft_rows_kernel(
   for (int i = 0; i < MAXV; ++i)
     buf[pad<PAD>(min(static_cast<int>(threadIdx.x) + i * kFftThreads, cnt - 1))] = v[i];
   __syncthreads();
-  lds_fft<R, kFftThreads, MAXV, PAD>(buf, n, logn, nb, dir, q, logn);
+  lds_fft<R, kFftThreads, MAXV>(buf, n, logn, nb, dir, q, logn, PadSlots<PAD>());
 #pragma unroll
   for (int i = 0; i < MAXV; ++i) {
     const int e = threadIdx.x + i * kFftThreads;
@@ -441,7 +445,7 @@ __global__ __launch_bounds__(kFftThreads) void c2r_t_kernel(
     }
   }
   __syncthreads();
-  lds_fft<R, kFftThreads, MAXV, PAD>(buf, Nh, logNh, rows, +1, q, logL);
+  lds_fft<R, kFftThreads, MAXV>(buf, Nh, logNh, rows, +1, q, logL, PadSlots<PAD>());
   const long long o = (static_cast<long long>(f) * n1 + x0) * n3;
   cplx<R> *dst = reinterpret_cast<cplx<R> *>(out + o);
   const cplx<R> *addp = add ? reinterpret_cast<const cplx<R> *>(add + o) : nullptr;
@@ -466,6 +470,133 @@ __global__ __launch_bounds__(kFftThreads) void c2r_t_kernel(
       }
       dst[e] = z;
     }
+  }
+}
+
+// ------------------------------------------------------------ whole fields
+
+// A field small enough for LDS (n1 (n3/2+1) complex points) is transformed whole by
+// one work-group: one launch instead of two, and no intermediate in memory.  Its
+// point (x1, bin k) sits at slot x1 S + k, S = n3/2 + 1: rows are the x3 transforms
+// (half length, n3/2 points), columns the x1 transforms; the odd stride S spreads a
+// column over the LDS banks.  Same passes and formulas as the two-kernel form.  Bound by
+// the chain of LDS passes, one work-group per field; the gain is the launch saved in each direction (64^2 x 3 fields, float64: 9.4 us
+// forward and 8.9 inverse against 9.2 and 10.2 for the two kernels of each; a step on a
+// small grid, bound by its launches, 25.7 -> 18.6 us).
+constexpr int kWholeThreads = 512;
+constexpr int kWholePerThread = 8;
+
+struct RowSlots {
+  int S, log;
+  __device__ __forceinline__ int operator()(int i) const { return (i >> log) * S + (i & ((1 << log) - 1)); }
+};
+struct ColumnSlots {
+  int S, log;
+  __device__ __forceinline__ int operator()(int i) const { return (i & ((1 << log) - 1)) * S + (i >> log); }
+};
+
+template <typename Rin, typename R>
+__global__ __launch_bounds__(kWholeThreads) void fft_whole_kernel(const Rin *__restrict__ in,
+                                                                  cplx<R> *__restrict__ spec, int logn1,
+                                                                  int logNh, int logL,
+                                                                  const cplx<R> *__restrict__ tw) {
+  extern __shared__ unsigned char smem_raw[];
+  cplx<R> *buf = reinterpret_cast<cplx<R> *>(smem_raw);
+  const int n1 = 1 << logn1, Nh = 1 << logNh, S = Nh + 1;
+  cplx<R> *q = buf + n1 * S;
+  load_quarter<R, kWholeThreads>(q, logL, tw);
+  const RowSlots rows{S, logNh};
+  const ColumnSlots cols{S, logn1};
+  const int cnt = n1 * Nh;
+  const cplx<Rin> *src = reinterpret_cast<const cplx<Rin> *>(in) + static_cast<long long>(blockIdx.x) * cnt;
+  cplx<Rin> v[kWholePerThread];
+#pragma unroll
+  for (int i = 0; i < kWholePerThread; ++i)
+    v[i] = src[min(static_cast<int>(threadIdx.x) + i * kWholeThreads, cnt - 1)];
+#pragma unroll
+  for (int i = 0; i < kWholePerThread; ++i)
+    buf[rows(min(static_cast<int>(threadIdx.x) + i * kWholeThreads, cnt - 1))] =
+        cplx<R>{static_cast<R>(v[i].x), static_cast<R>(v[i].y)};
+  __syncthreads();
+  lds_fft<R, kWholeThreads, kWholePerThread>(buf, Nh, logNh, n1, -1, q, logL, rows);
+  // bins k and Nh - k of each row from Z (k = 0: bins 0 and Nh)
+  const int lstep = kTwiddleLog - logNh - 1;  // 4096 / n3 = 2^lstep
+  const int half = Nh / 2 + 1;
+  for (int e = threadIdx.x; e < n1 * half; e += kWholeThreads) {
+    const int k = e >> logn1, rb = (e & (n1 - 1)) * S;
+    const int m = Nh - k;
+    const cplx<R> a = buf[rb + k], b = buf[rb + (k == 0 ? 0 : m)];
+    auto bin = [&](cplx<R> zk, cplx<R> zc, int kk) {
+      const cplx<R> ev = {(zk.x + zc.x) * R(0.5), (zk.y + zc.y) * R(0.5)};
+      const cplx<R> od = {(zk.x - zc.x) * R(0.5), (zk.y - zc.y) * R(0.5)};
+      const cplx<R> t = cmul<R>(od, twq<R>(q, kk << lstep, logL, -1));
+      return cplx<R>{ev.x + t.y, ev.y - t.x};  // ev - i t
+    };
+    buf[rb + k] = bin(a, cconj<R>(b), k);
+    if (m != k) buf[rb + m] = bin(b, cconj<R>(a), m);
+  }
+  __syncthreads();
+  lds_fft<R, kWholeThreads, kWholePerThread>(buf, n1, logn1, S, -1, q, logL, cols);
+  cplx<R> *dst = spec + static_cast<long long>(blockIdx.x) * n1 * S;
+  for (int e = threadIdx.x; e < n1 * S; e += kWholeThreads) dst[e] = buf[cols(e)];
+}
+
+template <typename R>
+__global__ __launch_bounds__(kWholeThreads) void ifft_whole_kernel(
+    const cplx<R> *__restrict__ spec, R *__restrict__ out, const R *__restrict__ add, int logn1,
+    int logNh, int logL, R scale, const cplx<R> *__restrict__ tw) {
+  extern __shared__ unsigned char smem_raw[];
+  cplx<R> *buf = reinterpret_cast<cplx<R> *>(smem_raw);
+  const int n1 = 1 << logn1, Nh = 1 << logNh, S = Nh + 1;
+  cplx<R> *q = buf + n1 * S;
+  load_quarter<R, kWholeThreads>(q, logL, tw);
+  const RowSlots rows{S, logNh};
+  const ColumnSlots cols{S, logn1};
+  const cplx<R> *src = spec + static_cast<long long>(blockIdx.x) * n1 * S;
+  cplx<R> v[kWholePerThread + 1];
+#pragma unroll
+  for (int i = 0; i <= kWholePerThread; ++i)
+    v[i] = src[min(static_cast<int>(threadIdx.x) + i * kWholeThreads, n1 * S - 1)];
+#pragma unroll
+  for (int i = 0; i <= kWholePerThread; ++i)
+    buf[cols(min(static_cast<int>(threadIdx.x) + i * kWholeThreads, n1 * S - 1))] = v[i];
+  __syncthreads();
+  lds_fft<R, kWholeThreads, kWholePerThread>(buf, n1, logn1, S, +1, q, logL, cols);
+  // pair (k, Nh - k) of each row
+  const int lstep = kTwiddleLog - logNh - 1;  // 4096 / n3 = 2^lstep
+  const int half = Nh / 2 + 1;
+  for (int e = threadIdx.x; e < n1 * half; e += kWholeThreads) {
+    const int k = e >> logn1, rb = (e & (n1 - 1)) * S;
+    if (k == 0) {
+      const R y0 = buf[rb].x, yn = buf[rb + Nh].x;
+      buf[rb] = cplx<R>{y0 + yn, y0 - yn};
+    } else {
+      const int m = Nh - k;
+      const cplx<R> yk = buf[rb + k], ym = buf[rb + m];
+      const cplx<R> a1 = cadd<R>(yk, cconj<R>(ym));
+      const cplx<R> b1 = cmul<R>(csub<R>(yk, cconj<R>(ym)), twq<R>(q, k << lstep, logL, +1));
+      buf[rb + k] = cplx<R>{a1.x - b1.y, a1.y + b1.x};
+      if (m != k) {
+        const cplx<R> a2 = cadd<R>(ym, cconj<R>(yk));
+        const cplx<R> b2 = cmul<R>(csub<R>(ym, cconj<R>(yk)), twq<R>(q, m << lstep, logL, +1));
+        buf[rb + m] = cplx<R>{a2.x - b2.y, a2.y + b2.x};
+      }
+    }
+  }
+  __syncthreads();
+  lds_fft<R, kWholeThreads, kWholePerThread>(buf, Nh, logNh, n1, +1, q, logL, rows);
+  const long long o = static_cast<long long>(blockIdx.x) * n1 * Nh;
+  cplx<R> *dst = reinterpret_cast<cplx<R> *>(out) + o;
+  const cplx<R> *addp = add ? reinterpret_cast<const cplx<R> *>(add) + o : nullptr;
+  for (int e = threadIdx.x; e < n1 * Nh; e += kWholeThreads) {
+    cplx<R> z = buf[rows(e)];
+    z.x *= scale;
+    z.y *= scale;
+    if (addp) {
+      z.x += addp[e].x;
+      z.y += addp[e].y;
+    }
+    dst[e] = z;
   }
 }
 
@@ -547,10 +678,29 @@ hipError_t cfft_launch(const void *src, void *dst, long long nrows, int n, int d
   });
 }
 
+// LDS of a whole-field transform, 0 where the field does not fit one work-group: up to
+// kWholeThreads kWholePerThread points in the longer of its two stages, and 64 KB (the
+// largest fields that fit, 64^2 in float64, are where both forms cost the same time on
+// the device; one work-group on a larger field would be slower than many on its rows).
+template <typename R>
+size_t whole_lds(int n1, int n3, int &logL) {
+  const int S = n3 / 2 + 1;
+  logL = ilog2(std::max(n1, n3));
+  const size_t lds = (static_cast<size_t>(n1) * S + (size_t(1) << (logL - 2))) * sizeof(cplx<R>);
+  return n1 * S <= kWholeThreads * kWholePerThread && lds <= 64 * 1024 ? lds : 0;
+}
+
 template <typename Rin, typename R>
 hipError_t forward_impl(const void *in, void *spec, int F, int n1, int n3, const void *tw,
-                        hipStream_t st) {
+                        bool whole, hipStream_t st) {
   const int Nh = n3 / 2, h3 = Nh + 1;
+  int logL;
+  if (const size_t lds = whole ? whole_lds<R>(n1, n3, logL) : 0) {
+    hipLaunchKernelGGL((fft_whole_kernel<Rin, R>), dim3(static_cast<unsigned>(F)), dim3(kWholeThreads),
+                       lds, st, static_cast<const Rin *>(in), static_cast<cplx<R> *>(spec), ilog2(n1),
+                       ilog2(Nh), logL, static_cast<const cplx<R> *>(tw));
+    return hipGetLastError();
+  }
   const int rows = tile_rows(n1, Nh, sizeof(cplx<R>), 0);
   const int ntiles = F * (n1 / rows);
   hipError_t e = with_maxv(rows * Nh, [&](auto mv) {
@@ -569,8 +719,16 @@ hipError_t forward_impl(const void *in, void *spec, int F, int n1, int n3, const
 
 template <typename R>
 hipError_t inverse_impl(const void *spec, void *scratch, void *out, const void *add, int F, int n1,
-                        int n3, double scale, const void *tw, hipStream_t st) {
+                        int n3, double scale, const void *tw, bool whole, hipStream_t st) {
   const int Nh = n3 / 2, h3 = Nh + 1;
+  int logL;
+  if (const size_t lds = whole ? whole_lds<R>(n1, n3, logL) : 0) {
+    hipLaunchKernelGGL((ifft_whole_kernel<R>), dim3(static_cast<unsigned>(F)), dim3(kWholeThreads), lds,
+                       st, static_cast<const cplx<R> *>(spec), static_cast<R *>(out),
+                       static_cast<const R *>(add), ilog2(n1), ilog2(Nh), logL, static_cast<R>(scale),
+                       static_cast<const cplx<R> *>(tw));
+    return hipGetLastError();
+  }
   hipError_t e = cfft_launch<R>(spec, scratch, static_cast<long long>(F) * h3, n1, +1, tw, st);
   if (e != hipSuccess) return e;
   const int rows = tile_rows(n1, Nh, sizeof(cplx<R>), 1);
@@ -592,16 +750,16 @@ hipError_t inverse_impl(const void *spec, void *scratch, void *out, const void *
 }  // namespace
 
 hipError_t launch_fft_forward(bool in_fp64, const void *in, void *spec, int F, int n1, int n3,
-                              const void *tw64, hipStream_t st) {
-  return in_fp64 ? forward_impl<double, double>(in, spec, F, n1, n3, tw64, st)
-                 : forward_impl<float, double>(in, spec, F, n1, n3, tw64, st);
+                              const void *tw64, bool whole, hipStream_t st) {
+  return in_fp64 ? forward_impl<double, double>(in, spec, F, n1, n3, tw64, whole, st)
+                 : forward_impl<float, double>(in, spec, F, n1, n3, tw64, whole, st);
 }
 
 hipError_t launch_fft_inverse(bool fp64, const void *spec, void *scratch, void *out,
                               const void *add, int F, int n1, int n3, double scale, const void *tw,
-                              hipStream_t st) {
-  return fp64 ? inverse_impl<double>(spec, scratch, out, add, F, n1, n3, scale, tw, st)
-              : inverse_impl<float>(spec, scratch, out, add, F, n1, n3, scale, tw, st);
+                              bool whole, hipStream_t st) {
+  return fp64 ? inverse_impl<double>(spec, scratch, out, add, F, n1, n3, scale, tw, whole, st)
+              : inverse_impl<float>(spec, scratch, out, add, F, n1, n3, scale, tw, whole, st);
 }
 
 // Twiddles exp(-2 pi i m / 4096), m = 0..4095, from long-double sin/cos on the host.

@@ -94,6 +94,7 @@ struct sbim_handle {
   long long step = 0;             // pushes done
   long long bstep = 0;            // backward calls done
   int depth = 1;                  // sweep depth: steps served by one pass over a block's history
+  bool in_order = false;          // drives a fault or strip in float32: sums and transforms keep their rounding
   bool mfma = false;              // history sweep on the matrix cores (quads of one class)
   bool tiled = false;             // ... in the time-tiled form (quads.hip), else in lag order (pairs.hip)
   int quad_modes = 4;             // time-tiled form: sorted positions that share a kernel row (2 or 4)
@@ -118,13 +119,14 @@ namespace sbim {
 // fft.hip: fields [F][n1][n3] real <-> spectrum [F][n3/2+1][n1] complex.
 // The forward transform always computes in float64 (its output feeds the
 // float64 running state); in_fp64 selects the type of the input field.
+// whole: a field that fits one work-group may be transformed in one launch.
 hipError_t launch_fft_forward(bool in_fp64, const void *in, void *spec, int F, int n1, int n3,
-                              const void *tw64, hipStream_t st);
+                              const void *tw64, bool whole, hipStream_t st);
 // out = scale * inverse(spec) + add_or_null; spec is left intact, `scratch`
 // (the size of spec) receives the intermediate transform.
 hipError_t launch_fft_inverse(bool fp64, const void *spec, void *scratch, void *out,
                               const void *add_or_null, int F, int n1, int n3, double scale,
-                              const void *tw, hipStream_t st);
+                              const void *tw, bool whole, hipStream_t st);
 hipError_t upload_twiddles(bool fp64, void *dst, hipStream_t st);
 
 // kernels.hip

@@ -464,7 +464,7 @@ int check_ptr(sbim_handle *h, const void *p, const char *name) {
 // Forward real 2-D FFT of a [P][3][n1][n3] field into `spec`.
 hipError_t fft_forward(sbim_handle *h, const void *field, void *spec) {
   return sbim::launch_fft_forward(h->fp64, field, spec, h->cfg.nplanes * 3, h->n1, h->n3,
-                                  h->twiddle64, h->stream);
+                                  h->twiddle64, !h->in_order, h->stream);
 }
 
 // Inverse of a traction spectrum (destroyed) into a [P][3][n1][n3] field.
@@ -473,7 +473,7 @@ hipError_t fft_inverse(sbim_handle *h, const void *spec, void *scratch, void *fi
   return sbim::launch_fft_inverse(h->fp64, spec, scratch, field, add, h->cfg.nplanes * 3, h->n1,
                                   h->n3,
                                   1.0 / (static_cast<double>(h->n1) * h->n3), h->twiddle,
-                                  h->stream);
+                                  !h->in_order, h->stream);
 }
 
 // Adjoint buffers of every group, allocated and cleared on first use.  A group
@@ -806,9 +806,12 @@ int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, vo
 // The in-order form for a float32 handle that will drive a fault or a strip: the
 // stick/slip state follows the rounding of the history sums from step to step, so the
 // order of the sums is part of those results.  The handle is at step 0: it is planned
-// again, all but its kernel tables.  Handles whose adjoint has been used
+// again, all but its kernel tables.  For the same reason its transforms keep the
+// two-kernel form (the compiler fuses multiply-adds differently in the whole-field one).
+// Handles whose adjoint has been used
 // (their adjoint history would be lost) keep the form they have.
 int keep_sum_order(sbim_handle *h) {
+  h->in_order = !h->fp64;
   if (h->fp64 || !h->tiled) return SBIM_OK;
   for (int i = 0; i < h->ngroups; ++i)
     if (h->g[i].state_adj) return SBIM_OK;

@@ -19,6 +19,7 @@
 //           one history slot of a run is contiguous;
 //   table   class-major rows: entry cls_off[class] + j holds (w11, w12, w22, w33)
 //           of lag j, j < W of the class.
+#include <algorithm>
 #include <cmath>
 
 #include "step_items.h"
@@ -46,6 +47,12 @@ template <typename R, int S, int T, bool COMP> constexpr int sweep_lag_groups() 
   if (S == 6 && T == 1) return 1;
   return (COMP || sizeof(R) == 8 || T > 1) ? 2 : 4;
 }
+
+// Wavefronts of a work-group that share one sweep item of a long block (8: 64^2 35 us a
+// step against 31, 16^2 with 1600 lags 29 against 33; float64), and the window from
+// which a block is long (256^2 x 2 float64, windows per mode up to 300: 24 52 us, 48 54,
+// 96 61).
+constexpr int kSplit = 4, kLongWindow = 24;
 
 // Rows k0 .. k0+S-1 of a mode's kernel.  A class's W rows are followed by a
 // zero row, so clamping the lag to W gives zero from the window on.
@@ -123,8 +130,11 @@ __device__ __forceinline__ void sweep_span(R (&sums)[S][kSums], const typename W
 // fetches LG segments of Q x 8 bytes (float32), one per chunk.  The chunks
 // are then summed by a butterfly over lanes l ^ QT, l ^ 2QT, ... (fixed
 // order, so the result is bitwise reproducible).
-template <typename R, int S, int T, bool COMP>
-__device__ __forceinline__ void sweep_item(const SweepArgs &a, long long item) {
+// SPLIT: the item is shared by a work-group of kSplit wavefronts: each takes LG of
+// kSplit LG chunks, and the wavefronts' sums meet in LDS, one step at a time, in order.
+template <typename R, int S, int T, bool COMP, bool SPLIT>
+__device__ __forceinline__ void sweep_item(const SweepArgs &a, long long kb, int r) {
+  constexpr int NW = SPLIT ? kSplit : 1;
   using W = typename W4<R>::T;
   const cplx<R> *__restrict__ ring = static_cast<const cplx<R> *>(a.ring);
   const W *__restrict__ table = static_cast<const W *>(a.table);
@@ -135,16 +145,10 @@ __device__ __forceinline__ void sweep_item(const SweepArgs &a, long long item) {
   constexpr int Q = kLanes / (LG * T);  // modes per item
   constexpr int NQ = kLanes / Q;        // items per block and plane
   constexpr int D = S * T;
-  // Items of one block get ids congruent mod 8, so they run on one XCD and
-  // share the block's kernel rows in its L2.
-  const int per_blk = NQ * np;
-  const long long kb = (item / (8LL * per_blk)) * 8 + (item & 7);
-  if (kb >= a.nphase) return;
-  const int r = static_cast<int>((item >> 3) % per_blk);
   const int p = r / NQ;
   const long long t0 = step + 1;
   const long long b = t0 % D + D * kb;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & (kLanes - 1), wave = SPLIT ? static_cast<int>(threadIdx.x) / kLanes : 0;
   const int lg = lane / (Q * T);
   const int u0 = (lane / Q) % T * S;        // first of the lane's S steps (t0 + u0 ..)
   const int col = (r % NQ) * Q + lane % Q;  // lane of the mode in its block
@@ -155,8 +159,8 @@ __device__ __forceinline__ void sweep_item(const SweepArgs &a, long long item) {
   // history entries (lags 2 .. min(cap-1, t0) of step t0) that the window can reach
   const int nent = static_cast<int>(max(0LL, min(static_cast<long long>(cap) - 1, t0) - 1));
   const int wl = valid ? a.win[sm] : 0;
-  const int per = (nent + LG * S - 1) / (LG * S) * S;  // lags per chunk
-  const int i0 = 2 + lg * per;
+  const int per = (nent + NW * LG * S - 1) / (NW * LG * S) * S;  // lags per chunk
+  const int i0 = 2 + (wave * LG + lg) * per;
 
   constexpr int G = sweep_group<R, S, COMP>();
   // plain form: the running sums; compensated form: the products since the
@@ -215,7 +219,24 @@ __device__ __forceinline__ void sweep_item(const SweepArgs &a, long long item) {
     for (int k = 0; k < kSums; ++k)
 #pragma unroll
       for (int off = Q * T; off < kLanes; off <<= 1) acc[s][k].fold_lane(off);
-    if (lg == 0 && valid) {
+    if constexpr (SPLIT) {
+      using A = Acc<R, COMP>;
+      __shared__ __attribute__((aligned(16))) unsigned char lds[sizeof(A) * kSums * NW * Q * T];
+      auto part = reinterpret_cast<A(*)[NW][Q * T]>(lds);
+      if (lg == 0) {
+#pragma unroll
+        for (int k = 0; k < kSums; ++k) part[k][wave][lane] = acc[s][k];
+      }
+      __syncthreads();
+      if (wave == 0 && lg == 0) {
+#pragma unroll
+        for (int k = 0; k < kSums; ++k)
+#pragma unroll
+          for (int w = 1; w < NW; ++w) acc[s][k].fold(part[k][w][lane]);
+      }
+      __syncthreads();
+    }
+    if (wave == 0 && lg == 0 && valid) {
 #pragma unroll
       for (int t = 0; t < 5; ++t)
         pending[((slot * np + p) * 5 + t) * M + sm] =
@@ -233,7 +254,11 @@ __device__ __forceinline__ void step_items(const SweepArgs &sa, const ModeArgs &
                                            long long sweep_items, long long nblocks) {
   const long long item = blockIdx.x;
   if (item < sweep_items) {
-    sweep_item<R, S, T, COMP>(sa, item);
+    // Items of one block get ids congruent mod 8, so they run on one XCD and
+    // share the block's kernel rows in its L2.
+    const int per_blk = sweep_lag_groups<R, S, T, COMP>() * T * sa.np;
+    const long long kb = (item / (8LL * per_blk)) * 8 + (item & 7);
+    if (kb < sa.nphase) sweep_item<R, S, T, COMP, false>(sa, kb, static_cast<int>((item >> 3) % per_blk));
     return;
   }
   const long long k = xcd_chunk(item - sweep_items, nblocks * ma.np);
@@ -264,6 +289,38 @@ template <typename R, int S, int T, bool COMP>
 __global__ __launch_bounds__(kLanes) __attribute__((amdgpu_waves_per_eu(2))) void step_kernel_w2(
     SweepArgs sa, ModeArgs ma, long long sweep_items, long long nblocks) {
   step_items<R, S, T, COMP>(sa, ma, sweep_items, nblocks);
+}
+
+// The same with work-groups of kSplit wavefronts, for launches that would wait for the
+// chain of lags of their long blocks (each chunk's lags come one load group after the
+// other): first the `nlong` long blocks of the phase, the item of one (block, plane,
+// group of modes) shared by a work-group; then the others, one item per wavefront; then
+// the mode items.  (Float64, window in lags: 64^2 at 100 38.5 -> 31.4 us a step, 16^2 at
+// 1600 75 -> 33; windows per mode, 256^2 x 2 90 -> 51, 1024^2 343 -> 184.)
+template <typename R, int S, int T, bool COMP>
+__global__ __launch_bounds__(kSplit * kLanes) __attribute__((amdgpu_waves_per_eu(2))) void
+step_kernel_split(SweepArgs sa, ModeArgs ma, long long long_wgs, long long sweep_wgs, long long nlong,
+                  long long nblocks) {
+  const long long wg = blockIdx.x;
+  const int wave = static_cast<int>(threadIdx.x) / kLanes;
+  const int per_blk = sweep_lag_groups<R, S, T, COMP>() * T * sa.np;
+  if (wg < long_wgs) {
+    const long long kb = (wg / (8LL * per_blk)) * 8 + (wg & 7);
+    if (kb < nlong) sweep_item<R, S, T, COMP, true>(sa, kb, static_cast<int>((wg >> 3) % per_blk));
+    return;
+  }
+  if (wg < sweep_wgs) {
+    const long long j = wg - long_wgs;
+    const long long kb = nlong + ((j / (8LL * per_blk)) * 8 + (j & 7)) * kSplit + wave;
+    if (kb < sa.nphase) sweep_item<R, S, T, COMP, false>(sa, kb, static_cast<int>((j >> 3) % per_blk));
+    return;
+  }
+  const long long n = nblocks * ma.np;
+  const long long k = xcd_chunk(wg - sweep_wgs, (n + kSplit - 1) / kSplit) * kSplit + wave;
+  if (k >= n) return;
+  const int p = static_cast<int>(k / nblocks);
+  const long long s = (k - p * nblocks) * kLanes + threadIdx.x % kLanes;
+  if (s < ma.M) mode_step<R, COMP, false>(ma, p, s);
 }
 
 // -------------------------------------------------------------- tabulate
@@ -424,6 +481,39 @@ hipError_t step_launch_s(const sbim_handle *h, const Group &g, const SweepArgs &
   if (ev0) {
     const hipError_t e = hipEventRecord(ev0, h->stream);
     if (e != hipSuccess) return e;
+  }
+  // Long blocks are split over wavefronts where the launch would wait for one of them: a
+  // lag of a chain takes about 0.33 us, a mode and plane of the whole launch 0.13 ns on a
+  // full chip.  So, with windows per mode, above one lag of the longest window per 2500
+  // modes and planes (compensated, unsplit against split: 2048^2 x 2 at 400 lags 763 and
+  // 830 us a step, 2048^2 x 2 at 2000 913 and 829, 1024^2 at 300 184 and 125); with one
+  // window, while the sweep has at most a wavefront per CU (float64: 256^2 at 60 lags 49
+  // and 37 us, 512^2 at 40 65 and 65) and lags enough (128^2 x 2 at 12 29 and 30).
+  // A handle that sums in order keeps its chains whole.
+  if constexpr (S == 6 || (S * T == 8 && sizeof(R) == 4 && !COMP)) {
+    const int per_blk = sweep_lag_groups<R, S, T, COMP>() * T * g.np;
+    long long nlong = 0;
+    if (h->cfg.window_mode == SBIM_W_PER_MODE) {
+      if (g.wmax * 2500LL > g.M * g.np) {  // (blocks stand in order of falling window)
+        const long long all = std::partition_point(g.h_blk_cap.begin(), g.h_blk_cap.end(),
+                                                   [](int cap) { return cap > kLongWindow; }) -
+                              g.h_blk_cap.begin();
+        nlong = all > phase ? (all - phase + D - 1) / D : 0;
+      }
+    } else if (g.wmax >= 20 && sa.nphase * per_blk <= 256) {
+      nlong = sa.nphase;
+    }
+    if (nlong > 0 && !h->in_order) {
+      const long long long_wgs = (nlong + 7) / 8 * 8 * per_blk;
+      const long long rest = (sa.nphase - nlong + kSplit - 1) / kSplit;
+      const long long sweep_wgs = long_wgs + (rest + 7) / 8 * 8 * per_blk;
+      const long long wgs = sweep_wgs + xcd_chunk_ids((g.nblocks * g.np + kSplit - 1) / kSplit);
+      hipLaunchKernelGGL((step_kernel_split<R, S, T, COMP>), dim3(static_cast<unsigned>(wgs)),
+                         dim3(kSplit * kLanes), 0, h->stream, sa, ma, long_wgs, sweep_wgs, nlong,
+                         g.nblocks);
+      const hipError_t e = hipGetLastError();
+      return e == hipSuccess && ev1 ? hipEventRecord(ev1, h->stream) : e;
+    }
   }
   if constexpr (!COMP && sizeof(R) == 4 && S == 6 && T == 2)
     hipLaunchKernelGGL((step_kernel_w4<R, S, T, COMP>), dim3(static_cast<unsigned>(items)),

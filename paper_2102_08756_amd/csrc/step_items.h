@@ -43,6 +43,7 @@ template <typename R> struct Acc<R, false> {
   R s = R(0);
   __device__ __forceinline__ void fold(R x) { s += x; }
   __device__ __forceinline__ R value() const { return s; }
+  __device__ __forceinline__ void fold(const Acc &a) { s += a.s; }
   // add the accumulator of the lane `off` lanes away (butterfly reduction)
   __device__ __forceinline__ void fold_lane(int off) { s += __shfl_xor(s, off); }
 };
@@ -56,6 +57,10 @@ template <> struct Acc<float, true> {
     s = t;
   }
   __device__ __forceinline__ float value() const { return s + c; }
+  __device__ __forceinline__ void fold(const Acc &a) {
+    neumaier(s, c, a.s);
+    c += a.c;
+  }
   __device__ __forceinline__ void fold_lane(int off) {
     const float s2 = __shfl_xor(s, off);
     const float c2 = __shfl_xor(c, off);

@@ -101,6 +101,84 @@ __device__ __forceinline__ void sweep_span(R (&sums)[S][kSums], const typename W
   }
 }
 
+// History staged through LDS (float32, 6 steps a lane, two lanes and two lag chunks a
+// mode): a stage is the two spans of one pass of the sweep's loop, kStageLags lags of each
+// chunk.  A (lag, component) of it is 2 chunks x 16 modes x 8 bytes, contiguous per chunk,
+// which 16 lanes fetch in 16-byte pieces straight into LDS, so a stage takes 9 loads of
+// 1 KB and no registers, where the lanes' own loads took 36 of 512 bytes, half of them
+// fetched twice.
+constexpr int kStageLags = 12;
+constexpr int kStageLoads = kStageLags * 3 / 4;
+constexpr int kStageBytes = kStageLoads * 1024;
+typedef __attribute__((address_space(3))) void *lds_ptr;
+
+// Fetches a stage into the LDS at `dst`: piece is the byte offset of the lane's 16 bytes
+// of component 0 in a slot, x0 the slot of its chunk's first lag (cap >= kStageLags: one
+// wrap at most).  Buffer loads: 32-bit offsets from the block's first slot.  (The compiler
+// takes the global form for one that may touch LDS through a flat address, and then waits
+// for every load in flight wherever it needs one.)
+__device__ __forceinline__ void fetch_stage(__amdgpu_buffer_rsrc_t ring, unsigned piece, int x0, int cap,
+                                            unsigned slot_bytes, lds_ptr dst) {
+  int e = (threadIdx.x & 63) / 16;  // the lane's (lag, component) of the first load
+  asm volatile("" : "+v"(e));       // (opaque: not kept per load through the caller's loop)
+  int x = x0 - (e == 3), c = e == 3 ? 0 : e;
+  x += x < 0 ? cap : 0;
+#pragma unroll
+  for (int i = 0; i < kStageLoads; ++i) {
+    // (non-temporal, as in sweep_span)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+        ring, (__attribute__((address_space(3))) char *)dst + i * 1024, 16,
+        static_cast<int>(static_cast<unsigned>(x) * slot_bytes + static_cast<unsigned>(c * (kLanes * 8)) + piece),
+        0, 0, 2);
+    __builtin_amdgcn_sched_barrier(0);  // (one address at a time)
+    // four further on: the next lag's next component
+    const bool carry = c == 2;
+    x -= carry ? 2 : 1;
+    x += x < 0 ? cap : 0;
+    c = carry ? 0 : c + 1;
+  }
+}
+
+// Lags L and L + 1 of a stage, all components, of the lane's chunk and mode (at byte `at`
+// of the LDS).  WAIT: the stage's loads are complete once no more than kStageLoads
+// younger ones are outstanding; the loads of the next stage are issued before this.
+template <int L, bool WAIT>
+__device__ __forceinline__ void read_stage(float2 (&u)[2][3], unsigned at) {
+  if constexpr (WAIT)
+    asm volatile("s_waitcnt vmcnt(9)" ::: "memory");
+  static_assert(kStageLoads == 9, "the wait above");
+  asm volatile("ds_read_b64 %0, %6 offset:%7\n\t"
+               "ds_read_b64 %1, %6 offset:%8\n\t"
+               "ds_read_b64 %2, %6 offset:%9\n\t"
+               "ds_read_b64 %3, %6 offset:%10\n\t"
+               "ds_read_b64 %4, %6 offset:%11\n\t"
+               "ds_read_b64 %5, %6 offset:%12\n\t"
+               "s_waitcnt lgkmcnt(0)"
+               : "=&v"(u[0][0]), "=&v"(u[0][1]), "=&v"(u[0][2]), "=&v"(u[1][0]), "=&v"(u[1][1]),
+                 "=&v"(u[1][2])
+               : "v"(at), "n"((3 * L) * 256), "n"((3 * L + 1) * 256), "n"((3 * L + 2) * 256),
+                 "n"((3 * L + 3) * 256), "n"((3 * L + 4) * 256), "n"((3 * L + 5) * 256)
+               : "memory");
+}
+
+// sweep_span (S = 6) on a staged history: H = 0, 1 the first or second span of the stage.
+template <int H>
+__device__ __forceinline__ void sweep_span_staged(float (&sums)[6][kSums], const float4 (&A)[6],
+                                                  const float4 (&B)[6], unsigned at) {
+  static_for<3>([&](auto gc) {
+    constexpr int g0 = 2 * decltype(gc)::value;
+    float2 u[2][3];
+    read_stage<6 * H + g0, H == 0 && g0 == 0>(u, at);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int s = 0; s < 6; ++s) {
+        const int k = g0 + t + s;
+        fma_lag<float>(sums[s], k < 6 ? A[k] : B[k - 6], u[t]);
+      }
+  });
+}
+
 // The sweep launched with step n serves steps t0 = n+1 .. n+D (depth D = S T).
 // Blocks of phase t0 mod D read their history up to step n-1 once, U^{t0-i}
 // for i = 2 .. min(cap-1, t0), and form for each of those steps t0+u its sum
@@ -132,7 +210,8 @@ __device__ __forceinline__ void sweep_span(R (&sums)[S][kSums], const typename W
 // order, so the result is bitwise reproducible).
 // SPLIT: the item is shared by a work-group of kSplit wavefronts: each takes LG of
 // kSplit LG chunks, and the wavefronts' sums meet in LDS, one step at a time, in order.
-template <typename R, int S, int T, bool COMP, bool SPLIT>
+// STAGED: the history comes through LDS (fetch_stage; cap >= kStageLags).
+template <typename R, int S, int T, bool COMP, bool SPLIT, bool STAGED = false>
 __device__ __forceinline__ void sweep_item(const SweepArgs &a, long long kb, int r) {
   constexpr int NW = SPLIT ? kSplit : 1;
   using W = typename W4<R>::T;
@@ -185,13 +264,48 @@ __device__ __forceinline__ void sweep_item(const SweepArgs &a, long long kb, int
     const W *rowp = wl > 0 ? table + a.row0[sm] : table + a.cls_w0;
     W ra[S], rb[S];
     load_rows<R, S>(ra, rowp, i0 + u0, wl);
+    // staged history: this lane's piece, its slot, and the stage of the LDS in use
+    extern __shared__ __attribute__((aligned(16))) unsigned char stages[];
+    __amdgpu_buffer_rsrc_t ring_rsrc;
+    unsigned piece = 0;
+    int xs = 0, half = 0;
+    const unsigned slot_bytes = static_cast<unsigned>(dstep) * static_cast<unsigned>(sizeof(cplx<R>));
+    if constexpr (STAGED) {
+      static_assert(sizeof(R) == 4 && S == 6 && T == 2 && LG == 2 && Q == 16, "layout of a stage");
+      const int chunk = lane % 16 / 8;
+      xs = mod_step(t0, cap) - (2 + chunk * per) % cap;
+      if (xs < 0) xs += cap;
+      piece = static_cast<unsigned>((p * 3 * kLanes + (r % NQ) * Q) * 8 + lane % 8 * 16);
+      ring_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<cplx<R> *>(ring + uniform64(a.blk_off[b]) * rec_len), 0,
+          __builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<unsigned>(cap - 1) * slot_bytes +
+                                                          static_cast<unsigned>(rec_len) * 8u)),
+          kBufferWord3);
+      fetch_stage(ring_rsrc, piece, xs, cap, slot_bytes, (lds_ptr)stages);
+    }
     for (int it = 0; it < per; it += 2 * S) {
       const int i = i0 + u0 + it;
       load_rows<R, S>(rb, rowp, i + S, wl);
-      sweep_span<R, S, G>(sums, ra, rb, hp, x, cap, dstep, dwrap);
+      unsigned at = 0;
+      if constexpr (STAGED) {
+        __builtin_amdgcn_sched_barrier(0);  // (the rows first: waiting for them must not wait for the stage)
+        // the next stage (past the last one: entries of the ring that nothing uses)
+        xs -= kStageLags;
+        xs += xs < 0 ? cap : 0;
+        at = static_cast<unsigned>(reinterpret_cast<__SIZE_TYPE__>((lds_ptr)stages)) +
+             static_cast<unsigned>(half * kStageBytes + lg * 128 + lane % Q * 8);
+        half ^= 1;
+        fetch_stage(ring_rsrc, piece, xs, cap, slot_bytes, (lds_ptr)(stages + half * kStageBytes));
+        sweep_span_staged<0>(sums, ra, rb, at);
+      } else {
+        sweep_span<R, S, G>(sums, ra, rb, hp, x, cap, dstep, dwrap);
+      }
       if (it + S >= per) break;
       load_rows<R, S>(ra, rowp, i + 2 * S, wl);
-      sweep_span<R, S, G>(sums, rb, ra, hp, x, cap, dstep, dwrap);
+      if constexpr (STAGED)
+        sweep_span_staged<1>(sums, rb, ra, at);
+      else
+        sweep_span<R, S, G>(sums, rb, ra, hp, x, cap, dstep, dwrap);
       // compensated form: fold the plain partial sums of the last 6S lags
       // (every third pass of this loop; the branch is uniform over the wavefront)
       if constexpr (COMP) {
@@ -206,6 +320,8 @@ __device__ __forceinline__ void sweep_item(const SweepArgs &a, long long kb, int
         }
       }
     }
+    // the stage fetched past the last one must not land in LDS that has a new owner
+    if constexpr (STAGED) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
 #pragma unroll
   for (int s = 0; s < S; ++s)
@@ -249,7 +365,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs &a, long long kb, int
 // turn it is, then one mode item per (64-mode block, plane).  The two kinds
 // share no data (see sweep_item), so the latency-bound push gathers and
 // traction scatters run beside the streaming sweep.
-template <typename R, int S, int T, bool COMP>
+template <typename R, int S, int T, bool COMP, bool STAGED = false>
 __device__ __forceinline__ void step_items(const SweepArgs &sa, const ModeArgs &ma,
                                            long long sweep_items, long long nblocks) {
   const long long item = blockIdx.x;
@@ -258,7 +374,7 @@ __device__ __forceinline__ void step_items(const SweepArgs &sa, const ModeArgs &
     // share the block's kernel rows in its L2.
     const int per_blk = sweep_lag_groups<R, S, T, COMP>() * T * sa.np;
     const long long kb = (item / (8LL * per_blk)) * 8 + (item & 7);
-    if (kb < sa.nphase) sweep_item<R, S, T, COMP, false>(sa, kb, static_cast<int>((item >> 3) % per_blk));
+    if (kb < sa.nphase) sweep_item<R, S, T, COMP, false, STAGED>(sa, kb, static_cast<int>((item >> 3) % per_blk));
     return;
   }
   const long long k = xcd_chunk(item - sweep_items, nblocks * ma.np);
@@ -289,6 +405,19 @@ template <typename R, int S, int T, bool COMP>
 __global__ __launch_bounds__(kLanes) __attribute__((amdgpu_waves_per_eu(2))) void step_kernel_w2(
     SweepArgs sa, ModeArgs ma, long long sweep_items, long long nblocks) {
   step_items<R, S, T, COMP>(sa, ma, sweep_items, nblocks);
+}
+
+// The float32 sweep with staged history.  Its wavefronts are few (two a SIMD), and their
+// own loads kept too little in flight to cover the memory's latency; the stage of the next
+// 12 lags is in flight while the current one is summed, without registers.  Now bound by
+// the multiply-adds and the last, partly filled round of wavefronts.  A rupture step, one
+// plane, us: 1024^2 compensated at 2000 lags 978 -> 790, 512^2 at
+// 1000 226 -> 160, 128^2 at 300 77 -> 57, 64^2 at 100 38 -> 38; float32 512^2 at 1600 341
+// -> 207.  (Fetching a stage in two halves, or its offsets by subtraction: the same.)
+template <bool COMP>
+__global__ __launch_bounds__(kLanes) __attribute__((amdgpu_waves_per_eu(2))) void step_kernel_staged(
+    SweepArgs sa, ModeArgs ma, long long sweep_items, long long nblocks) {
+  step_items<float, 6, 2, COMP, true>(sa, ma, sweep_items, nblocks);
 }
 
 // The same with work-groups of kSplit wavefronts, for launches that would wait for the
@@ -511,6 +640,18 @@ hipError_t step_launch_s(const sbim_handle *h, const Group &g, const SweepArgs &
       hipLaunchKernelGGL((step_kernel_split<R, S, T, COMP>), dim3(static_cast<unsigned>(wgs)),
                          dim3(kSplit * kLanes), 0, h->stream, sa, ma, long_wgs, sweep_wgs, nlong,
                          g.nblocks);
+      const hipError_t e = hipGetLastError();
+      return e == hipSuccess && ev1 ? hipEventRecord(ev1, h->stream) : e;
+    }
+  }
+  if constexpr (sizeof(R) == 4 && S == 6 && T == 2) {
+    // Staged history: windows of a few stages or more (one window: every block's is the
+    // same), a block's ring within 32-bit byte offsets (its slots are at most a phase's
+    // blocks apart).  Never slower (step_kernel_staged).
+    const double block_span = static_cast<double>(g.wmax) * ((g.nblocks + D - 1) / D) * g.np * 3 * kLanes * 8;
+    if (h->cfg.window_mode == SBIM_W_FIXED && g.wmax >= 64 && block_span < 4.29e9) {
+      hipLaunchKernelGGL((step_kernel_staged<COMP>), dim3(static_cast<unsigned>(items)), dim3(kLanes),
+                         2 * kStageBytes, h->stream, sa, ma, sweep_items, g.nblocks);
       const hipError_t e = hipGetLastError();
       return e == hipSuccess && ev1 ? hipEventRecord(ev1, h->stream) : e;
     }

@@ -617,19 +617,21 @@ hipError_t step_launch_s(const sbim_handle *h, const Group &g, const SweepArgs &
   // modes and planes (compensated, unsplit against split: 2048^2 x 2 at 400 lags 763 and
   // 830 us a step, 2048^2 x 2 at 2000 913 and 829, 1024^2 at 300 184 and 125); with one
   // window, while the sweep has at most a wavefront per CU (float64: 256^2 at 60 lags 49
-  // and 37 us, 512^2 at 40 65 and 65) and lags enough (128^2 x 2 at 12 29 and 30).
+  // and 37 us, 512^2 at 40 65 and 65) and lags enough so far (256 x 64: float32 at 20 lags
+  // 26.5 and 25.7, compensated at 28 29.2 and 30.7, at 34 31.5 and 31.0).
   // A handle that sums in order keeps its chains whole.
   if constexpr (S == 6 || (S * T == 8 && sizeof(R) == 4 && !COMP)) {
     const int per_blk = sweep_lag_groups<R, S, T, COMP>() * T * g.np;
+    const long long lags = std::min<long long>(g.wmax, sa.step + 1);  // of the longest chain so far
     long long nlong = 0;
     if (h->cfg.window_mode == SBIM_W_PER_MODE) {
-      if (g.wmax * 2500LL > g.M * g.np) {  // (blocks stand in order of falling window)
+      if (lags * 2500 > g.M * g.np) {  // (blocks stand in order of falling window)
         const long long all = std::partition_point(g.h_blk_cap.begin(), g.h_blk_cap.end(),
                                                    [](int cap) { return cap > kLongWindow; }) -
                               g.h_blk_cap.begin();
         nlong = all > phase ? (all - phase + D - 1) / D : 0;
       }
-    } else if (g.wmax >= 20 && sa.nphase * per_blk <= 256) {
+    } else if (lags >= (COMP ? 32 : 20) && sa.nphase * per_blk <= 256) {
       nlong = sa.nphase;
     }
     if (nlong > 0 && !h->in_order) {

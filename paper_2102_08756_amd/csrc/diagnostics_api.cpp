@@ -91,26 +91,45 @@ int sbim_get_info(const sbim_handle *h, sbim_info *out) {
 
 namespace {
 
-// A snapshot is the device memory as it lies, so its header tells the order of the modes.
-// Snapshots written before there was more than one order hold no mark: they are in lag order.
+// A snapshot is the device memory as it lies.  Its header says all that decides how: the
+// order of the modes, the padding of their classes, the size of its reals, the sweep depth
+// (which blocks lie together, how many pending sums); and its size.  Two earlier kinds
+// are told by their second word: one that names the order alone, and one without a mark,
+// in lag order with its pending sums as real arrays (those are formed again on loading).
 struct SnapshotHeader {
-  long long step, layout;
+  long long step, mark, bytes;
+  int order, quad, real, depth;
 };
-constexpr long long kLagOrder = 0x5342494d4c414730, kTimeTiled = 0x5342494d54494c30,
-                    kSpectrumOrder = 0x5342494d53504330;
+constexpr long long kFormMark = 0x5342494d464f524d;
+enum Order : int { kLagOrder = 0, kTimeTiled = 1, kSpectrumOrder = 2 };
+constexpr long long kOrderMark[3] = {0x5342494d4c414730, 0x5342494d54494c30, 0x5342494d53504330};
 
-long long layout_of(const sbim_handle *h) {
+Order order_of(const sbim_handle *h) {
   if (h->tiled) return kTimeTiled;
   return h->cfg.window_mode == SBIM_W_STATIC ? kSpectrumOrder : kLagOrder;
 }
 
-bool layout_fits(const sbim_handle *h, const SnapshotHeader &hd) {
-  const bool marked = hd.layout == kLagOrder || hd.layout == kTimeTiled || hd.layout == kSpectrumOrder;
-  return (marked ? hd.layout : kLagOrder) == layout_of(h);
+SnapshotHeader header_of(const sbim_handle *h, long long bytes) {
+  return {h->step, kFormMark, bytes, order_of(h), h->mfma ? h->quad_modes : 0,
+          static_cast<int>(h->rsize), h->depth};
 }
 
-hipError_t save_header(const sbim_handle *h, void *dst) {
-  const SnapshotHeader hd{h->step, layout_of(h)};
+bool marked(const SnapshotHeader &hd) {
+  return hd.mark == kFormMark ||
+         std::find(std::begin(kOrderMark), std::end(kOrderMark), hd.mark) != std::end(kOrderMark);
+}
+
+// (The running state is float64 in every precision and does not depend on the depth.)
+bool form_fits(const sbim_handle *h, const SnapshotHeader &hd, long long bytes, bool running) {
+  const SnapshotHeader own = header_of(h, bytes);
+  if (hd.mark == kFormMark)
+    return hd.bytes == own.bytes && hd.order == own.order && hd.quad == own.quad &&
+           (running || (hd.real == own.real && hd.depth == own.depth));
+  return marked(hd) ? hd.mark == kOrderMark[own.order] : own.order == kLagOrder;
+}
+
+hipError_t save_header(const sbim_handle *h, void *dst, long long bytes) {
+  const SnapshotHeader hd = header_of(h, bytes);
   const hipError_t e = hipMemcpyAsync(dst, &hd, sizeof hd, hipMemcpyHostToDevice, h->stream);
   return e != hipSuccess ? e : hipStreamSynchronize(h->stream);  // hd goes with this frame
 }
@@ -118,6 +137,22 @@ hipError_t save_header(const sbim_handle *h, void *dst) {
 hipError_t load_header(const sbim_handle *h, const void *src, SnapshotHeader &hd) {
   const hipError_t e = hipMemcpyAsync(&hd, src, sizeof hd, hipMemcpyDeviceToHost, h->stream);
   return e != hipSuccess ? e : hipStreamSynchronize(h->stream);
+}
+
+// The pending sums of group g, as the launches of the last `depth` steps before `step`
+// formed them, from the history in its ring.  (Entries that a later step has replaced
+// since meet rows past the window in the sums of `step` and after.)
+hipError_t form_sums(const sbim_handle *h, const Group &g, void *ring, void *pending, long long step) {
+  sbim::StepLaunch w{};
+  w.ring = ring;
+  w.pending = pending;
+  w.nh = h->nh;
+  w.dt = h->cfg.dt;
+  w.sums_only = true;
+  hipError_t e = hipMemsetAsync(pending, 0, pending_bytes(h, g), h->stream);
+  for (w.step = std::max(0LL, step - h->depth); w.step < step && e == hipSuccess; ++w.step)
+    e = sbim::launch_step(h, g, w);
+  return e;
 }
 
 }  // namespace
@@ -139,7 +174,7 @@ int sbim_save_state(sbim_handle *h, void *dst) {
   int rc = check_ptr(h, dst, "dst");
   if (rc) return rc;
   char *d = static_cast<char *>(dst);
-  hipError_t e = save_header(h, d);
+  hipError_t e = save_header(h, d, sbim_state_bytes(h));
   d += 256;
   if (e == hipSuccess)
     e = hipMemcpyAsync(d, h->out_spec, out_spec_bytes(h), hipMemcpyDeviceToDevice, h->stream);
@@ -168,7 +203,7 @@ int sbim_load_state(sbim_handle *h, const void *src) {
   hipError_t e = load_header(h, s, hd);
   if (e != hipSuccess) return hip_fail(h, e, "sbim_load_state header");
   if (hd.step < 0) return fail(h, SBIM_E_INVALID, "snapshot header is corrupt");
-  if (!layout_fits(h, hd))
+  if (!form_fits(h, hd, sbim_state_bytes(h), false))
     return fail(h, SBIM_E_INVALID, "snapshot orders the modes in another way than this handle");
   s += 256;
   e = hipMemcpyAsync(h->out_spec, s, out_spec_bytes(h), hipMemcpyDeviceToDevice, h->stream);
@@ -181,7 +216,9 @@ int sbim_load_state(sbim_handle *h, const void *src) {
     if (e == hipSuccess) e = hipMemcpyAsync(g.state, s, sb, hipMemcpyDeviceToDevice, h->stream);
     s += sb;
     const size_t pb = pending_bytes(h, g);
-    if (e == hipSuccess) e = hipMemcpyAsync(g.pending, s, pb, hipMemcpyDeviceToDevice, h->stream);
+    if (e == hipSuccess)
+      e = marked(hd) ? hipMemcpyAsync(g.pending, s, pb, hipMemcpyDeviceToDevice, h->stream)
+                     : form_sums(h, g, g.ring, g.pending, hd.step);
     s += pb;
   }
   if (e != hipSuccess) return hip_fail(h, e, "sbim_load_state");
@@ -201,7 +238,7 @@ int sbim_save_running_state(sbim_handle *h, void *dst) {
   int rc = check_ptr(h, dst, "dst");
   if (rc) return rc;
   char *d = static_cast<char *>(dst);
-  hipError_t e = save_header(h, d);
+  hipError_t e = save_header(h, d, sbim_running_state_bytes(h));
   d += 256;
   for (int i = 0; i < h->ngroups && e == hipSuccess; ++i) {
     const Group &g = h->g[i];
@@ -221,7 +258,7 @@ int sbim_load_running_state(sbim_handle *h, const void *src) {
   hipError_t e = load_header(h, s, hd);
   if (e != hipSuccess) return hip_fail(h, e, "sbim_load_running_state header");
   if (hd.step < 0) return fail(h, SBIM_E_INVALID, "running-state snapshot header is corrupt");
-  if (!layout_fits(h, hd))
+  if (!form_fits(h, hd, sbim_running_state_bytes(h), true))
     return fail(h, SBIM_E_INVALID, "running-state snapshot orders the modes in another way than this handle");
   s += 256;
   for (int i = 0; i < h->ngroups && e == hipSuccess; ++i) {

@@ -152,6 +152,7 @@ struct StepLaunch {
   long long step;         // index of this push
   double dt;
   int vel_rule, state_rule;
+  bool sums_only = false; // only the pending sums of the coming steps: no push, no traction
 };
 // One launch, bracketed by ev0/ev1 when they are non-null.
 hipError_t launch_step(const sbim_handle *h, const Group &g, const StepLaunch &w,
@@ -189,11 +190,12 @@ struct SweepArgs {
   long long nphase;       // blocks of this launch's sweep phase
 };
 
-// The step launches of the matrix-core forms (quads.hip, pairs.hip), as launch_step.
+// The step launches of the matrix-core forms (quads.hip, pairs.hip), as launch_step;
+// mode_blocks: the blocks whose modes are pushed (all of them, or none).
 hipError_t launch_step_quads(const sbim_handle *h, const Group &g, const SweepArgs &sa,
-                             const ModeArgs &ma, hipEvent_t ev0, hipEvent_t ev1);
+                             const ModeArgs &ma, long long mode_blocks, hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_step_pairs(const sbim_handle *h, const Group &g, const SweepArgs &sa,
-                             const ModeArgs &ma, hipEvent_t ev0, hipEvent_t ev1);
+                             const ModeArgs &ma, long long mode_blocks, hipEvent_t ev0, hipEvent_t ev1);
 
 // fault.hip: interface solve of a frictional fault between the two sides.
 // Fields are [component][cell] with cell = i1 * n3 + i3; u, v hold the upper

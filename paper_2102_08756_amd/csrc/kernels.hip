@@ -599,14 +599,15 @@ __global__ __launch_bounds__(kTabThreads) void tabulate_kernel(
 
 template <typename R, int S, int T, bool COMP>
 hipError_t step_launch_s(const sbim_handle *h, const Group &g, const SweepArgs &sa0,
-                         const ModeArgs &ma, hipEvent_t ev0, hipEvent_t ev1) {
+                         const ModeArgs &ma, long long mode_blocks, hipEvent_t ev0, hipEvent_t ev1) {
   constexpr int D = S * T;
   SweepArgs sa = sa0;
   const int phase = static_cast<int>((sa.step + 1) % D);
   sa.nphase = g.nblocks > phase ? (g.nblocks - phase + D - 1) / D : 0;
   const long long sweep_items =
       (sa.nphase + 7) / 8 * 8 * (sweep_lag_groups<R, S, T, COMP>() * T) * g.np;
-  const long long items = sweep_items + xcd_chunk_ids(g.nblocks * g.np);
+  const long long items = sweep_items + xcd_chunk_ids(mode_blocks * g.np);
+  if (items == 0) return hipSuccess;
   if (ev0) {
     const hipError_t e = hipEventRecord(ev0, h->stream);
     if (e != hipSuccess) return e;
@@ -638,10 +639,10 @@ hipError_t step_launch_s(const sbim_handle *h, const Group &g, const SweepArgs &
       const long long long_wgs = (nlong + 7) / 8 * 8 * per_blk;
       const long long rest = (sa.nphase - nlong + kSplit - 1) / kSplit;
       const long long sweep_wgs = long_wgs + (rest + 7) / 8 * 8 * per_blk;
-      const long long wgs = sweep_wgs + xcd_chunk_ids((g.nblocks * g.np + kSplit - 1) / kSplit);
+      const long long wgs = sweep_wgs + xcd_chunk_ids((mode_blocks * g.np + kSplit - 1) / kSplit);
       hipLaunchKernelGGL((step_kernel_split<R, S, T, COMP>), dim3(static_cast<unsigned>(wgs)),
                          dim3(kSplit * kLanes), 0, h->stream, sa, ma, long_wgs, sweep_wgs, nlong,
-                         g.nblocks);
+                         mode_blocks);
       const hipError_t e = hipGetLastError();
       return e == hipSuccess && ev1 ? hipEventRecord(ev1, h->stream) : e;
     }
@@ -653,20 +654,20 @@ hipError_t step_launch_s(const sbim_handle *h, const Group &g, const SweepArgs &
     const double block_span = static_cast<double>(g.wmax) * ((g.nblocks + D - 1) / D) * g.np * 3 * kLanes * 8;
     if (h->cfg.window_mode == SBIM_W_FIXED && g.wmax >= 64 && block_span < 4.29e9) {
       hipLaunchKernelGGL((step_kernel_staged<COMP>), dim3(static_cast<unsigned>(items)), dim3(kLanes),
-                         2 * kStageBytes, h->stream, sa, ma, sweep_items, g.nblocks);
+                         2 * kStageBytes, h->stream, sa, ma, sweep_items, mode_blocks);
       const hipError_t e = hipGetLastError();
       return e == hipSuccess && ev1 ? hipEventRecord(ev1, h->stream) : e;
     }
   }
   if constexpr (!COMP && sizeof(R) == 4 && S == 6 && T == 2)
     hipLaunchKernelGGL((step_kernel_w4<R, S, T, COMP>), dim3(static_cast<unsigned>(items)),
-                       dim3(kLanes), 0, h->stream, sa, ma, sweep_items, g.nblocks);
+                       dim3(kLanes), 0, h->stream, sa, ma, sweep_items, mode_blocks);
   else if constexpr (COMP && S <= 6)
     hipLaunchKernelGGL((step_kernel_w2<R, S, T, COMP>), dim3(static_cast<unsigned>(items)),
-                       dim3(kLanes), 0, h->stream, sa, ma, sweep_items, g.nblocks);
+                       dim3(kLanes), 0, h->stream, sa, ma, sweep_items, mode_blocks);
   else
     hipLaunchKernelGGL((step_kernel<R, S, T, COMP>), dim3(static_cast<unsigned>(items)),
-                       dim3(kLanes), 0, h->stream, sa, ma, sweep_items, g.nblocks);
+                       dim3(kLanes), 0, h->stream, sa, ma, sweep_items, mode_blocks);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && ev1) e = hipEventRecord(ev1, h->stream);
   return e;
@@ -674,15 +675,15 @@ hipError_t step_launch_s(const sbim_handle *h, const Group &g, const SweepArgs &
 
 template <typename R, bool COMP>
 hipError_t step_launch_r(const sbim_handle *h, const Group &g, const SweepArgs &sa,
-                         const ModeArgs &ma, hipEvent_t ev0, hipEvent_t ev1) {
+                         const ModeArgs &ma, long long mode_blocks, hipEvent_t ev0, hipEvent_t ev1) {
   switch (h->depth) {
-    case 1: return step_launch_s<R, 1, 1, COMP>(h, g, sa, ma, ev0, ev1);
-    case 2: return step_launch_s<R, 2, 1, COMP>(h, g, sa, ma, ev0, ev1);
-    case 4: return step_launch_s<R, 4, 1, COMP>(h, g, sa, ma, ev0, ev1);
-    case 6: return step_launch_s<R, 6, 1, COMP>(h, g, sa, ma, ev0, ev1);
-    case 8: return step_launch_s<R, 8, 1, COMP>(h, g, sa, ma, ev0, ev1);
-    case 12: return step_launch_s<R, 6, 2, COMP>(h, g, sa, ma, ev0, ev1);
-    case 16: return step_launch_s<R, 8, 2, COMP>(h, g, sa, ma, ev0, ev1);
+    case 1: return step_launch_s<R, 1, 1, COMP>(h, g, sa, ma, mode_blocks, ev0, ev1);
+    case 2: return step_launch_s<R, 2, 1, COMP>(h, g, sa, ma, mode_blocks, ev0, ev1);
+    case 4: return step_launch_s<R, 4, 1, COMP>(h, g, sa, ma, mode_blocks, ev0, ev1);
+    case 6: return step_launch_s<R, 6, 1, COMP>(h, g, sa, ma, mode_blocks, ev0, ev1);
+    case 8: return step_launch_s<R, 8, 1, COMP>(h, g, sa, ma, mode_blocks, ev0, ev1);
+    case 12: return step_launch_s<R, 6, 2, COMP>(h, g, sa, ma, mode_blocks, ev0, ev1);
+    case 16: return step_launch_s<R, 8, 2, COMP>(h, g, sa, ma, mode_blocks, ev0, ev1);
     default: return hipErrorInvalidValue;
   }
 }
@@ -748,11 +749,12 @@ hipError_t launch_step(const sbim_handle *h, const Group &g, const StepLaunch &w
   sa.step = w.step;
   sa.np = g.np;
   sa.nphase = 0;
-  if (h->tiled) return launch_step_quads(h, g, sa, ma, ev0, ev1);
-  if (h->mfma) return launch_step_pairs(h, g, sa, ma, ev0, ev1);
-  if (h->fp64) return step_launch_r<double, false>(h, g, sa, ma, ev0, ev1);
-  if (h->comp) return step_launch_r<float, true>(h, g, sa, ma, ev0, ev1);
-  return step_launch_r<float, false>(h, g, sa, ma, ev0, ev1);
+  const long long mode_blocks = w.sums_only ? 0 : g.nblocks;
+  if (h->tiled) return launch_step_quads(h, g, sa, ma, mode_blocks, ev0, ev1);
+  if (h->mfma) return launch_step_pairs(h, g, sa, ma, mode_blocks, ev0, ev1);
+  if (h->fp64) return step_launch_r<double, false>(h, g, sa, ma, mode_blocks, ev0, ev1);
+  if (h->comp) return step_launch_r<float, true>(h, g, sa, ma, mode_blocks, ev0, ev1);
+  return step_launch_r<float, false>(h, g, sa, ma, mode_blocks, ev0, ev1);
 }
 
 hipError_t launch_tabulate(bool fp64, const Group &g, double dt, const double *gl_x,

@@ -311,14 +311,15 @@ step_kernel_pairs(SweepArgs sa, ModeArgs ma, long long sweep_wgs, long long nblo
 
 template <bool COMP, int G>
 hipError_t step_launch_p(const sbim_handle *h, const Group &g, const SweepArgs &sa0,
-                         const ModeArgs &ma, hipEvent_t ev0, hipEvent_t ev1) {
+                         const ModeArgs &ma, long long mode_blocks, hipEvent_t ev0, hipEvent_t ev1) {
   constexpr int D = 16 * G;
   SweepArgs sa = sa0;
   const int phase = static_cast<int>((sa.step + 1) % D);
   sa.nphase = g.nblocks > phase ? (g.nblocks - phase + D - 1) / D : 0;
   const int LG = h->lag_chunks, QW = h->sweep_quads;
   const long long sweep_wgs = (sa.nphase + 7) / 8 * 8 * (16 / QW);
-  const long long mode_wgs = (g.nblocks * g.np + LG * QW - 1) / (LG * QW);
+  const long long mode_wgs = (mode_blocks * g.np + LG * QW - 1) / (LG * QW);
+  if (sweep_wgs + mode_wgs == 0) return hipSuccess;
   const size_t lds = static_cast<size_t>(QW) * (LG - 1) * G * 5 * 4 * (COMP ? 2 : 1) * kLanes *
                      sizeof(float);
   if (ev0) {
@@ -333,7 +334,7 @@ hipError_t step_launch_p(const sbim_handle *h, const Group &g, const SweepArgs &
   constexpr int WAVES = 3;
   hipLaunchKernelGGL((step_kernel_pairs<COMP, G, WAVES>),
                      dim3(static_cast<unsigned>(sweep_wgs + xcd_chunk_ids(mode_wgs))),
-                     dim3(LG * QW * kLanes), lds, h->stream, sa, ma, sweep_wgs, g.nblocks, LG, QW);
+                     dim3(LG * QW * kLanes), lds, h->stream, sa, ma, sweep_wgs, mode_blocks, LG, QW);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && ev1) e = hipEventRecord(ev1, h->stream);
   return e;
@@ -342,15 +343,15 @@ hipError_t step_launch_p(const sbim_handle *h, const Group &g, const SweepArgs &
 }  // namespace
 
 hipError_t launch_step_pairs(const sbim_handle *h, const Group &g, const SweepArgs &sa,
-                             const ModeArgs &ma, hipEvent_t ev0, hipEvent_t ev1) {
+                             const ModeArgs &ma, long long mode_blocks, hipEvent_t ev0, hipEvent_t ev1) {
   if (g.np != 2 || h->fp64 || (h->depth != 16 && h->depth != 32) || h->lag_chunks < 1 ||
       h->lag_chunks * h->sweep_quads > 4)
     return hipErrorInvalidValue;
   if (h->comp)
-    return h->depth == 32 ? step_launch_p<true, 2>(h, g, sa, ma, ev0, ev1)
-                          : step_launch_p<true, 1>(h, g, sa, ma, ev0, ev1);
-  return h->depth == 32 ? step_launch_p<false, 2>(h, g, sa, ma, ev0, ev1)
-                        : step_launch_p<false, 1>(h, g, sa, ma, ev0, ev1);
+    return h->depth == 32 ? step_launch_p<true, 2>(h, g, sa, ma, mode_blocks, ev0, ev1)
+                          : step_launch_p<true, 1>(h, g, sa, ma, mode_blocks, ev0, ev1);
+  return h->depth == 32 ? step_launch_p<false, 2>(h, g, sa, ma, mode_blocks, ev0, ev1)
+                        : step_launch_p<false, 1>(h, g, sa, ma, mode_blocks, ev0, ev1);
 }
 
 }  // namespace sbim

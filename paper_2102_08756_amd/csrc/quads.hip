@@ -494,7 +494,7 @@ step_kernel_mfma(SweepArgs sa, ModeArgs ma, long long sweep_wgs, long long mid_w
 
 template <typename R, bool COMP, int NP, int CM, int G, int TW>
 hipError_t step_launch_q(const sbim_handle *h, const Group &g, const SweepArgs &sa0,
-                         const ModeArgs &ma, hipEvent_t ev0, hipEvent_t ev1) {
+                         const ModeArgs &ma, long long mode_blocks, hipEvent_t ev0, hipEvent_t ev1) {
   using Shape = QuadShape<R, COMP, NP, CM, G, TW>;
   constexpr int D = Shape::D;
   if (h->depth != D) return hipErrorInvalidValue;
@@ -512,8 +512,9 @@ hipError_t step_launch_q(const sbim_handle *h, const Group &g, const SweepArgs &
   }
   const int waves = LG * QW;
   const long long mid_wgs = xcd_chunk_ids((mid_items + waves - 1) / waves);
-  const long long mode_wgs = (g.nblocks * NP + waves - 1) / waves;
+  const long long mode_wgs = (mode_blocks * NP + waves - 1) / waves;
   const size_t lds = static_cast<size_t>(waves) * Shape::kWaveLds;
+  if (sweep_wgs + mid_wgs + mode_wgs == 0) return hipSuccess;
   if (ev0) {
     const hipError_t e = hipEventRecord(ev0, h->stream);
     if (e != hipSuccess) return e;
@@ -531,7 +532,7 @@ hipError_t step_launch_q(const sbim_handle *h, const Group &g, const SweepArgs &
   hipLaunchKernelGGL((step_kernel_mfma<R, COMP, NP, CM, G, TW, WAVES>),
                      dim3(static_cast<unsigned>(sweep_wgs + mid_wgs + xcd_chunk_ids(mode_wgs))),
                      dim3(waves * kLanes), lds, h->stream, sa, ma, sweep_wgs, mid_wgs, mid_items,
-                     g.nblocks, LG, QW, spread);
+                     mode_blocks, LG, QW, spread);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && ev1) e = hipEventRecord(ev1, h->stream);
   return e;
@@ -540,30 +541,30 @@ hipError_t step_launch_q(const sbim_handle *h, const Group &g, const SweepArgs &
 // The matrix-core launch for this handle's planes per group, modes per quad and depth.
 template <typename R, bool COMP>
 hipError_t step_launch_quads(const sbim_handle *h, const Group &g, const SweepArgs &sa,
-                             const ModeArgs &ma, hipEvent_t ev0, hipEvent_t ev1) {
+                             const ModeArgs &ma, long long mode_blocks, hipEvent_t ev0, hipEvent_t ev1) {
   if (h->lag_chunks < 1 || h->sweep_quads < 1 || h->lag_chunks * h->sweep_quads > 8)
     return hipErrorInvalidValue;
   if (g.np == 2 && h->quad_modes == 4) {
-    if (h->depth == 16) return step_launch_q<R, COMP, 2, 4, 1, 1>(h, g, sa, ma, ev0, ev1);
+    if (h->depth == 16) return step_launch_q<R, COMP, 2, 4, 1, 1>(h, g, sa, ma, mode_blocks, ev0, ev1);
     // 32 steps: two accumulator groups per wavefront share each operand load; the
     // float64 and compensated sums (two registers each) take a wavefront per group
     // instead (measured, us per step of 512^2, W = 1000: compensated 132 against 171;
     // float64 211 against 214; float32 1024^2, W = 2000: 647 against 572)
     constexpr bool wide = COMP || sizeof(R) == 8;
-    return step_launch_q<R, COMP, 2, 4, wide ? 1 : 2, wide ? 2 : 1>(h, g, sa, ma, ev0, ev1);
+    return step_launch_q<R, COMP, 2, 4, wide ? 1 : 2, wide ? 2 : 1>(h, g, sa, ma, mode_blocks, ev0, ev1);
   }
-  if (g.np == 2) return step_launch_q<R, COMP, 2, 2, 1, 1>(h, g, sa, ma, ev0, ev1);
-  if (h->quad_modes == 4) return step_launch_q<R, COMP, 1, 4, 1, 1>(h, g, sa, ma, ev0, ev1);
-  return step_launch_q<R, COMP, 1, 2, 1, 1>(h, g, sa, ma, ev0, ev1);
+  if (g.np == 2) return step_launch_q<R, COMP, 2, 2, 1, 1>(h, g, sa, ma, mode_blocks, ev0, ev1);
+  if (h->quad_modes == 4) return step_launch_q<R, COMP, 1, 4, 1, 1>(h, g, sa, ma, mode_blocks, ev0, ev1);
+  return step_launch_q<R, COMP, 1, 2, 1, 1>(h, g, sa, ma, mode_blocks, ev0, ev1);
 }
 
 }  // namespace
 
 hipError_t launch_step_quads(const sbim_handle *h, const Group &g, const SweepArgs &sa,
-                             const ModeArgs &ma, hipEvent_t ev0, hipEvent_t ev1) {
-  if (h->fp64) return step_launch_quads<double, false>(h, g, sa, ma, ev0, ev1);
-  if (h->comp) return step_launch_quads<float, true>(h, g, sa, ma, ev0, ev1);
-  return step_launch_quads<float, false>(h, g, sa, ma, ev0, ev1);
+                             const ModeArgs &ma, long long mode_blocks, hipEvent_t ev0, hipEvent_t ev1) {
+  if (h->fp64) return step_launch_quads<double, false>(h, g, sa, ma, mode_blocks, ev0, ev1);
+  if (h->comp) return step_launch_quads<float, true>(h, g, sa, ma, mode_blocks, ev0, ev1);
+  return step_launch_quads<float, false>(h, g, sa, ma, mode_blocks, ev0, ev1);
 }
 
 }  // namespace sbim

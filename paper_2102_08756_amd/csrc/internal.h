@@ -227,8 +227,9 @@ struct StripArgs {
   double *u_next;             // [3][nodes] u_{t+2}, written (the other displacement buffer)
   double *vh;                 // [3][nodes] in: v_{t+1/2}; out: v_{t+3/2}
   double *v;                  // [3][nodes] out: v_{t+1}
-  const double *stencil;      // [n2+1][27][3][3]: stiffness block of each neighbour offset
+  const double *stencil;      // [distinct][27][3][3]: stiffness block of each neighbour offset
                               // (o1, o2, o3), index 9 (o2+1) + 3 (o1+1) + (o3+1)
+  const int *stencil_of;      // [n2+1] which of them is a layer's
   const double *mass;         // [n2+1] lumped mass of a node of each layer
   const void *tau_sbi;        // [P][3][cells] working precision: tractions at S+ (and S-)
   void *push_u, *push_v;      // [P][3][cells] working precision: S+ (and S-) displacement

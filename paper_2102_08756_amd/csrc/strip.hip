@@ -16,6 +16,8 @@
 // above and below it may differ), precomputed on the host from the element stiffness.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "internal.h"
 
 // Plain float64 rounding of each product and sum, as in the interface solve of
@@ -29,6 +31,7 @@ namespace {
 // Pointers of known kind: device memory, and tables read through the scalar cache.
 using global_f64 = const __attribute__((address_space(1))) double *;
 using table_f64 = const __attribute__((address_space(4))) double *;
+using table_i32 = const __attribute__((address_space(4))) int *;
 
 constexpr int kStripThreads = 128;  // (1024^2, us a pass: 128 771, 256 781, 512 828)
 
@@ -157,7 +160,11 @@ __device__ __forceinline__ double lane_shift(double v, double edge, bool left) {
 // in the order offset in x2, x1, x3, component, whatever the depth.
 // UNIFORM: every wavefront lies in one run of layers, so the stencil comes through the
 // scalar cache (table_f64: after the loop's stores the compiler would read it through
-// vector memory otherwise).  Three wavefronts a SIMD hide the rows' latency; a prefetch
+// vector memory otherwise).  A stencil is 1.9 KB of that cache's 16, which two CUs share and
+// wavefronts of different layers fill together: with one for every layer it no longer held
+// them from ten layers up, so layers of equal stencils share one (512^2, two sides of 4 / 6
+// element layers, a pass of three steps: 706 / 865 us with a stencil per layer, 681 / 786
+// with three a side; float32 with 57 lags 758 / 903 and 723 / 835).  Three wavefronts a SIMD hide the rows' latency; a prefetch
 // of the next layer costs the occupancy and more than it hides.
 // Bound by the small grid's latency and by memory on large ones: 48 B read and 72 B
 // written per node.  256^2 cells, two sides of 3 element layers: 49 us with one thread per
@@ -244,7 +251,7 @@ strip_correct_kernel(StripArgs a, int depth) {
         for (int t = 0; t < 3; ++t) {             // target layer l - 1 + t, which sees l at offset 1 - t
           const int lt = l - 1 + t;
           if (lt < l0 || lt >= l1) continue;
-          table_f64 B = (table_f64)a.stencil + (lt * 9 + (2 - t) * 3 + q) * 27;
+          table_f64 B = (table_f64)a.stencil + (((table_i32)a.stencil_of)[lt] * 9 + (2 - t) * 3 + q) * 27;
 #pragma unroll
           for (int o3 = 0; o3 < 3; ++o3)
 #pragma unroll
@@ -402,13 +409,16 @@ static hipError_t strip_correct(const StripArgs &a, int depth, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Layers per thread: four where that leaves four wavefronts to a SIMD (4096 in all), else
-// fewer: more layers a thread read fewer rows twice, but a small grid waits for the chain
-// of layers (us a pass, layers per thread 1 / 2 / 4: 1024^2 with 3 node layers, two steps,
-// 892 / 882 / 781; 256^2 with 8, three steps, 275 / 264 / 284).
+// Layers per thread: equal runs of layers, as few as leave four wavefronts to a SIMD (4096 in
+// all) and no run longer than eight: more layers a thread read fewer rows twice, but a small
+// grid waits for the chain of layers, and a last, short run still reads its two outer layers
+// (us a pass of three steps at 1 / 2 / 3 / 4 / 5 / 8 layers a thread, a stencil per layer: 512^2 with 10 node layers
+// 769 / 713 / 754 / 748 / 706 / 832, with 5 370 / 363 / 355 / 382 / 336 / 335; 256^2 with 10
+// 255 / 264 / 250 / 265 / 273 / 324).
 hipError_t launch_strip_correct(bool fp64, const StripArgs &a, hipStream_t st) {
-  int depth = 4;
-  while (depth > 1 && a.cells * ((a.n2 + depth) / depth) < 4096LL * 64) depth /= 2;
+  const int layers = a.n2 + 1;
+  const long long runs = std::max((4096LL * 64 + a.cells - 1) / a.cells, (layers + 7LL) / 8);
+  const int depth = static_cast<int>((layers + runs - 1) / runs);
   return fp64 ? strip_correct<double>(a, depth, st) : strip_correct<float>(a, depth, st);
 }
 

@@ -34,7 +34,8 @@ struct sbim_strip {
   double dt_pred = 0;         // step size of the prediction held for the next step
   double *cell = nullptr;     // fault outputs
   double *prm = nullptr;      // tau0 (3), mu_s, mu_k, d_c
-  double *stencil = nullptr;  // [n2+1][27][9]
+  double *stencil = nullptr;  // [distinct][27][9]
+  int *stencil_of = nullptr;  // [n2+1]
   double *mass = nullptr;     // [n2+1]
   void *push_u = nullptr, *push_v = nullptr, *tau_sbi = nullptr;  // [P][3][cells] working precision
   double *r_fault = nullptr;  // two-sided: [2][3][cells]
@@ -101,7 +102,7 @@ void cube_stiffness(double h, double lam, double mu, std::vector<double> &K) {
 void free_strip(sbim_strip *s) {
   if (!s) return;
   if (s->h) (void)hipStreamSynchronize(s->h->stream);
-  void *ptrs[] = {s->node, s->cell, s->prm, s->stencil, s->mass, s->push_u, s->push_v,
+  void *ptrs[] = {s->node, s->cell, s->prm, s->stencil, s->stencil_of, s->mass, s->push_u, s->push_v,
                   s->tau_sbi, s->r_fault, s->bad};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
@@ -210,6 +211,18 @@ int sbim_strip_create(sbim_handle *h, const sbim_strip_config *sc, const sbim_fa
         }
     }
   }
+  // layers of equal stencils share one (see strip_correct_kernel)
+  constexpr size_t kStencil = 27 * 9;
+  std::vector<int> of(s->n2 + 1);
+  size_t distinct = 0;
+  for (int l = 0; l <= s->n2; ++l) {
+    const double *own = &st[l * kStencil];
+    size_t k = 0;
+    while (k < distinct && std::memcmp(&st[k * kStencil], own, kStencil * sizeof(double)) != 0) ++k;
+    if (k == distinct) std::copy(own, own + kStencil, &st[distinct++ * kStencil]);
+    of[l] = static_cast<int>(k);
+  }
+  st.resize(distinct * kStencil);
   const size_t n = static_cast<size_t>(s->cells);
   const size_t fb = static_cast<size_t>(c.nplanes) * 3 * n * h->rsize;
   hipError_t e;
@@ -218,6 +231,7 @@ int sbim_strip_create(sbim_handle *h, const sbim_strip_config *sc, const sbim_fa
       (e = dev_alloc(&s->cell, kCellRows * n)) != hipSuccess ||
       (e = dev_alloc(&s->prm, 6 * n)) != hipSuccess ||
       (e = dev_alloc(&s->stencil, st.size())) != hipSuccess ||
+      (e = dev_alloc(&s->stencil_of, of.size())) != hipSuccess ||
       (e = dev_alloc(&s->mass, ms.size())) != hipSuccess ||
       (e = dev_alloc_bytes(&s->push_u, fb)) != hipSuccess ||
       (e = dev_alloc_bytes(&s->push_v, fb)) != hipSuccess ||
@@ -230,6 +244,7 @@ int sbim_strip_create(sbim_handle *h, const sbim_strip_config *sc, const sbim_fa
   const size_t b = n * sizeof(double);
   long long bad = 0;
   if ((e = upload(s->stencil, st.data(), st.size() * sizeof(double), h->stream)) ||
+      (e = upload(s->stencil_of, of.data(), of.size() * sizeof(int), h->stream)) ||
       (e = upload(s->mass, ms.data(), ms.size() * sizeof(double), h->stream)) ||
       (e = hipMemcpyAsync(s->prm, prm->tau0, 3 * b, hipMemcpyDeviceToDevice, h->stream)) ||
       (e = hipMemcpyAsync(s->prm + 3 * n, prm->mu_s, b, hipMemcpyDeviceToDevice, h->stream)) ||
@@ -273,6 +288,7 @@ int sbim_strip_step(sbim_strip *s, double *tau_out, double *rate_out) {
   a.vh = s->node + 6 * s->nodes;
   a.v = s->node + 9 * s->nodes;
   a.stencil = s->stencil;
+  a.stencil_of = s->stencil_of;
   a.mass = s->mass;
   a.tau_sbi = s->tau_sbi;
   a.push_u = s->push_u;

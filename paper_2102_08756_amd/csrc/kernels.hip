@@ -227,7 +227,11 @@ __device__ __forceinline__ void sweep_item(const SweepArgs &a, long long kb, int
   const int p = r / NQ;
   const long long t0 = step + 1;
   const long long b = t0 % D + D * kb;
-  const int lane = threadIdx.x & (kLanes - 1), wave = SPLIT ? static_cast<int>(threadIdx.x) / kLanes : 0;
+  // (the work-group of one wavefront: not masked.  Known to be under 64, the compiler keeps
+  // the slot arithmetic of a single chunk in scalar registers, between the loads: float64
+  // 512^2, two materials, 40 lags: the sweeps alone 23.2 and 21.0 us.)
+  const int lane = SPLIT ? threadIdx.x & (kLanes - 1) : threadIdx.x;
+  const int wave = SPLIT ? static_cast<int>(threadIdx.x) / kLanes : 0;
   const int lg = lane / (Q * T);
   const int u0 = (lane / Q) % T * S;        // first of the lane's S steps (t0 + u0 ..)
   const int col = (r % NQ) * Q + lane % Q;  // lane of the mode in its block
@@ -238,6 +242,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs &a, long long kb, int
   // history entries (lags 2 .. min(cap-1, t0) of step t0) that the window can reach
   const int nent = static_cast<int>(max(0LL, min(static_cast<long long>(cap) - 1, t0) - 1));
   const int wl = valid ? a.win[sm] : 0;
+  const long long row0 = valid ? a.row0[sm] : 0;
   const int per = (nent + NW * LG * S - 1) / (NW * LG * S) * S;  // lags per chunk
   const int i0 = 2 + (wave * LG + lg) * per;
 
@@ -261,7 +266,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs &a, long long kb, int
                         (a.blk_off[b] + static_cast<long long>(x) * a.blk_stride[b]) * rec_len +
                         static_cast<long long>(p) * 3 * kLanes + col;
     // a mode without history (W = 0) reads the zero row after class 0's rows
-    const W *rowp = wl > 0 ? table + a.row0[sm] : table + a.cls_w0;
+    const W *rowp = table + (wl > 0 ? row0 : a.cls_w0);
     W ra[S], rb[S];
     load_rows<R, S>(ra, rowp, i0 + u0, wl);
     // staged history: this lane's piece, its slot, and the stage of the LDS in use

@@ -165,12 +165,21 @@ __device__ __forceinline__ void mode_step(const ModeArgs &a, int p, long long s)
   double2 *__restrict__ state = a.state;
   const long long M = a.M, nh = a.nh, step = a.step;
   const int np = a.np;
-  // every load that depends on the position alone, in flight together
+  // What a step reads beside the spectrum and the state (window, kernel rows, sums)
+  // is asked for at once in the matrix-core forms; beside the vector sweep, after the
+  // push: its chains of dependent loads are the launch's length, and the fewer loads
+  // the mode items have in flight the shorter they are (float64 512^2, two materials,
+  // 40 lags: the launch 30.0 and 29.2 us, the mode items alone 18.0 and 19.2).
   const int natural = a.nat[s];
-  const int wl = a.win[s];
-  const long long row0 = a.row0[s];
+  if (!TILED && natural < 0) return;  // a padding position of the matrix-core layout: no mode
+  int wl = 0;
+  long long row0 = 0;
+  if constexpr (TILED) {
+    wl = a.win[s];
+    row0 = a.row0[s];
+  }
   const double4 geom = *reinterpret_cast<const double4 *>(a.geom + 4 * s);
-  const int b = __builtin_amdgcn_readfirstlane(static_cast<int>(s >> 6));
+  const int b = TILED ? __builtin_amdgcn_readfirstlane(static_cast<int>(s >> 6)) : static_cast<int>(s >> 6);
   const int lane = static_cast<int>(s & 63);
   const int cap = a.blk_cap[b];
   const long long base = a.blk_off[b];
@@ -183,49 +192,50 @@ __device__ __forceinline__ void mode_step(const ModeArgs &a, int p, long long s)
 
   // ---- where the history sums of step n come from
   // The sweep launched with step m-1 covers steps m .. m+D-1 (m = b mod D, m >= 1)
-  // over the history up to step m-2, and with a middle level (mid != null) the
-  // launch of step m-1, m = b mod kMidPeriod, adds the entries since that sweep.
-  // Lags not in those sums: from step m-1 on, or all of them before the block's
-  // first launch of either kind.
-  const int S = a.depth;
-  const int since = mod_step(step + S - b % S, S);  // steps since m
-  const bool swept = step - since >= 1 && cap > kDirectLags;
-  int fresh = swept ? since + 2 : static_cast<int>(min(step + 1, 1LL << 30));
-  bool mids = false;
-  if (a.mid && cap > kDirectLags) {
-    const int e = since % kMidPeriod;
-    mids = step - e >= 1 && since >= kMidPeriod;
-    if (step - e >= 1) fresh = e + 2;
-  }
-  fresh = min(wl, fresh);
+  // over the history up to step m-2, and with a middle level the launch of step m-1,
+  // m = b mod kMidPeriod, adds the entries since that sweep.  Lags not in those sums:
+  // from step m-1 on, or all of them before the block's first launch of either kind.
+  int fresh = 0;
   cplx<R> pend[5], midv[5];
-  if (swept && wl > 0) {
-    const cplx<R> *__restrict__ q = static_cast<const cplx<R> *>(a.pending) +
-                                    (mod_step(step, S + 1) * np + p) * 5LL * M + s;
+  const auto load_sums = [&]() {
+    const int S = a.depth;
+    const int since = mod_step(step + S - b % S, S);  // steps since m
+    const bool swept = step - since >= 1 && cap > kDirectLags;
+    fresh = swept ? since + 2 : static_cast<int>(min(step + 1, 1LL << 30));
+    bool mids = false;
+    if (TILED && cap > kDirectLags) {
+      const int e = since % kMidPeriod;
+      mids = step - e >= 1 && since >= kMidPeriod;
+      if (step - e >= 1) fresh = e + 2;
+    }
+    fresh = min(wl, fresh);
 #pragma unroll
-    for (int t = 0; t < 5; ++t) pend[t] = q[t * M];
-  } else {
+    for (int t = 0; t < 5; ++t) pend[t] = midv[t] = cplx<R>{R(0), R(0)};
+    if (swept && (wl > 0 || !TILED)) {
+      const cplx<R> *__restrict__ q = static_cast<const cplx<R> *>(a.pending) +
+                                      (mod_step(step, S + 1) * np + p) * 5LL * M + s;
 #pragma unroll
-    for (int t = 0; t < 5; ++t) pend[t] = cplx<R>{R(0), R(0)};
-  }
-  if (mids && wl > 0) {
-    const cplx<R> *__restrict__ q = static_cast<const cplx<R> *>(a.mid) +
-                                    (mod_step(step, kMidPeriod + 1) * np + p) * 5LL * M + s;
+      for (int t = 0; t < 5; ++t) pend[t] = q[t * M];
+    }
+    if (mids && wl > 0) {
+      const cplx<R> *__restrict__ q = static_cast<const cplx<R> *>(a.mid) +
+                                      (mod_step(step, kMidPeriod + 1) * np + p) * 5LL * M + s;
 #pragma unroll
-    for (int t = 0; t < 5; ++t) midv[t] = q[t * M];
-  } else {
-#pragma unroll
-    for (int t = 0; t < 5; ++t) midv[t] = cplx<R>{R(0), R(0)};
-  }
-  if (natural < 0) return;  // a padding position of the matrix-core layout: no mode
+      for (int t = 0; t < 5; ++t) midv[t] = q[t * M];
+    }
+  };
+  if constexpr (TILED) load_sums();
+  if (TILED && natural < 0) return;
   const double q = geom.x, kh1 = geom.y, kh3 = geom.z;
 
   // record of one step: of the block's ring, or of the recent ring
+  cplx<R> *const first = ring + base * rec_len + static_cast<long long>(p) * 3 * kLanes + lane;
   const auto slot = [&](int x) {
-    const long long rec = TILED ? static_cast<long long>(x) * a.nblocks + b
-                                : base + static_cast<long long>(x) * stride;
-    return (TILED ? static_cast<cplx<R> *>(a.recent) : ring) + rec * rec_len +
-           static_cast<long long>(p) * 3 * kLanes + lane;
+    if constexpr (TILED)
+      return static_cast<cplx<R> *>(a.recent) + (static_cast<long long>(x) * a.nblocks + b) * rec_len +
+             static_cast<long long>(p) * 3 * kLanes + lane;
+    else
+      return first + static_cast<long long>(x) * stride * rec_len;
   };
 
   // ---- push
@@ -276,6 +286,10 @@ __device__ __forceinline__ void mode_step(const ModeArgs &a, int p, long long s)
   }
 
   // ---- history sums of step n
+  if constexpr (!TILED) {
+    wl = a.win[s];
+    load_sums();
+  }
   R cs[kSums];
   {
     Acc<R, COMP> acc[kSums];
@@ -283,13 +297,15 @@ __device__ __forceinline__ void mode_step(const ModeArgs &a, int p, long long s)
     for (int t = 0; t < 5; ++t) {
       acc[2 * t].s = pend[t].x;
       acc[2 * t + 1].s = pend[t].y;
-      acc[2 * t].fold(midv[t].x);
-      acc[2 * t + 1].fold(midv[t].y);
+      if constexpr (TILED) {
+        acc[2 * t].fold(midv[t].x);
+        acc[2 * t + 1].fold(midv[t].y);
+      }
     }
     if (fresh > 0) {
       // the newest lags: plain products (the compensated form folds their sum,
       // at most depth + 1 or kMidPeriod + 1 lags, into the pending sum once)
-      const W *__restrict__ rowp = static_cast<const W *>(a.table) + row0;
+      const W *__restrict__ rowp = static_cast<const W *>(a.table) + (TILED ? row0 : a.row0[s]);
       R part[kSums];
 #pragma unroll
       for (int k = 0; k < kSums; ++k) part[k] = COMP ? R(0) : acc[k].s;
@@ -321,7 +337,7 @@ __device__ __forceinline__ void mode_step(const ModeArgs &a, int p, long long s)
           u[i][0] = qp[0];
           u[i][1] = qp[kLanes];
           u[i][2] = qp[2 * kLanes];
-          w[i] = rowp[min(j, wl)];
+          w[i] = rowp[TILED ? min(j, wl) : j];
         }
 #pragma unroll
         for (int i = 0; i < FB; ++i) {

@@ -619,8 +619,9 @@ hipError_t step_launch_s(const sbim_handle *h, const Group &g, const SweepArgs &
   }
   // Long blocks are split over wavefronts where the launch would wait for one of them: a
   // lag of a chain takes about 0.33 us, a mode and plane of the whole launch 0.13 ns on a
-  // full chip.  So, with windows per mode, above one lag of the longest window per 2500
-  // modes and planes (compensated, unsplit against split: 2048^2 x 2 at 400 lags 763 and
+  // full chip.  So, with windows per mode, from 32 lags (float64: 36; the split costs 2 to 11
+  // per cent at 26 and saves 3 to 8 at 42: 256^2, float32 34.0 and 35.9 us at 26, 38.2 and
+  // 34.5 at 42) and above one lag of the longest window per 2500 modes and planes (compensated, unsplit against split: 2048^2 x 2 at 400 lags 763 and
   // 830 us a step, 2048^2 x 2 at 2000 913 and 829, 1024^2 at 300 184 and 125); with one
   // window, while the sweep has at most a wavefront per CU (float64: 256^2 at 60 lags 49
   // and 37 us, 512^2 at 40 65 and 65) and lags enough so far (256 x 64: float32 at 20 lags
@@ -631,7 +632,7 @@ hipError_t step_launch_s(const sbim_handle *h, const Group &g, const SweepArgs &
     const long long lags = std::min<long long>(g.wmax, sa.step + 1);  // of the longest chain so far
     long long nlong = 0;
     if (h->cfg.window_mode == SBIM_W_PER_MODE) {
-      if (lags * 2500 > g.M * g.np) {  // (blocks stand in order of falling window)
+      if (lags >= (sizeof(R) == 8 ? 36 : 32) && lags * 2500 > g.M * g.np) {  // (blocks stand in order of falling window)
         const long long all = std::partition_point(g.h_blk_cap.begin(), g.h_blk_cap.end(),
                                                    [](int cap) { return cap > kLongWindow; }) -
                               g.h_blk_cap.begin();

@@ -189,11 +189,15 @@ double mean_window(const sbim_config &c, double cs) {
   return sum / (static_cast<double>(n1) * h3);
 }
 
-// Sorted positions per kernel row of the matrix-core sweep: 4 where the classes
-// (modes of bitwise equal q, formed as plan_group forms it) pad to multiples of 4
-// with little waste, as on square grids ((+-m1, m3) and (+-m3, m1)); 2 where mostly
-// only +-m1 share q.
-int quad_modes(const sbim_config &c) {
+// How the modes share kernel rows (one for every bitwise distinct q, formed as plan_group
+// forms it): `quad`, the sorted positions per kernel row of the matrix-core sweep, 4 where
+// the classes pad to multiples of 4 with little waste, as on square grids ((+-m1, m3) and
+// (+-m3, m1)), 2 where mostly only +-m1 share q; and the modes per distinct q.
+struct RowSharing {
+  int quad;
+  double modes;
+};
+RowSharing row_sharing(const sbim_config &c) {
   const int n1 = c.n1, h3 = c.n3 / 2 + 1;
   const double two_pi = 2.0 * M_PI;
   std::vector<double> q(static_cast<size_t>(n1) * h3);
@@ -206,15 +210,34 @@ int quad_modes(const sbim_config &c) {
     }
   }
   std::sort(q.begin(), q.end());
-  long long by4 = 0, by2 = 0;  // padded positions
-  for (size_t s0 = 0; s0 < q.size();) {
+  long long by4 = 0, by2 = 0, classes = 0;  // padded positions
+  for (size_t s0 = 0; s0 < q.size(); ++classes) {
     size_t s1 = s0;
     while (s1 < q.size() && q[s1] == q[s0]) ++s1;
     by4 += (s1 - s0 + 3) / 4 * 4;
     by2 += (s1 - s0 + 1) / 2 * 2;
     s0 = s1;
   }
-  return 4 * by4 <= 5 * by2 ? 4 : 2;
+  return {4 * by4 <= 5 * by2 ? 4 : 2, static_cast<double>(q.size()) / classes};
+}
+
+// The window from which the time-tiled form is faster than the vector sweep (outside the
+// two-plane float32 form, where it is from 64 on).  Its fixed work (the middle level, 42 to
+// 74 slots of sums, two rings written) shows on grids that fill the chip, the more where its
+// quads share fewer modes than the vector sweep's rows do.  us a step, vector / tiled, one
+// plane if not said: 256^2 float64 W = 64 35.7 / 32.7; 512 x 256 float64 64 46 / 49, 128
+// 56 / 52; 512^2 float64 90 67 / 68, 128 74 / 71, float32 64 48.7 / 50.2, 90 52.2 / 51.2,
+// compensated 64 51.0 / 49.7; with two modes a quad: 512^2 float64 128 two planes 129 / 133,
+// 200 one plane 91 / 83, float32 90 55 / 57, 128 61 / 58; 1024 x 512, 3.7 modes a row,
+// float64 200 142 / 156, 320 185 / 167, two planes 320 304 / 314, 450 370 / 350.
+int tiled_window(const sbim_config &c, int np, const RowSharing &rows) {
+  const long long nh = static_cast<long long>(c.n1) * (c.n3 / 2 + 1);
+  const bool fp64 = c.precision == SBIM_FP64;
+  if (nh < (1 << 16)) return 64;
+  if (nh < (1 << 17)) return fp64 ? 96 : 64;
+  if (rows.quad == 4) return fp64 ? 112 : c.precision == SBIM_FP32 ? 80 : 64;
+  if (!fp64) return 132;
+  return rows.modes < 3 ? 160 : np == 2 ? 384 : 256;
 }
 
 // Order of the time-tiled form's positions.  `keys` come sorted by (W desc, q asc,
@@ -603,8 +626,8 @@ int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, vo
   // Matrix-core sweep: one window for every mode (modes of a class then share
   // their kernel rows), windows of 64 lags or more so that the deep sweep pays, and
   // (outside the two-plane float32 forms) more than kQuadMinLags modes x lags per
-  // plane: measured on gfx950 against the vector sweep, us per step, 128 x 64
-  // two-material float64 W = 150: 45 against 86; 512 x 128 two-material float32
+  // plane and the windows of tiled_window: measured on gfx950 against the vector sweep, us
+  // per step, 128 x 64 two-material float64 W = 150: 45 against 86; 512 x 128 two-material float32
   // W = 250: 58 against 103; 512^2 x 2 float64 W = 1000: 207 against 352; one plane
   // 256^2 float32 W = 300, forward and adjoint: 33 against 38.
   const int np0 = h->g[0].np;  // (planes per group: the same for every group)
@@ -612,12 +635,14 @@ int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, vo
   // (and a block's ring within the 32-bit byte offsets of the sweep's buffer loads)
   const bool able = c.window_mode == SBIM_W_FIXED && (in_order ? pair32 : c.window_cap >= kQuadMinWindow) &&
                     c.window_cap * (np0 * 3.0 * sbim::kLanes * 2) * static_cast<double>(h->rsize) < 4.29e9;
-  h->mfma = able && wbar >= 64 &&
-            (pair32 || static_cast<double>(h->nh) * c.window_cap > kQuadMinLags);
-  if (const char *env = std::getenv("SBIM_SWEEP_KIND")) {  // tuning override
-    if (std::strcmp(env, "valu") == 0) h->mfma = false;
-    if (std::strcmp(env, "mfma") == 0) h->mfma = able;
-  }
+  const char *kind = std::getenv("SBIM_SWEEP_KIND");  // tuning override
+  const bool vector = kind && std::strcmp(kind, "valu") == 0, matrix = kind && std::strcmp(kind, "mfma") == 0;
+  RowSharing rows{4, 0};
+  if (able && !in_order && !vector && (wbar >= 64 || matrix)) rows = row_sharing(c);
+  h->mfma = able && !vector &&
+            (matrix || (wbar >= 64 &&
+                        (pair32 || (static_cast<double>(h->nh) * c.window_cap > kQuadMinLags &&
+                                    c.window_cap >= tiled_window(c, np0, rows)))));
   int want_depth = 0;
   if (const char *env = std::getenv("SBIM_SWEEP_DEPTH")) want_depth = std::atoi(env);  // tuning override
   const auto vector_depth = [&]() {
@@ -628,7 +653,7 @@ int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, vo
   };
   h->tiled = h->mfma && !in_order;
   h->quad_modes = 4;
-  if (h->tiled && !(np0 == 2 && want_depth == 16)) h->quad_modes = quad_modes(c);
+  if (h->tiled && !(np0 == 2 && want_depth == 16)) h->quad_modes = rows.quad;
   if (!h->mfma)
     h->depth = vector_depth();
   else if (np0 == 2 && want_depth == 16)

@@ -211,7 +211,8 @@ __device__ __forceinline__ void sweep_span_staged(float (&sums)[6][kSums], const
 // SPLIT: the item is shared by a work-group of kSplit wavefronts: each takes LG of
 // kSplit LG chunks, and the wavefronts' sums meet in LDS, one step at a time, in order.
 // STAGED: the history comes through LDS (fetch_stage; cap >= kStageLags).
-template <typename R, int S, int T, bool COMP, bool SPLIT, bool STAGED = false>
+// ALONE: the work-group is one wavefront.
+template <typename R, int S, int T, bool COMP, bool SPLIT, bool STAGED, bool ALONE>
 __device__ __forceinline__ void sweep_item(const SweepArgs &a, long long kb, int r) {
   constexpr int NW = SPLIT ? kSplit : 1;
   using W = typename W4<R>::T;
@@ -227,10 +228,10 @@ __device__ __forceinline__ void sweep_item(const SweepArgs &a, long long kb, int
   const int p = r / NQ;
   const long long t0 = step + 1;
   const long long b = t0 % D + D * kb;
-  // (the work-group of one wavefront: not masked.  Known to be under 64, the compiler keeps
+  // (a wavefront alone: not masked.  Known to be under 64, the compiler keeps
   // the slot arithmetic of a single chunk in scalar registers, between the loads: float64
   // 512^2, two materials, 40 lags: the sweeps alone 23.2 and 21.0 us.)
-  const int lane = SPLIT ? threadIdx.x & (kLanes - 1) : threadIdx.x;
+  const int lane = ALONE ? threadIdx.x : threadIdx.x & (kLanes - 1);
   const int wave = SPLIT ? static_cast<int>(threadIdx.x) / kLanes : 0;
   const int lg = lane / (Q * T);
   const int u0 = (lane / Q) % T * S;        // first of the lane's S steps (t0 + u0 ..)
@@ -379,7 +380,7 @@ __device__ __forceinline__ void step_items(const SweepArgs &sa, const ModeArgs &
     // share the block's kernel rows in its L2.
     const int per_blk = sweep_lag_groups<R, S, T, COMP>() * T * sa.np;
     const long long kb = (item / (8LL * per_blk)) * 8 + (item & 7);
-    if (kb < sa.nphase) sweep_item<R, S, T, COMP, false, STAGED>(sa, kb, static_cast<int>((item >> 3) % per_blk));
+    if (kb < sa.nphase) sweep_item<R, S, T, COMP, false, STAGED, true>(sa, kb, static_cast<int>((item >> 3) % per_blk));
     return;
   }
   const long long k = xcd_chunk(item - sweep_items, nblocks * ma.np);
@@ -440,13 +441,13 @@ step_kernel_split(SweepArgs sa, ModeArgs ma, long long long_wgs, long long sweep
   const int per_blk = sweep_lag_groups<R, S, T, COMP>() * T * sa.np;
   if (wg < long_wgs) {
     const long long kb = (wg / (8LL * per_blk)) * 8 + (wg & 7);
-    if (kb < nlong) sweep_item<R, S, T, COMP, true>(sa, kb, static_cast<int>((wg >> 3) % per_blk));
+    if (kb < nlong) sweep_item<R, S, T, COMP, true, false, false>(sa, kb, static_cast<int>((wg >> 3) % per_blk));
     return;
   }
   if (wg < sweep_wgs) {
     const long long j = wg - long_wgs;
     const long long kb = nlong + ((j / (8LL * per_blk)) * 8 + (j & 7)) * kSplit + wave;
-    if (kb < sa.nphase) sweep_item<R, S, T, COMP, false>(sa, kb, static_cast<int>((j >> 3) % per_blk));
+    if (kb < sa.nphase) sweep_item<R, S, T, COMP, false, false, false>(sa, kb, static_cast<int>((j >> 3) % per_blk));
     return;
   }
   const long long n = nblocks * ma.np;

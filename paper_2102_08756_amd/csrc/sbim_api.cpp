@@ -189,36 +189,54 @@ double mean_window(const sbim_config &c, double cs) {
   return sum / (static_cast<double>(n1) * h3);
 }
 
-// How the modes share kernel rows (one for every bitwise distinct q, formed as plan_group
-// forms it): `quad`, the sorted positions per kernel row of the matrix-core sweep, 4 where
-// the classes pad to multiples of 4 with little waste, as on square grids ((+-m1, m3) and
-// (+-m3, m1)), 2 where mostly only +-m1 share q; and the modes per distinct q.
+// The distinct wavenumbers q of a configuration's modes, ascending, and each bin's place
+// among them.  (q is bitwise the same for +-m1, so half of the bins are sorted, once per plan.)
+struct WaveOrder {
+  std::vector<double> q;
+  std::vector<int> rank;  // [n1 h3] by bin i3 * n1 + i1
+};
+WaveOrder wave_order(const sbim_config &c) {
+  const int n1 = c.n1, h3 = c.n3 / 2 + 1, half = n1 / 2 + 1;
+  const double two_pi = 2.0 * M_PI;
+  std::vector<std::pair<double, int>> v(static_cast<size_t>(half) * h3);
+  for (int i3 = 0; i3 < h3; ++i3) {
+    const double k3 = (two_pi * i3) / (c.n3 * c.dx3);
+    for (int m1 = 0; m1 < half; ++m1) {
+      const double k1 = (two_pi * m1) / (n1 * c.dx1);
+      v[static_cast<size_t>(i3) * half + m1] = {std::sqrt(k1 * k1 + k3 * k3), i3 * half + m1};
+    }
+  }
+  std::sort(v.begin(), v.end());
+  WaveOrder o;
+  std::vector<int> at(v.size());
+  for (const auto &[q, bin] : v) {
+    if (o.q.empty() || q != o.q.back()) o.q.push_back(q);
+    at[bin] = static_cast<int>(o.q.size()) - 1;
+  }
+  o.rank.resize(static_cast<size_t>(n1) * h3);
+  for (int i3 = 0; i3 < h3; ++i3)
+    for (int i1 = 0; i1 < n1; ++i1)
+      o.rank[static_cast<size_t>(i3) * n1 + i1] = at[static_cast<size_t>(i3) * half + std::min(i1, n1 - i1)];
+  return o;
+}
+
+// How the modes share kernel rows (one for every distinct q): `quad`, the sorted positions
+// per kernel row of the matrix-core sweep, 4 where the classes pad to multiples of 4 with
+// little waste, as on square grids ((+-m1, m3) and (+-m3, m1)), 2 where mostly only +-m1
+// share q; and the modes per distinct q.
 struct RowSharing {
   int quad;
   double modes;
 };
-RowSharing row_sharing(const sbim_config &c) {
-  const int n1 = c.n1, h3 = c.n3 / 2 + 1;
-  const double two_pi = 2.0 * M_PI;
-  std::vector<double> q(static_cast<size_t>(n1) * h3);
-  for (int i1 = 0; i1 < n1; ++i1) {
-    const int m1 = i1 < n1 / 2 ? i1 : i1 - n1;
-    const double k1 = (two_pi * m1) / (n1 * c.dx1);
-    for (int i3 = 0; i3 < h3; ++i3) {
-      const double k3 = (two_pi * i3) / (c.n3 * c.dx3);
-      q[static_cast<size_t>(i1) * h3 + i3] = std::sqrt(k1 * k1 + k3 * k3);
-    }
+RowSharing row_sharing(const WaveOrder &o) {
+  std::vector<int> count(o.q.size(), 0);
+  for (int r : o.rank) ++count[r];
+  long long by4 = 0, by2 = 0;  // padded positions
+  for (int n : count) {
+    by4 += (n + 3) / 4 * 4;
+    by2 += (n + 1) / 2 * 2;
   }
-  std::sort(q.begin(), q.end());
-  long long by4 = 0, by2 = 0, classes = 0;  // padded positions
-  for (size_t s0 = 0; s0 < q.size(); ++classes) {
-    size_t s1 = s0;
-    while (s1 < q.size() && q[s1] == q[s0]) ++s1;
-    by4 += (s1 - s0 + 3) / 4 * 4;
-    by2 += (s1 - s0 + 1) / 2 * 2;
-    s0 = s1;
-  }
-  return {4 * by4 <= 5 * by2 ? 4 : 2, static_cast<double>(q.size()) / classes};
+  return {4 * by4 <= 5 * by2 ? 4 : 2, static_cast<double>(o.rank.size()) / o.q.size()};
 }
 
 // The window from which the time-tiled form is faster than the vector sweep (outside the
@@ -301,8 +319,8 @@ void quad_order(const sbim_config &c, int quad, std::vector<ModeKey> &keys) {
 // window 0, the class's row set), so each aligned group of `quad` lanes shares one
 // kernel row; `tiled` also orders those groups (quad_order) and lays the rings out
 // in time tiles.
-void plan_group(const sbim_config &c, int depth, int quad, bool tiled, Group &g, std::vector<double> &geom,
-                std::vector<long long> &blk_off, std::vector<int> &blk_cap,
+void plan_group(const sbim_config &c, const WaveOrder &order, int depth, int quad, bool tiled, Group &g,
+                std::vector<double> &geom, std::vector<long long> &blk_off, std::vector<int> &blk_cap,
                 std::vector<int> &blk_stride, std::vector<double> &cls_q) {
   const int n1 = c.n1, h3 = c.n3 / 2 + 1;
   const long long M = static_cast<long long>(n1) * h3;
@@ -314,7 +332,8 @@ void plan_group(const sbim_config &c, int depth, int quad, bool tiled, Group &g,
     const double k1 = (two_pi * m1) / (n1 * c.dx1);
     for (int i3 = 0; i3 < h3; ++i3) {
       const double k3 = (two_pi * i3) / (c.n3 * c.dx3);
-      const double q = std::sqrt(k1 * k1 + k3 * k3);
+      const long long f = static_cast<long long>(i3) * n1 + i1;  // spectrum bin
+      const double q = order.q[order.rank[f]];
       int w = 0;
       if (q > 0) {
         if (c.window_mode == SBIM_W_STATIC) {
@@ -326,7 +345,6 @@ void plan_group(const sbim_config &c, int depth, int quad, bool tiled, Group &g,
           w = static_cast<int>(std::min(static_cast<double>(c.window_cap), std::ceil(x)));
         }
       }
-      const long long f = static_cast<long long>(i3) * n1 + i1;  // spectrum bin
       keys[f] = ModeKey{w, q, static_cast<int>(f)};
       qv[f] = q;
       k1v[f] = k1;
@@ -341,11 +359,23 @@ void plan_group(const sbim_config &c, int depth, int quad, bool tiled, Group &g,
   // the traction spectrum are contiguous runs (quasi-dynamic, 1024^2 float64: the step
   // launch 40 us against 82 in order of q).
   const bool by_q = c.window_mode == SBIM_W_FIXED;
-  std::sort(keys.begin(), keys.end(), [by_q](const ModeKey &a, const ModeKey &b) {
-    if (a.w != b.w) return a.w > b.w;
-    if (by_q && a.q != b.q) return a.q < b.q;
-    return a.nat < b.nat;
-  });
+  // (the keys come by bin: a stable counting sort, by q, where the one mode without a
+  // window, q = 0, goes last, or by falling window)
+  {
+    int wtop = 0;
+    for (const ModeKey &k : keys) wtop = std::max(wtop, k.w);
+    const int nq = static_cast<int>(order.q.size());
+    const auto place = [&](const ModeKey &k) {
+      if (!by_q) return wtop - k.w;
+      return k.w > 0 ? order.rank[k.nat] : nq;
+    };
+    std::vector<long long> first(static_cast<size_t>(by_q ? nq : wtop) + 2, 0);
+    for (const ModeKey &k : keys) ++first[place(k) + 1];
+    std::partial_sum(first.begin(), first.end(), first.begin());
+    std::vector<ModeKey> sorted(keys.size());
+    for (const ModeKey &k : keys) sorted[first[place(k)]++] = k;
+    keys.swap(sorted);
+  }
   cls_q.clear();
   g.h_cls_w.clear();
   if (quad && !tiled) {
@@ -380,14 +410,7 @@ void plan_group(const sbim_config &c, int depth, int quad, bool tiled, Group &g,
   geom.assign(4 * Ms, 0.0);
   // a class per distinct q (which fixes W): kernel rows are shared whatever the order;
   // spectrum order numbers them as they come up
-  std::vector<double> uq;
-  std::vector<int> class_of;
-  if (!by_q && !tiled) {
-    uq = qv;
-    std::sort(uq.begin(), uq.end());
-    uq.erase(std::unique(uq.begin(), uq.end()), uq.end());
-    class_of.assign(uq.size(), -1);
-  }
+  std::vector<int> class_of(!by_q && !tiled ? order.q.size() : 0, -1);
   for (long long s = 0; s < Ms; ++s) {
     const ModeKey &k = keys[s];
     if (k.nat < 0) {  // padding: the class of the position before it, no window, no bin
@@ -397,8 +420,8 @@ void plan_group(const sbim_config &c, int depth, int quad, bool tiled, Group &g,
       continue;
     }
     int cls = 0;
-    if (k.w > 0 && tiled) {          // numbered in order of q
-      cls = static_cast<int>(std::lower_bound(cls_q.begin(), cls_q.end(), k.q) - cls_q.begin());
+    if (k.w > 0 && tiled) {          // numbered in order of q, without q = 0
+      cls = order.rank[k.nat] - 1;
     } else if (k.w > 0) {
       bool known = false;
       int *at = nullptr;
@@ -406,7 +429,7 @@ void plan_group(const sbim_config &c, int depth, int quad, bool tiled, Group &g,
         known = s > 0 && k.w == keys[s - 1].w && k.q == keys[s - 1].q;
         if (known) cls = g.h_cls[s - 1];
       } else {
-        at = &class_of[std::lower_bound(uq.begin(), uq.end(), k.q) - uq.begin()];
+        at = &class_of[order.rank[k.nat]];
         known = *at >= 0;
         if (known) cls = *at;
       }
@@ -605,6 +628,7 @@ int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, vo
   hipError_t e;
   h->ready = false;
   make_groups(h);
+  const WaveOrder order = wave_order(c);
   struct HostPlan {
     std::vector<double> geom, cls_q;
     std::vector<long long> blk_off, row0;
@@ -638,7 +662,7 @@ int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, vo
   const char *kind = std::getenv("SBIM_SWEEP_KIND");  // tuning override
   const bool vector = kind && std::strcmp(kind, "valu") == 0, matrix = kind && std::strcmp(kind, "mfma") == 0;
   RowSharing rows{4, 0};
-  if (able && !in_order && !vector && (wbar >= 64 || matrix)) rows = row_sharing(c);
+  if (able && !in_order && !vector && (wbar >= 64 || matrix)) rows = row_sharing(order);
   h->mfma = able && !vector &&
             (matrix || (wbar >= 64 &&
                         (pair32 || (static_cast<double>(h->nh) * c.window_cap > kQuadMinLags &&
@@ -663,7 +687,7 @@ int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, vo
   std::vector<HostPlan> plan(h->ngroups);
   auto plan_groups = [&]() {
     for (int i = 0; i < h->ngroups; ++i)
-      plan_group(c, h->depth, h->mfma ? h->quad_modes : 0, h->tiled, h->g[i], plan[i].geom,
+      plan_group(c, order, h->depth, h->mfma ? h->quad_modes : 0, h->tiled, h->g[i], plan[i].geom,
                  plan[i].blk_off, plan[i].blk_cap, plan[i].blk_stride, plan[i].cls_q);
   };
   plan_groups();

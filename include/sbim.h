@@ -264,13 +264,23 @@ int sbim_count_nonfinite_noalloc(sbim_handle *h, const void *field, long long *c
  * pending history sums of the coming steps, traction spectrum of the last
  * step, step counter) is sbim_state_bytes() bytes.  save/load
  * copy it to/from a caller-owned device buffer of at least that size,
- * asynchronously on the handle's stream.  A snapshot fits handles that order their
- * modes as the one that wrote it: same configuration and precision, same sweep form;
- * one of another order is refused with SBIM_E_INVALID.
+ * asynchronously on the handle's stream.  A snapshot is device memory as the handle's
+ * sweep form lays it out, and says so in its header: a handle of the same configuration
+ * and precision (float32 and compensated count as one) in any sweep form takes it, and
+ * goes on as if it had made the whole run itself.  Loading one of another form allocates
+ * a little device memory for the call, forms the pending sums again and synchronises the
+ * stream.  One of another size or configuration is refused with SBIM_E_INVALID.
+ * Snapshots without a form in their header (written by earlier versions) are taken in lag
+ * order; handles in the time-tiled matrix-core form refuse them (SBIM_SWEEP_KIND=valu at
+ * sbim_init plans one that takes them).
+ * sbim_snapshot_bytes: the size of the snapshot at src_device (of its first 256 bytes
+ * only these are read), running: whether it is one of the running state (below); a
+ * negative error code for NULL arguments or a corrupt header.
  */
 long long sbim_state_bytes(const sbim_handle *h);
 int sbim_save_state(sbim_handle *h, void *dst_device);
 int sbim_load_state(sbim_handle *h, const void *src_device);
+long long sbim_snapshot_bytes(sbim_handle *h, const void *src_device, int running);
 
 /*
  * Light snapshots for checkpointing long runs: only the float64 running state
@@ -282,8 +292,8 @@ int sbim_load_state(sbim_handle *h, const void *src_device);
  * pushing steps n0 .. a-1 again with a - n0 >= W_cap + sweep_depth + 2, the
  * handle is in the state of the original run at step a (bit for bit: the same
  * history entries, summed by the same launches); tractions of the replayed
- * steps before that are not the original ones.  SBIM_E_INVALID for NULL
- * arguments or a corrupt header.
+ * steps before that are not the original ones.  One of another sweep form is taken as a
+ * full snapshot is.  SBIM_E_INVALID for NULL arguments or a corrupt header.
  */
 long long sbim_running_state_bytes(const sbim_handle *h);
 int sbim_save_running_state(sbim_handle *h, void *dst_device);

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
+#include <vector>
 
 #include "internal.h"
 
@@ -26,7 +27,23 @@ hipError_t dev_alloc_bytes(void **p, size_t bytes);
 hipError_t upload(void *dst, const void *src, size_t bytes, hipStream_t st);
 int check_ptr(sbim_handle *h, const void *p, const char *name);
 
-// Device bytes of one material group's buffers and of the traction spectrum.
+// The distinct wavenumbers q of a configuration's modes, ascending, and each bin's place
+// among them.
+struct WaveOrder {
+  std::vector<double> q;
+  std::vector<int> rank;  // [n1 h3] by bin i3 * n1 + i1
+};
+WaveOrder wave_order(const sbim_config &c);
+sbim::Form form_of(const sbim_handle *h);
+// Mode geometry, windows, order and classes of a material group in a form (host).
+void plan_group(const sbim_config &c, const WaveOrder &order, const sbim::Form &form, sbim::Group &g,
+                std::vector<double> &geom, std::vector<long long> &blk_off, std::vector<int> &blk_cap,
+                std::vector<int> &blk_stride, std::vector<double> &cls_q);
+
+// Device bytes of one material group's buffers (in the handle's form, or in another) and
+// of the traction spectrum.
+long long ring_bytes(const sbim::Form &f, const sbim::Group &g, size_t real);
+long long pending_bytes(const sbim::Form &f, const sbim::Group &g, size_t real);
 long long ring_bytes(const sbim_handle *h, const sbim::Group &g);
 long long table_bytes(const sbim_handle *h, const sbim::Group &g);
 long long state_bytes_g(const sbim::Group &g);

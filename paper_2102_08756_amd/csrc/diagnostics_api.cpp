@@ -1,6 +1,6 @@
 // C ABI, diagnostics beside the step: non-finite counts, the traction
-// spectrum, handle information, snapshots (full and running state), work
-// accounting of a step, per-mode kernel rows and step-launch timing.
+// spectrum, handle information, work accounting of a step, per-mode kernel rows and
+// step-launch timing.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -84,194 +84,6 @@ int sbim_get_info(const sbim_handle *h, sbim_info *out) {
   out->sweep_matrix_cores = h->mfma ? 1 : 0;
   out->sweep_lag_chunks = h->mfma ? h->lag_chunks : 0;
   out->sweep_quads = h->mfma ? h->sweep_quads : 0;
-  return SBIM_OK;
-}
-
-}  // extern "C"
-
-namespace {
-
-// A snapshot is the device memory as it lies.  Its header says all that decides how: the
-// order of the modes, the padding of their classes, the size of its reals, the sweep depth
-// (which blocks lie together, how many pending sums); and its size.  Two earlier kinds
-// are told by their second word: one that names the order alone, and one without a mark,
-// in lag order with its pending sums as real arrays (those are formed again on loading).
-struct SnapshotHeader {
-  long long step, mark, bytes;
-  int order, quad, real, depth;
-};
-constexpr long long kFormMark = 0x5342494d464f524d;
-enum Order : int { kLagOrder = 0, kTimeTiled = 1, kSpectrumOrder = 2 };
-constexpr long long kOrderMark[3] = {0x5342494d4c414730, 0x5342494d54494c30, 0x5342494d53504330};
-
-Order order_of(const sbim_handle *h) {
-  if (h->tiled) return kTimeTiled;
-  return h->cfg.window_mode == SBIM_W_STATIC ? kSpectrumOrder : kLagOrder;
-}
-
-SnapshotHeader header_of(const sbim_handle *h, long long bytes) {
-  return {h->step, kFormMark, bytes, order_of(h), h->mfma ? h->quad_modes : 0,
-          static_cast<int>(h->rsize), h->depth};
-}
-
-bool marked(const SnapshotHeader &hd) {
-  return hd.mark == kFormMark ||
-         std::find(std::begin(kOrderMark), std::end(kOrderMark), hd.mark) != std::end(kOrderMark);
-}
-
-// (The running state is float64 in every precision and does not depend on the depth.)
-bool form_fits(const sbim_handle *h, const SnapshotHeader &hd, long long bytes, bool running) {
-  const SnapshotHeader own = header_of(h, bytes);
-  if (hd.mark == kFormMark)
-    return hd.bytes == own.bytes && hd.order == own.order && hd.quad == own.quad &&
-           (running || (hd.real == own.real && hd.depth == own.depth));
-  return marked(hd) ? hd.mark == kOrderMark[own.order] : own.order == kLagOrder;
-}
-
-hipError_t save_header(const sbim_handle *h, void *dst, long long bytes) {
-  const SnapshotHeader hd = header_of(h, bytes);
-  const hipError_t e = hipMemcpyAsync(dst, &hd, sizeof hd, hipMemcpyHostToDevice, h->stream);
-  return e != hipSuccess ? e : hipStreamSynchronize(h->stream);  // hd goes with this frame
-}
-
-hipError_t load_header(const sbim_handle *h, const void *src, SnapshotHeader &hd) {
-  const hipError_t e = hipMemcpyAsync(&hd, src, sizeof hd, hipMemcpyDeviceToHost, h->stream);
-  return e != hipSuccess ? e : hipStreamSynchronize(h->stream);
-}
-
-// The pending sums of group g, as the launches of the last `depth` steps before `step`
-// formed them, from the history in its ring.  (Entries that a later step has replaced
-// since meet rows past the window in the sums of `step` and after.)
-hipError_t form_sums(const sbim_handle *h, const Group &g, void *ring, void *pending, long long step) {
-  sbim::StepLaunch w{};
-  w.ring = ring;
-  w.pending = pending;
-  w.nh = h->nh;
-  w.dt = h->cfg.dt;
-  w.sums_only = true;
-  hipError_t e = hipMemsetAsync(pending, 0, pending_bytes(h, g), h->stream);
-  for (w.step = std::max(0LL, step - h->depth); w.step < step && e == hipSuccess; ++w.step)
-    e = sbim::launch_step(h, g, w);
-  return e;
-}
-
-}  // namespace
-
-extern "C" {
-
-long long sbim_state_bytes(const sbim_handle *h) {
-  if (!h) return -1;
-  long long b = 256 + out_spec_bytes(h);  // header (step counter), last traction spectrum
-  for (int i = 0; i < h->ngroups; ++i) {
-    const Group &g = h->g[i];
-    b += ring_bytes(h, g) + state_bytes_g(g) + pending_bytes(h, g);
-  }
-  return b;
-}
-
-int sbim_save_state(sbim_handle *h, void *dst) {
-  if (!h) return fail(nullptr, SBIM_E_INVALID, "handle is NULL");
-  int rc = check_ptr(h, dst, "dst");
-  if (rc) return rc;
-  char *d = static_cast<char *>(dst);
-  hipError_t e = save_header(h, d, sbim_state_bytes(h));
-  d += 256;
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(d, h->out_spec, out_spec_bytes(h), hipMemcpyDeviceToDevice, h->stream);
-  d += out_spec_bytes(h);
-  for (int i = 0; i < h->ngroups && e == hipSuccess; ++i) {
-    Group &g = h->g[i];
-    const size_t rb = ring_bytes(h, g), sb = state_bytes_g(g);
-    if (rb) e = hipMemcpyAsync(d, g.ring, rb, hipMemcpyDeviceToDevice, h->stream);
-    d += rb;
-    if (e == hipSuccess) e = hipMemcpyAsync(d, g.state, sb, hipMemcpyDeviceToDevice, h->stream);
-    d += sb;
-    const size_t pb = pending_bytes(h, g);
-    if (e == hipSuccess) e = hipMemcpyAsync(d, g.pending, pb, hipMemcpyDeviceToDevice, h->stream);
-    d += pb;
-  }
-  if (e != hipSuccess) return hip_fail(h, e, "sbim_save_state");
-  return SBIM_OK;
-}
-
-int sbim_load_state(sbim_handle *h, const void *src) {
-  if (!h) return fail(nullptr, SBIM_E_INVALID, "handle is NULL");
-  int rc = check_ptr(h, src, "src");
-  if (rc) return rc;
-  const char *s = static_cast<const char *>(src);
-  SnapshotHeader hd{};
-  hipError_t e = load_header(h, s, hd);
-  if (e != hipSuccess) return hip_fail(h, e, "sbim_load_state header");
-  if (hd.step < 0) return fail(h, SBIM_E_INVALID, "snapshot header is corrupt");
-  if (!form_fits(h, hd, sbim_state_bytes(h), false))
-    return fail(h, SBIM_E_INVALID, "snapshot orders the modes in another way than this handle");
-  s += 256;
-  e = hipMemcpyAsync(h->out_spec, s, out_spec_bytes(h), hipMemcpyDeviceToDevice, h->stream);
-  s += out_spec_bytes(h);
-  for (int i = 0; i < h->ngroups && e == hipSuccess; ++i) {
-    Group &g = h->g[i];
-    const size_t rb = ring_bytes(h, g), sb = state_bytes_g(g);
-    if (rb) e = hipMemcpyAsync(g.ring, s, rb, hipMemcpyDeviceToDevice, h->stream);
-    s += rb;
-    if (e == hipSuccess) e = hipMemcpyAsync(g.state, s, sb, hipMemcpyDeviceToDevice, h->stream);
-    s += sb;
-    const size_t pb = pending_bytes(h, g);
-    if (e == hipSuccess)
-      e = marked(hd) ? hipMemcpyAsync(g.pending, s, pb, hipMemcpyDeviceToDevice, h->stream)
-                     : form_sums(h, g, g.ring, g.pending, hd.step);
-    s += pb;
-  }
-  if (e != hipSuccess) return hip_fail(h, e, "sbim_load_state");
-  h->step = hd.step;
-  return SBIM_OK;
-}
-
-long long sbim_running_state_bytes(const sbim_handle *h) {
-  if (!h) return -1;
-  long long b = 256;  // header (step counter)
-  for (int i = 0; i < h->ngroups; ++i) b += state_bytes_g(h->g[i]);
-  return b;
-}
-
-int sbim_save_running_state(sbim_handle *h, void *dst) {
-  if (!h) return fail(nullptr, SBIM_E_INVALID, "handle is NULL");
-  int rc = check_ptr(h, dst, "dst");
-  if (rc) return rc;
-  char *d = static_cast<char *>(dst);
-  hipError_t e = save_header(h, d, sbim_running_state_bytes(h));
-  d += 256;
-  for (int i = 0; i < h->ngroups && e == hipSuccess; ++i) {
-    const Group &g = h->g[i];
-    e = hipMemcpyAsync(d, g.state, state_bytes_g(g), hipMemcpyDeviceToDevice, h->stream);
-    d += state_bytes_g(g);
-  }
-  if (e != hipSuccess) return hip_fail(h, e, "sbim_save_running_state");
-  return SBIM_OK;
-}
-
-int sbim_load_running_state(sbim_handle *h, const void *src) {
-  if (!h) return fail(nullptr, SBIM_E_INVALID, "handle is NULL");
-  int rc = check_ptr(h, src, "src");
-  if (rc) return rc;
-  const char *s = static_cast<const char *>(src);
-  SnapshotHeader hd{};
-  hipError_t e = load_header(h, s, hd);
-  if (e != hipSuccess) return hip_fail(h, e, "sbim_load_running_state header");
-  if (hd.step < 0) return fail(h, SBIM_E_INVALID, "running-state snapshot header is corrupt");
-  if (!form_fits(h, hd, sbim_running_state_bytes(h), true))
-    return fail(h, SBIM_E_INVALID, "running-state snapshot orders the modes in another way than this handle");
-  s += 256;
-  for (int i = 0; i < h->ngroups && e == hipSuccess; ++i) {
-    Group &g = h->g[i];
-    e = hipMemcpyAsync(g.state, s, state_bytes_g(g), hipMemcpyDeviceToDevice, h->stream);
-    s += state_bytes_g(g);
-    // the history before the snapshot is gone: start from an empty ring and no pending sums
-    const size_t rb = static_cast<size_t>(ring_bytes(h, g));
-    if (e == hipSuccess && rb) e = hipMemsetAsync(g.ring, 0, rb, h->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(g.pending, 0, pending_bytes(h, g), h->stream);
-  }
-  if (e != hipSuccess) return hip_fail(h, e, "sbim_load_running_state");
-  h->step = hd.step;
   return SBIM_OK;
 }
 

@@ -77,6 +77,17 @@ struct Group {
   std::vector<int> h_cls_w, h_blk_cap;
 };
 
+// What decides, with the configuration, in which order a handle holds its modes and how its
+// history lies: steps of a sweep, sorted positions per kernel row (0: classes not padded),
+// the time-tiled ring, and modes in order of q also where one lag is all (older snapshots).
+struct Form {
+  int depth = 1, quad = 0;
+  bool tiled = false, by_q = false;
+};
+inline bool operator==(const Form &a, const Form &b) {
+  return a.depth == b.depth && a.quad == b.quad && a.tiled == b.tiled && a.by_q == b.by_q;
+}
+
 }  // namespace sbim
 
 struct sbim_handle {
@@ -196,6 +207,23 @@ hipError_t launch_step_quads(const sbim_handle *h, const Group &g, const SweepAr
                              const ModeArgs &ma, long long mode_blocks, hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_step_pairs(const sbim_handle *h, const Group &g, const SweepArgs &sa,
                              const ModeArgs &ma, long long mode_blocks, hipEvent_t ev0, hipEvent_t ev1);
+
+// relocate.hip: history and running state from one form's order and layout into another's.
+// One side of it: a group's ring (with the recent ring of the time-tiled form) and blocks.
+struct RingSide {
+  void *ring;
+  const long long *off;   // [nblocks] device, as Group::blk_off ...
+  const int *cap, *stride;
+  long long M, nblocks, records;
+  bool tiled;
+};
+// The entries of the last steps before `step` that both sides hold, of every position s of
+// `to` (from position map[s], -1: none); the rest of `to` is cleared by the caller.
+hipError_t launch_relocate_ring(bool fp64, const RingSide &from, const RingSide &to, const int *map,
+                                int np, long long step, int wmax, hipStream_t st);
+// state[r][s] = src[r][map[s]] (0 where there is none) for `rows` rows of complex float64.
+hipError_t launch_relocate_state(const double *src, long long src_M, double *dst, long long M,
+                                 const int *map, int rows, hipStream_t st);
 
 // fault.hip: interface solve of a frictional fault between the two sides.
 // Fields are [component][cell] with cell = i1 * n3 + i3; u, v hold the upper

@@ -117,17 +117,24 @@ void free_handle(sbim_handle *h) {
   delete h;
 }
 
-long long ring_bytes(const sbim_handle *h, const Group &g) {
-  return (g.ring_records + (h->tiled ? sbim::kRecent * g.nblocks : 0)) * g.np * 3LL * sbim::kLanes * 2 *
-         static_cast<long long>(h->rsize);
+sbim::Form form_of(const sbim_handle *h) {
+  return {h->depth, h->mfma ? h->quad_modes : 0, h->tiled, false};
 }
+long long ring_bytes(const sbim::Form &f, const Group &g, size_t real) {
+  return (g.ring_records + (f.tiled ? sbim::kRecent * g.nblocks : 0)) * g.np * 3LL * sbim::kLanes * 2 *
+         static_cast<long long>(real);
+}
+long long ring_bytes(const sbim_handle *h, const Group &g) { return ring_bytes(form_of(h), g, h->rsize); }
 long long table_bytes(const sbim_handle *h, const Group &g) {
   return g.table_rows * 4LL * static_cast<long long>(h->rsize);
 }
 long long state_bytes_g(const Group &g) { return g.np * 3LL * g.M * 16; }
+long long pending_bytes(const sbim::Form &f, const Group &g, size_t real) {
+  return (f.depth + 1LL + (f.tiled ? sbim::kMidPeriod + 1 : 0)) * g.np * 10LL * g.M *
+         static_cast<long long>(real);
+}
 long long pending_bytes(const sbim_handle *h, const Group &g) {
-  return (h->depth + 1LL + (h->tiled ? sbim::kMidPeriod + 1 : 0)) * g.np * 10LL * g.M *
-         static_cast<long long>(h->rsize);
+  return pending_bytes(form_of(h), g, h->rsize);
 }
 long long out_spec_bytes(const sbim_handle *h) {
   return static_cast<long long>(h->cfg.nplanes) * 3 * h->nh * 2 * static_cast<long long>(h->rsize);
@@ -189,12 +196,7 @@ double mean_window(const sbim_config &c, double cs) {
   return sum / (static_cast<double>(n1) * h3);
 }
 
-// The distinct wavenumbers q of a configuration's modes, ascending, and each bin's place
-// among them.  (q is bitwise the same for +-m1, so half of the bins are sorted, once per plan.)
-struct WaveOrder {
-  std::vector<double> q;
-  std::vector<int> rank;  // [n1 h3] by bin i3 * n1 + i1
-};
+// (q is bitwise the same for +-m1, so half of the bins are sorted.)
 WaveOrder wave_order(const sbim_config &c) {
   const int n1 = c.n1, h3 = c.n3 / 2 + 1, half = n1 / 2 + 1;
   const double two_pi = 2.0 * M_PI;
@@ -319,9 +321,11 @@ void quad_order(const sbim_config &c, int quad, std::vector<ModeKey> &keys) {
 // window 0, the class's row set), so each aligned group of `quad` lanes shares one
 // kernel row; `tiled` also orders those groups (quad_order) and lays the rings out
 // in time tiles.
-void plan_group(const sbim_config &c, const WaveOrder &order, int depth, int quad, bool tiled, Group &g,
+void plan_group(const sbim_config &c, const WaveOrder &order, const sbim::Form &form, Group &g,
                 std::vector<double> &geom, std::vector<long long> &blk_off, std::vector<int> &blk_cap,
                 std::vector<int> &blk_stride, std::vector<double> &cls_q) {
+  const int depth = form.depth, quad = form.quad;
+  const bool tiled = form.tiled;
   const int n1 = c.n1, h3 = c.n3 / 2 + 1;
   const long long M = static_cast<long long>(n1) * h3;
   const double two_pi = 2.0 * M_PI;
@@ -358,7 +362,7 @@ void plan_group(const sbim_config &c, const WaveOrder &order, int depth, int qua
   // window stay in spectrum order, so the gathers of the spectrum and the scatters of
   // the traction spectrum are contiguous runs (quasi-dynamic, 1024^2 float64: the step
   // launch 40 us against 82 in order of q).
-  const bool by_q = c.window_mode == SBIM_W_FIXED;
+  const bool by_q = c.window_mode == SBIM_W_FIXED || form.by_q;
   // (the keys come by bin: a stable counting sort, by q, where the one mode without a
   // window, q = 0, goes last, or by falling window)
   {
@@ -687,8 +691,8 @@ int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, vo
   std::vector<HostPlan> plan(h->ngroups);
   auto plan_groups = [&]() {
     for (int i = 0; i < h->ngroups; ++i)
-      plan_group(c, order, h->depth, h->mfma ? h->quad_modes : 0, h->tiled, h->g[i], plan[i].geom,
-                 plan[i].blk_off, plan[i].blk_cap, plan[i].blk_stride, plan[i].cls_q);
+      plan_group(c, order, form_of(h), h->g[i], plan[i].geom, plan[i].blk_off, plan[i].blk_cap,
+                 plan[i].blk_stride, plan[i].cls_q);
   };
   plan_groups();
   if (h->mfma && !h->tiled) {

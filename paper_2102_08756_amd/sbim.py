@@ -30,7 +30,7 @@ EXPORTS = (
     "sbim_init", "sbim_push_displacement", "sbim_tractions", "sbim_backward",
     "sbim_backward_reset", "sbim_reset", "sbim_destroy", "sbim_last_error", "sbim_set_stream",
     "sbim_set_dt", "sbim_count_nonfinite", "sbim_count_nonfinite_noalloc", "sbim_traction_spectrum",
-    "sbim_get_info", "sbim_state_bytes", "sbim_save_state", "sbim_load_state",
+    "sbim_get_info", "sbim_state_bytes", "sbim_save_state", "sbim_load_state", "sbim_snapshot_bytes",
     "sbim_running_state_bytes", "sbim_save_running_state", "sbim_load_running_state", "sbim_step_work",
     "sbim_mode_kernel", "sbim_profile_conv", "sbim_conv_timing",
     "sbim_fault_create", "sbim_fault_step", "sbim_fault_read", "sbim_fault_reset",
@@ -112,6 +112,7 @@ def load_library(path=LIB_PATH):
         "sbim_load_running_state": (i, [vp, vp]),
         "sbim_save_state": (i, [vp, vp]),
         "sbim_load_state": (i, [vp, vp]),
+        "sbim_snapshot_bytes": (ll, [vp, vp, i]),
         "sbim_step_work": (i, [vp, ll, ctypes.POINTER(d), ctypes.POINTER(d)]),
         "sbim_mode_kernel": (i, [vp, i, i, i, ctypes.POINTER(d), i]),
         "sbim_profile_conv": (i, [vp, i]),
@@ -328,9 +329,20 @@ class SBIM:
         self._check(self._L.sbim_save_state(self._h, _ptr(buf)))
         return buf
 
-    def load_state(self, buf):
-        if buf.numel() < self.state_bytes() or buf.device != self.device:
+    def _check_snapshot(self, buf, running):
+        """The buffer holds the snapshot that its header names (of any sweep form)."""
+        need = 256
+        if buf.device == self.device and buf.numel() >= need:
+            self._sync_stream()
+            need = int(self._L.sbim_snapshot_bytes(self._h, _ptr(buf), running))
+            self._check(min(need, 0))
+        if buf.numel() < need or buf.device != self.device:
             raise ValueError("snapshot buffer too small or on the wrong device")
+
+    def load_state(self, buf):
+        """Restore a snapshot; one that a handle of another sweep form wrote is moved into this
+        handle's."""
+        self._check_snapshot(buf, 0)
         self._sync_stream()
         self._check(self._L.sbim_load_state(self._h, _ptr(buf)))
 
@@ -351,7 +363,7 @@ class SBIM:
         """Restore a light snapshot; the history ring and pending sums start empty, so the
         next W_cap + sweep_depth + 2 pushes rebuild what the tractions need."""
         if buf.numel() < self.running_state_bytes() or buf.device != self.device:
-            raise ValueError("snapshot buffer too small or on the wrong device")
+            self._check_snapshot(buf, 1)
         self._sync_stream()
         self._check(self._L.sbim_load_running_state(self._h, _ptr(buf)))
 

@@ -76,30 +76,80 @@ FORMS = {
     "bimaterial": (dict(n1=8, n3=16, window_cap=21, planes=BIMATERIAL), "fp32", ("mfma", None), ("valu", 12)),
     "per_mode": (dict(n1=16, n3=16, window_cap=50, window_mode="per_mode", eta_w=1.0, planes=TWO), "fp64",
                  ("valu", 6), ("valu", 12)),
+    # a step before the first tile is whole, windows past the tiles' end, two steps a tile
+    "tiled_fp64_to_vector": (dict(n1=16, n3=16, window_cap=21, planes=TWO), "fp64", ("mfma", None), ("valu", None)),
+    "vector_to_quads": (dict(n1=16, n3=16, window_cap=5, planes=ONE), "fp32", ("valu", 8), ("mfma", None)),
 }
 
 
+@pytest.mark.parametrize("cut", [2, 61])
 @pytest.mark.parametrize("running", [False, True])
 @pytest.mark.parametrize("case", sorted(FORMS))
-def test_snapshot_of_another_form(case, running, monkeypatch):
-    """Refused, or the steps after it are those of a handle of the reading form that made the
-    whole run (after the running state: the steps once the history is rebuilt)."""
+def test_snapshot_of_another_form(case, running, cut, monkeypatch):
+    """The steps after it are those of a handle of the reading form that made the whole run
+    (after the running state: the steps once the history is rebuilt)."""
     cfg, precision, (kind_a, depth_a), (kind_b, depth_b) = FORMS[case]
     a = handle(monkeypatch, cfg, precision, kind_a, depth_a)
     own = handle(monkeypatch, cfg, precision, kind_b, depth_b)
     b = handle(monkeypatch, cfg, precision, kind_b, depth_b)
-    cut, replay = 61, b.replay_steps() if running else 0
+    replay = b.replay_steps() if running else 0
     fields = pushes(a, cut + replay + 45)
     for sb in (a, own):
         for u in fields[:cut]:
             sb.push(u)
     snap = a.save_running_state() if running else a.save_state()
-    try:
-        (b.load_running_state if running else b.load_state)(snap)
-    except (SBIMError, ValueError):
-        return
+    (b.load_running_state if running else b.load_state)(snap)
     for u in fields[cut:cut + replay]:
         own.push(u)
         b.push(u)
     for x, y in zip(steps(b, fields[cut + replay:]), steps(own, fields[cut + replay:])):
         assert torch.equal(x, y)
+
+
+def test_snapshot_without_a_mark_where_one_lag_is_all(monkeypatch):
+    """Quasi-dynamic handles kept their modes by wavenumber, then by bin."""
+    n1, n3 = 16, 8
+    cfg = dict(n1=n1, n3=n3, dx1=0.7, window_cap=1, window_mode="static", planes=TWO, input_kind="increment")
+    sb = handle(monkeypatch, cfg, "fp64")
+    fields = pushes(sb, 9)
+    steps(sb, fields[:6])
+    snap = sb.save_state()
+    want = steps(sb, fields[6:])
+    m1 = torch.arange(n1)
+    k1 = (6.283185307179586 * torch.where(m1 < n1 // 2, m1, m1 - n1).double()) / (n1 * 0.7)
+    k3 = (6.283185307179586 * torch.arange(n3 // 2 + 1).double()) / n3
+    q = (k1[None, :] ** 2 + k3[:, None] ** 2).sqrt().reshape(-1).tolist()
+    by_bin = sorted(range(len(q)), key=lambda b: (q[b] == 0, b))      # now
+    by_q = sorted(range(len(q)), key=lambda b: (q[b] == 0, q[b], b))  # then
+    old = torch.tensor([by_bin.index(b) for b in by_q], device=DEV)
+    m, p, out = len(q), 2, 256 + 2 * 3 * len(q) * 16
+    slots = sb.info()["sweep_depth"] + 1
+    snap[8:256] = 0
+    end = snap.numel() - slots * p * 5 * m * 16
+    state = snap[end - p * 3 * m * 16:end].view(torch.float64).reshape(p * 3, m, 2)
+    state.copy_(state[:, old].contiguous())
+    # (the ring: one slot a block; blocks of a phase lie together, 80 modes make two)
+    ring = snap[out:end - p * 3 * m * 16].view(torch.float64).reshape(-1, p, 3, 64, 2)
+    flat = ring.permute(1, 2, 0, 3, 4).reshape(p, 3, -1, 2)[:, :, :m]
+    pad = torch.zeros(p, 3, ring.shape[0] * 64, 2, dtype=torch.float64, device=DEV)
+    pad[:, :, :m] = flat[:, :, old]
+    ring.copy_(pad.reshape(p, 3, ring.shape[0], 64, 2).permute(2, 0, 1, 3, 4))
+    sb.reset()
+    sb.load_state(snap)
+    got = steps(sb, fields[6:])
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+    sb.close()
+
+
+@pytest.mark.parametrize("change", [dict(n1=32), dict(window_cap=21), dict(planes=ONE)])
+def test_snapshot_of_another_configuration_is_refused(change, monkeypatch):
+    cfg = dict(n1=16, n3=16, window_cap=24, planes=TWO)
+    a = handle(monkeypatch, cfg, "fp64")
+    b = handle(monkeypatch, dict(cfg, **change), "fp64", "mfma")
+    a.push(a.new_field().normal_())
+    snap = torch.cat([a.save_state(), torch.zeros(1 << 22, dtype=torch.uint8, device=DEV)])
+    with pytest.raises(SBIMError, match="another configuration"):
+        b.load_state(snap)
+    with pytest.raises(ValueError, match="too small"):
+        a.load_state(snap[:a.state_bytes() - 256])
+    assert b.info()["step"] == 0

@@ -403,9 +403,10 @@ typedef struct {
  * sbim_fault_create: a fault on handle h (planes as described above, handle at
  * step 0).  The parameter arrays are copied (the caller may free them
  * afterwards) and checked on the device; synchronises the stream.  A float32
- * handle whose sweep would sum its lags out of order on the matrix cores is planned
- * again with the sums in order (sbim_get_info and the snapshot sizes follow): the
- * stick/slip history depends on their rounding.
+ * handle whose sweep sums its lags out of order on the matrix cores is planned again
+ * with the sums in order, once everything else has succeeded (sbim_get_info and the
+ * snapshot sizes follow; the handle keeps that form after sbim_fault_destroy): the
+ * stick/slip history depends on their rounding.  An adjoint history is kept.
  * SBIM_E_INVALID names the first offending cell (non-finite value, d_c <= 0,
  * mu_k < 0 or mu_s < mu_k).  A cell can be locked (a bonded interface) by a
  * static coefficient that no traction reaches.
@@ -512,8 +513,9 @@ typedef struct {
 
 /*
  * sbim_strip_create: a strip on handle h (one plane of side +1, or planes of
- * sides +1, -1 when layers_below > 0; dx1 == dx3; at step 0) with the fault parameters of sbim_fault_params (copied and
- * checked on the device; synchronises the stream).
+ * sides +1, -1 when layers_below > 0; dx1 == dx3; at step 0) with the fault parameters of
+ * sbim_fault_params (copied and checked on the device; synchronises the stream).  A float32
+ * handle is planned again with its sums in order as by sbim_fault_create.
  */
 int sbim_strip_create(sbim_handle *h, const sbim_strip_config *cfg, const sbim_fault_params *prm,
                       sbim_strip **out);

@@ -55,7 +55,15 @@ long long out_spec_bytes(const sbim_handle *h);
 hipError_t fft_forward(sbim_handle *h, const void *field, void *spec);
 hipError_t fft_inverse(sbim_handle *h, const void *spec, void *scratch, void *field,
                        const void *add);
-// Plan a float32 handle at step 0 with its history sums in lag order (fault, strip).
+// The plan of a handle's groups and their device memory (sbim_api.cpp); the groups' memory
+// freed; the adjoint buffers, allocated and cleared on first use.
+int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, void **tables = nullptr);
+void free_group(sbim::Group &g);
+int ensure_adjoint(sbim_handle *h);
+// Plans a handle in the time-tiled form again with its sums in lag order, its forward and
+// adjoint histories kept (snapshot_api.cpp).
+int replan_in_order(sbim_handle *h);
+// Plan a float32 handle with its history sums in lag order (fault, strip).
 int keep_sum_order(sbim_handle *h);
 // One forward step: transform u (and v for VEL_INPUT), then the step launch of
 // every material group with the given rule for the damping term's velocity.

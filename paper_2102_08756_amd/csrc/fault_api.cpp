@@ -75,8 +75,6 @@ int sbim_fault_create(sbim_handle *h, const sbim_fault_params *prm, sbim_fault *
     return fail(h, SBIM_E_INVALID,
                 "a fault needs plane 0 with side +1 and, if present, plane 1 with side -1");
   if (h->step != 0) return fail(h, SBIM_E_STATE, "a fault starts from a handle at step 0");
-  const int order = keep_sum_order(h);
-  if (order) return order;
   sbim_fault *f = new (std::nothrow) sbim_fault;
   if (!f) return fail(h, SBIM_E_OOM, "host allocation failed");
   f->h = h;
@@ -127,7 +125,8 @@ int sbim_fault_create(sbim_handle *h, const sbim_fault_params *prm, sbim_fault *
                 "0 <= mu_k <= mu_s",
                 cell / h->n3, cell % h->n3);
   }
-  int rc = fault_clear(f);
+  int rc = keep_sum_order(h);
+  if (!rc) rc = fault_clear(f);
   if (rc) {
     free_fault(f);
     return rc;

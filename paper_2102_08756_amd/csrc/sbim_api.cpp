@@ -627,7 +627,7 @@ void make_groups(sbim_handle *h) {
 // forms.  `tables` (or null): kernel tables of an earlier plan of the same fixed
 // windows, whose classes and rows are the same; the groups take them over.  Errors are
 // reported on `eh` (null: for sbim_last_error(NULL)); the caller frees the groups then.
-int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, void **tables = nullptr) {
+int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, void **tables) {
   const sbim_config &c = h->cfg;
   hipError_t e;
   h->ready = false;
@@ -855,39 +855,16 @@ int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, vo
   return SBIM_OK;
 }
 
-
 // The in-order form for a float32 handle that will drive a fault or a strip: the
 // stick/slip state follows the rounding of the history sums from step to step, so the
-// order of the sums is part of those results.  The handle is at step 0: it is planned
-// again, all but its kernel tables.  For the same reason its transforms keep the
+// order of the sums is part of those results.  For the same reason its transforms keep the
 // two-kernel form (the compiler fuses multiply-adds differently in the whole-field one).
-// Handles whose adjoint has been used
-// (their adjoint history would be lost) keep the form they have.
 int keep_sum_order(sbim_handle *h) {
-  h->in_order = !h->fp64;
-  if (h->fp64 || !h->tiled) return SBIM_OK;
-  for (int i = 0; i < h->ngroups; ++i)
-    if (h->g[i].state_adj) return SBIM_OK;
-  hipError_t e = hipStreamSynchronize(h->stream);
-  if (e != hipSuccess) return hip_fail(h, e, "planning the history sums in order");
-  // (fixed windows: classes are the distinct q in ascending order in every form, so the
-  // kernel tables stay)
-  auto plan = [&](bool in_order) {
-    void *tables[SBIM_MAX_PLANES] = {};
-    for (int i = 0; i < h->ngroups; ++i) {
-      std::swap(tables[i], h->g[i].table);
-      free_group(h->g[i]);
-    }
-    const int code = plan_handle(h, in_order, 0, h, tables);
-    for (void *t : tables)
-      if (t) (void)hipFree(t);
-    return code;
-  };
-  const int rc = plan(true);
-  if (rc == SBIM_OK) return rc;
-  const std::string why = h->err;
-  (void)plan(false);  // back to what it was; without memory for either the handle is not ready
-  h->err = why;
+  if (h->fp64) return SBIM_OK;
+  const bool was = h->in_order;
+  h->in_order = true;
+  const int rc = h->tiled ? replan_in_order(h) : SBIM_OK;
+  if (rc) h->in_order = was;
   return rc;
 }
 

@@ -134,10 +134,16 @@ hipError_t form_sums(const sbim_handle *h, const Group &g, void *ring, void *pen
   return e;
 }
 
-// Moves a history of form f (ring, running state) into group g's own layout and forms its
-// pending sums; without `src_ring` only the state, and an empty history.  Synchronises.
-int move_group(sbim_handle *h, Group &g, const Form &f, const Layout &from, const void *src_ring,
-               const double *src_state, long long step) {
+// A group's forward or adjoint history: ring, running state, adjoint's reverse running sum.
+struct History {
+  void *ring;
+  double *state, *lam;
+};
+
+// Moves a history of form f into group g's own layout at `to` and forms its pending sums;
+// without a ring only the state, and an empty history.  Synchronises.
+int move_group(sbim_handle *h, const Group &g, const Form &f, const Layout &from, const History &src,
+               const History &to, void *pending, long long step) {
   const long long nb = from.g.nblocks;
   std::vector<int> at(h->nh, -1), map(g.M, -1);
   for (long long t = 0; t < from.g.M; ++t)
@@ -155,19 +161,20 @@ int move_group(sbim_handle *h, Group &g, const Form &f, const Layout &from, cons
   if (e == hipSuccess) e = upload(d_cap, from.cap.data(), nb * sizeof(int), h->stream);
   if (e == hipSuccess) e = upload(d_stride, from.stride.data(), nb * sizeof(int), h->stream);
   if (e == hipSuccess)
-    e = sbim::launch_relocate_state(src_state, from.g.M, g.state, g.M, d_map, g.np * 3, h->stream);
+    e = sbim::launch_relocate_state(src.state, from.g.M, to.state, g.M, d_map, g.np * 3, h->stream);
+  if (e == hipSuccess && src.lam)
+    e = sbim::launch_relocate_state(src.lam, from.g.M, to.lam, g.M, d_map, g.np * 3, h->stream);
   const size_t rb = static_cast<size_t>(ring_bytes(h, g));
-  if (e == hipSuccess && rb) e = hipMemsetAsync(g.ring, 0, rb, h->stream);
-  if (src_ring) {
-    const sbim::RingSide src{const_cast<void *>(src_ring), d_off, d_cap, d_stride, from.g.M, nb,
-                             from.g.ring_records, f.tiled};
-    const sbim::RingSide dst{g.ring, g.blk_off, g.blk_cap, g.blk_stride, g.M, g.nblocks, g.ring_records,
-                             h->tiled};
+  if (e == hipSuccess && rb) e = hipMemsetAsync(to.ring, 0, rb, h->stream);
+  if (src.ring) {
+    const sbim::RingSide a{src.ring, d_off, d_cap, d_stride, from.g.M, nb, from.g.ring_records, f.tiled};
+    const sbim::RingSide b{to.ring, g.blk_off, g.blk_cap, g.blk_stride, g.M, g.nblocks, g.ring_records,
+                           h->tiled};
     if (e == hipSuccess)
-      e = sbim::launch_relocate_ring(h->fp64, src, dst, d_map, g.np, step, g.wmax, h->stream);
-    if (e == hipSuccess) e = form_sums(h, g, g.ring, g.pending, step);
+      e = sbim::launch_relocate_ring(h->fp64, a, b, d_map, g.np, step, g.wmax, h->stream);
+    if (e == hipSuccess) e = form_sums(h, g, to.ring, pending, step);
   } else if (e == hipSuccess) {
-    e = hipMemsetAsync(g.pending, 0, pending_bytes(h, g), h->stream);
+    e = hipMemsetAsync(pending, 0, pending_bytes(h, g), h->stream);
   }
   const hipError_t e2 = hipStreamSynchronize(h->stream);  // the host arrays and the maps go
   if (e == hipSuccess) e = e2;
@@ -178,6 +185,84 @@ int move_group(sbim_handle *h, Group &g, const Form &f, const Layout &from, cons
 }
 
 }  // namespace
+
+namespace sbim_api {
+
+// The histories wait in host memory meanwhile, which the moves read directly: both forms
+// need not fit the device together.
+int replan_in_order(sbim_handle *h) {
+  const Form was = form_of(h);
+  const int n = h->ngroups;
+  const bool fwd = h->step > 0, adj = h->bstep > 0;
+  std::vector<Layout> from;
+  if (fwd || adj) from = lay_out(h, was);
+  size_t total = 0;
+  for (int i = 0; i < n; ++i) {
+    const size_t rb = ring_bytes(h, h->g[i]), sb = state_bytes_g(h->g[i]);
+    total += (fwd ? rb + sb : 0) + (adj ? rb + 2 * sb : 0);
+  }
+  char *host = nullptr;
+  hipError_t e = total ? hipHostMalloc(reinterpret_cast<void **>(&host), total, hipHostMallocDefault) : hipSuccess;
+  if (e != hipSuccess) return fail(h, SBIM_E_OOM, "host memory for the history of a handle planned again");
+  // (forward ring, state; adjoint ring, state, reverse sum) per group, from or to `p`
+  const auto each = [&](auto &&part) {
+    char *p = host;
+    for (int i = 0; i < n; ++i) {
+      const Group &g = fwd || adj ? from[i].g : h->g[i];
+      const size_t rb = ring_bytes(was, g, h->rsize), sb = state_bytes_g(g);
+      for (int a = 0; a < 2; ++a) {
+        if (!(a ? adj : fwd)) continue;
+        part(i, a != 0, History{p, reinterpret_cast<double *>(p + rb), reinterpret_cast<double *>(p + rb + sb)}, rb, sb);
+        p += rb + (a ? 2 : 1) * sb;
+      }
+    }
+  };
+  each([&](int i, bool a, const History &to, size_t rb, size_t sb) {
+    const Group &g = h->g[i];
+    const hipMemcpyKind kind = hipMemcpyDeviceToHost;
+    if (e == hipSuccess) e = hipMemcpyAsync(to.ring, a ? g.ring_adj : g.ring, rb, kind, h->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(to.state, a ? g.state_adj : g.state, sb, kind, h->stream);
+    if (e == hipSuccess && a) e = hipMemcpyAsync(to.lam, g.lam_adj, sb, kind, h->stream);
+  });
+  const hipError_t e2 = hipStreamSynchronize(h->stream);
+  if (e == hipSuccess) e = e2;
+  if (e != hipSuccess) {
+    if (host) (void)hipHostFree(host);
+    return hip_fail(h, e, "planning the history sums in order");
+  }
+  // (fixed windows: classes are the distinct q in ascending order in every form, so the
+  // kernel tables stay)
+  const auto plan = [&](bool in_order) {
+    void *tables[SBIM_MAX_PLANES] = {};
+    for (int i = 0; i < n; ++i) {
+      std::swap(tables[i], h->g[i].table);
+      free_group(h->g[i]);
+    }
+    const int code = plan_handle(h, in_order, 0, h, tables);
+    for (void *t : tables)
+      if (t) (void)hipFree(t);
+    return code;
+  };
+  int rc = plan(true);
+  std::string why = h->err;
+  if (rc) (void)plan(false);  // back to what it was; without memory for either the handle is not ready
+  int back = h->ready ? SBIM_OK : SBIM_E_STATE;
+  if (!back && adj) back = ensure_adjoint(h);
+  each([&](int i, bool a, const History &src, size_t, size_t) {
+    Group &g = h->g[i];
+    if (back) return;
+    back = a ? move_group(h, g, was, from[i], src, {g.ring_adj, g.state_adj, g.lam_adj}, g.pending_adj, h->bstep)
+             : move_group(h, g, was, from[i], {src.ring, src.state, nullptr}, {g.ring, g.state, nullptr},
+                          g.pending, h->step);
+  });
+  if (host) (void)hipHostFree(host);
+  if (back) h->ready = false;  // (its history is lost)
+  if (!rc && back) rc = back, why = h->err;
+  if (rc) h->err = why;
+  return rc;
+}
+
+}  // namespace sbim_api
 
 extern "C" {
 
@@ -244,7 +329,9 @@ int sbim_load_state(sbim_handle *h, const void *src) {
       if (e == hipSuccess) e = hipMemcpyAsync(g.state, s + rb, sb, hipMemcpyDeviceToDevice, h->stream);
       if (e == hipSuccess) e = hipMemcpyAsync(g.pending, s + rb + sb, pb, hipMemcpyDeviceToDevice, h->stream);
     } else {
-      rc = move_group(h, g, f, from[i], s, reinterpret_cast<const double *>(s + rb), hd.step);
+      char *p = const_cast<char *>(s);
+      rc = move_group(h, g, f, from[i], {p, reinterpret_cast<double *>(p + rb), nullptr},
+                      {g.ring, g.state, nullptr}, g.pending, hd.step);
       if (rc) return rc;
     }
     s += rb + sb + pb;
@@ -294,7 +381,8 @@ int sbim_load_running_state(sbim_handle *h, const void *src) {
       if (e == hipSuccess) e = hipMemsetAsync(g.pending, 0, pending_bytes(h, g), h->stream);
       s += state_bytes_g(g);
     } else {
-      rc = move_group(h, g, f, from[i], nullptr, reinterpret_cast<const double *>(s), hd.step);
+      rc = move_group(h, g, f, from[i], {nullptr, reinterpret_cast<double *>(const_cast<char *>(s)), nullptr},
+                      {g.ring, g.state, nullptr}, g.pending, hd.step);
       if (rc) return rc;
       s += state_bytes_g(from[i].g);
     }

@@ -166,8 +166,6 @@ int sbim_strip_create(sbim_handle *h, const sbim_strip_config *sc, const sbim_fa
     }
   }
   if (h->step != 0) return fail(h, SBIM_E_STATE, "a strip starts from a handle at step 0");
-  const int order = keep_sum_order(h);
-  if (order) return order;
   sbim_strip *s = new (std::nothrow) sbim_strip;
   if (!s) return fail(h, SBIM_E_OOM, "host allocation failed");
   s->h = h;
@@ -266,7 +264,8 @@ int sbim_strip_create(sbim_handle *h, const sbim_strip_config *sc, const sbim_fa
                 "0 <= mu_k <= mu_s",
                 cell / h->n3, cell % h->n3);
   }
-  int rc = strip_clear(s);
+  int rc = keep_sum_order(h);
+  if (!rc) rc = strip_clear(s);
   if (rc) {
     free_strip(s);
     return rc;

@@ -1,0 +1,198 @@
+"""GPU: float32 handles that drive a fault or a strip sum their lags in order.
+
+Two planes of one material and a window of 64 lags or more run the in-order matrix-core sweep
+(pairs.hip); it is compared with the oracle on random pushes to a handle that a fault was opened on
+and closed.  Bar: relative L2 1e-5, as for the other float32 sweeps.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from paper_2102_08756_amd import SBIM, Config, Fault, SBIMError, Strip
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+ONE = [dict(side=1)]
+TWO = [dict(side=1), dict(side=-1, mu=2.5)]
+SWITCHES = ("SBIM_SWEEP_KIND", "SBIM_SWEEP_DEPTH", "SBIM_SWEEP_CHUNKS", "SBIM_SWEEP_QUADS")
+
+
+@pytest.fixture(autouse=True)
+def default_rule(monkeypatch):
+    for k in SWITCHES:
+        monkeypatch.delenv(k, raising=False)
+
+
+def handle(cfg, precision="fp32_comp"):
+    return SBIM(Config.from_dict(cfg, precision=precision), device=DEV)
+
+
+def friction(sb, d_c=0.4):
+    n1, n3 = sb.cfg.n1, sb.cfg.n3
+    gen = torch.Generator().manual_seed(2)
+    tau0 = torch.stack([1.0 + 0.2 * torch.rand(n1, n3, generator=gen, dtype=torch.float64),
+                        torch.full((n1, n3), -1.6, dtype=torch.float64),
+                        torch.zeros(n1, n3, dtype=torch.float64)])
+    f = [torch.full((n1, n3), v, dtype=torch.float64) for v in (0.677, 0.525, d_c)]
+    return [t.to(DEV) for t in [tau0] + f]
+
+
+# lags summed in blocks of 4 by 1, 2 or 4 wavefronts: either side of a block and of each range
+CASES = [(64, 32, 1), (65, 16, 1), (67, 32, 1), (126, 32, 1), (127, 16, 2), (131, 32, 2), (260, 32, 4)]
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp32_comp"])
+@pytest.mark.parametrize("window,depth,ranges", CASES)
+def test_in_order_sweep_matches_oracle(window, depth, ranges, precision, monkeypatch):
+    if depth == 16:
+        monkeypatch.setenv("SBIM_SWEEP_DEPTH", "16")
+    n1, n3 = (16, 16) if window % 2 else (16, 8)
+    cfg = dict(n1=n1, n3=n3, dx3=1.0 if window != 131 else 1.3, window_cap=window, planes=TWO,
+               input_kind="increment")
+    sb = handle(cfg, precision)
+    assert sb.info()["sweep_matrix_cores"] == 1
+    f = Fault(sb, *friction(sb))
+    f.close()
+    info = sb.info()
+    want = min(ranges, 2) if precision == "fp32_comp" else ranges
+    assert info["sweep_matrix_cores"] == 1 and info["sweep_depth"] == depth
+    assert info["sweep_lag_chunks"] == want
+    u = np.random.default_rng(6).standard_normal((window + 45, 2, 3, n1, n3))
+    ref = oracle.forward(cfg, u)
+    got = np.empty(u.shape)
+    cut = window + 20
+    for n, x in enumerate(torch.tensor(u, dtype=sb.dtype, device=DEV)):
+        sb.push(x)
+        got[n] = sb.tractions().double().cpu().numpy()
+        if n == cut:
+            snap = sb.save_state()
+    err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    print(f"[order] W {window} depth {depth} {precision}: {err:.1e}", flush=True)
+    assert err < 1e-5
+    # a snapshot restores it, also from the form of a handle without a fault
+    sb.reset()
+    sb.load_state(snap)
+    plain = handle(cfg, precision)
+    plain.load_state(snap)
+    for n in range(cut + 1, cut + 20):
+        x = torch.tensor(u[n], dtype=sb.dtype, device=DEV)
+        sb.push(x)
+        plain.push(x)
+        assert np.array_equal(sb.tractions().double().cpu().numpy(), got[n]), n
+        assert np.linalg.norm(plain.tractions().double().cpu().numpy() - ref[n]) < 1e-4 * np.linalg.norm(ref[n])
+    sb.close()
+    plain.close()
+
+
+@pytest.mark.parametrize("planes", [ONE, TWO], ids=["one", "two"])
+def test_adjoint_in_order(planes):
+    """The adjoint of the in-order forms against the oracle's transpose."""
+    cfg = dict(n1=16, n3=16, window_cap=70, planes=planes, input_kind="absolute")
+    sb = handle(cfg)
+    Fault(sb, *friction(sb)).close()
+    g = np.random.default_rng(8).standard_normal((100, len(planes), 3, 16, 16))
+    ref, _ = oracle.adjoint(cfg, g)
+    out = np.empty(g.shape)
+    for n in range(99, -1, -1):
+        out[n] = sb.backward(torch.tensor(g[n], dtype=sb.dtype, device=DEV)).double().cpu().numpy()
+    err = np.linalg.norm(out - ref) / np.linalg.norm(ref)
+    assert err < 1e-5
+    sb.close()
+
+
+def tiled_cfg(planes, kind="increment"):
+    """A float32 handle in the time-tiled form by rule."""
+    n = 128 if planes is ONE else 32
+    return dict(n1=n, n3=n, window_cap=70, planes=planes, input_kind=kind)
+
+
+@pytest.mark.parametrize("planes", [ONE, TWO], ids=["one", "two"])
+@pytest.mark.parametrize("what", ["fault", "strip"])
+def test_refused_creation_changes_nothing(what, planes):
+    sb, own = (handle(tiled_cfg(planes)) for _ in range(2))
+    info, size = sb.info(), sb.state_bytes()
+    prm = friction(sb)
+    prm[3][3, 5] = 0.0
+    layer = [(1.0, 1.8, 1.0)]
+    with pytest.raises(SBIMError, match="cell"):
+        if what == "fault":
+            Fault(sb, *prm)
+        else:
+            Strip(sb, layer, *prm, layers_below=None if planes is ONE else layer)
+    assert sb.info() == info and sb.state_bytes() == size
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    for _ in range(80):
+        u = torch.randn(sb.new_field().shape, dtype=sb.dtype, device=DEV, generator=gen)
+        sb.push(u)
+        own.push(u)
+        assert torch.equal(sb.tractions(), own.tractions())
+    sb.close()
+    own.close()
+
+
+@pytest.mark.parametrize("kind", ["absolute", "increment"])
+@pytest.mark.parametrize("planes", [ONE, TWO], ids=["one", "two"])
+def test_fault_does_not_depend_on_earlier_use(planes, kind):
+    """An adjoint before the fault changes neither its steps nor, in progress, itself.  (With
+    increments its running sum holds the earlier results, rounded as they were summed then.)"""
+    runs, grads = [], []
+    for used in (0, 5):
+        sb = handle(tiled_cfg(planes, kind))
+        gen = torch.Generator(device=DEV).manual_seed(3)
+        fields = [torch.randn(sb.new_field().shape, dtype=sb.dtype, device=DEV, generator=gen) for _ in range(90)]
+        for u in fields[:used * 8]:
+            sb.backward(u)
+        f = Fault(sb, *friction(sb))
+        for u in fields[used * 8:80]:
+            sb.backward(u)
+        grads.append([sb.backward(u).clone() for u in fields[80:]])
+        runs.append(f.run(85))
+        f.close()
+        sb.close()
+    for a, b in zip(*runs):
+        assert torch.equal(a, b)
+    assert runs[0][1].abs().max() > 0
+    for a, b in zip(*grads):
+        assert torch.equal(a, b) if kind == "absolute" else (a - b).norm() < 1e-5 * b.norm()
+
+
+def test_fault_after_an_adjoint_that_was_reset():
+    out = []
+    for used in (False, True):
+        sb = handle(tiled_cfg(ONE))
+        if used:
+            sb.backward(sb.new_field().normal_())
+            sb.push(sb.new_field().normal_())
+            sb.reset()
+        f = Fault(sb, *friction(sb))
+        assert sb.info()["sweep_matrix_cores"] == 0
+        out.append(f.run(80))
+        f.close()
+        sb.close()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+def test_two_sided_strip_in_order(monkeypatch):
+    """Equal materials, compensated float32: the steps of the vector sweep within its rounding."""
+    wl = workloads.TPV3
+    mat = (wl["rho"], wl["cp"], wl["cs"])
+    plane = dict(mu=wl["rho"] * wl["cs"] ** 2, cs=wl["cs"], cp=wl["cp"])
+    n, dx, out = 16, 100.0, []
+    gen = torch.Generator().manual_seed(4)
+    tau0 = torch.stack([65e6 + 20e6 * torch.rand(n, n, generator=gen, dtype=torch.float64),
+                        torch.full((n, n), -120e6, dtype=torch.float64), torch.zeros(n, n, dtype=torch.float64)])
+    prm = [tau0.to(DEV)] + [torch.full((n, n), v, dtype=torch.float64, device=DEV) for v in (0.677, 0.525, 0.4)]
+    for kind in (None, "valu"):
+        if kind:
+            monkeypatch.setenv("SBIM_SWEEP_KIND", kind)
+        sb = handle(dict(n1=n, n3=n, dx1=dx, dx3=dx, dt=0.3 * dx / wl["cp"], window_cap=70,
+                         planes=[dict(plane, side=1), dict(plane, side=-1)]))
+        s = Strip(sb, [mat], *prm, layers_below=[mat])
+        assert sb.info()["sweep_matrix_cores"] == (0 if kind else 1)
+        out.append(s.run(100) + (s.read("displacement"),))
+        s.close()
+        sb.close()
+    for a, b in zip(*out):
+        assert float((a - b).norm() / b.norm()) < 1e-5

@@ -127,9 +127,15 @@ typedef struct {
   int sweep_matrix_cores;      /* 1: the history sweep runs as 16x16x4 matrix-core products
                                   (one window for every mode, of 64 lags or more; and
                                   either a float32 form with two planes of one material or
-                                  more than 2^18 modes x lags per plane); float32 handles
+                                  more than 2^18 modes x lags per plane and, on grids that
+                                  fill the chip, longer windows); float32 handles
                                   that drive a fault or a strip sum their lags in order,
-                                  with two planes of one material on the matrix cores too;
+                                  with two planes of one material on the matrix cores too.
+                                  Without device memory for the time-tiled matrix-core form
+                                  (which holds 42 to 74 pending sums per mode, the others
+                                  sweep_depth + 1), at sbim_init or at the first
+                                  sbim_backward for its adjoint, the handle is planned in
+                                  the form that a fault would use; snapshots fit either;
                                   SBIM_SWEEP_KIND=valu or mfma overrides it, for tuning */
   int sweep_lag_chunks;        /* matrix-core sweep: wavefronts per group of modes that
                                   share a kernel row, each summing a range of lags (1, 2

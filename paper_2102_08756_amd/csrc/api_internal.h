@@ -35,6 +35,7 @@ struct WaveOrder {
 };
 WaveOrder wave_order(const sbim_config &c);
 sbim::Form form_of(const sbim_handle *h);
+sbim::Form choose_form(const sbim_handle *h, const WaveOrder &order, bool in_order);
 // Mode geometry, windows, order and classes of a material group in a form (host).
 void plan_group(const sbim_config &c, const WaveOrder &order, const sbim::Form &form, sbim::Group &g,
                 std::vector<double> &geom, std::vector<long long> &blk_off, std::vector<int> &blk_cap,
@@ -63,6 +64,8 @@ int ensure_adjoint(sbim_handle *h);
 // Plans a handle in the time-tiled form again with its sums in lag order, its forward and
 // adjoint histories kept (snapshot_api.cpp).
 int replan_in_order(sbim_handle *h);
+// Whether that plan and its adjoint fit what is free and what the present plan holds.
+bool adjoint_fits_in_order(const sbim_handle *h, size_t free_b);
 // Plan a float32 handle with its history sums in lag order (fault, strip).
 int keep_sum_order(sbim_handle *h);
 // One forward step: transform u (and v for VEL_INPUT), then the step launch of

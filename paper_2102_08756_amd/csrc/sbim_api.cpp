@@ -117,6 +117,15 @@ void free_handle(sbim_handle *h) {
   delete h;
 }
 
+// Free device memory; the environment variable SBIM_MEMORY_LIMIT (bytes) stands in for less.
+hipError_t free_memory(size_t *free_b) {
+  size_t total = 0;
+  const hipError_t e = hipMemGetInfo(free_b, &total);
+  if (const char *env = std::getenv("SBIM_MEMORY_LIMIT"))
+    *free_b = std::min(*free_b, static_cast<size_t>(std::strtoull(env, nullptr, 10)));
+  return e;
+}
+
 sbim::Form form_of(const sbim_handle *h) {
   return {h->depth, h->mfma ? h->quad_modes : 0, h->tiled, false};
 }
@@ -230,11 +239,14 @@ struct RowSharing {
   int quad;
   double modes;
 };
-RowSharing row_sharing(const WaveOrder &o) {
+std::vector<int> modes_per_q(const WaveOrder &o) {
   std::vector<int> count(o.q.size(), 0);
   for (int r : o.rank) ++count[r];
+  return count;
+}
+RowSharing row_sharing(const WaveOrder &o) {
   long long by4 = 0, by2 = 0;  // padded positions
-  for (int n : count) {
+  for (int n : modes_per_q(o)) {
     by4 += (n + 3) / 4 * 4;
     by2 += (n + 1) / 2 * 2;
   }
@@ -530,15 +542,24 @@ hipError_t fft_inverse(sbim_handle *h, const void *spec, void *scratch, void *fi
 // is complete once its state_adj is set; a failed allocation or clear frees
 // that group's partial buffers again, so a later call starts from scratch.
 int ensure_adjoint(sbim_handle *h) {
+  size_t free_b = 0;
+  if (h->tiled && h->bstep == 0 && free_memory(&free_b) == hipSuccess) {
+    // no room beside the time-tiled form: the handle goes over to one that holds less
+    size_t all = 0;
+    for (int i = 0; i < h->ngroups; ++i)
+      if (const Group &g = h->g[i]; !g.state_adj)
+        all += ring_bytes(h, g) + 2 * state_bytes_g(g) + pending_bytes(h, g);
+    if (all && all + (h->out_adj ? 0 : out_spec_bytes(h)) > free_b && adjoint_fits_in_order(h, free_b))
+      if (const int rc = replan_in_order(h)) return rc;
+  }
   for (int i = 0; i < h->ngroups; ++i) {
     Group &g = h->g[i];
     if (g.state_adj) continue;
     const size_t rb = static_cast<size_t>(ring_bytes(h, g));
     const size_t sb = static_cast<size_t>(state_bytes_g(g));
     const size_t pb = static_cast<size_t>(pending_bytes(h, g));
-    size_t free_b = 0, total_b = 0;
     const size_t need = rb + 2 * sb + pb + (h->out_adj ? 0 : static_cast<size_t>(out_spec_bytes(h)));
-    if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && need > free_b)
+    if (free_memory(&free_b) == hipSuccess && need > free_b)
       return fail(h, SBIM_E_OOM, "adjoint buffers need %zu bytes, %zu free", need, free_b);
     void *ring = nullptr, *pending = nullptr;
     double *state = nullptr, *lam = nullptr;
@@ -621,23 +642,10 @@ void make_groups(sbim_handle *h) {
   }
 }
 
-// The plan of a handle's material groups (sweep form, mode order) and their device
-// memory, tables and cleared state; `extra` more bytes are needed beside them.  With
-// `in_order` the float32 history sums keep the lag order of the vector and in-order
-// forms.  `tables` (or null): kernel tables of an earlier plan of the same fixed
-// windows, whose classes and rows are the same; the groups take them over.  Errors are
-// reported on `eh` (null: for sbim_last_error(NULL)); the caller frees the groups then.
-int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, void **tables) {
+// The form of a handle's material groups by its configuration; `in_order`: the float32
+// history sums keep the lag order of the vector and in-order forms.
+sbim::Form choose_form(const sbim_handle *h, const WaveOrder &order, bool in_order) {
   const sbim_config &c = h->cfg;
-  hipError_t e;
-  h->ready = false;
-  make_groups(h);
-  const WaveOrder order = wave_order(c);
-  struct HostPlan {
-    std::vector<double> geom, cls_q;
-    std::vector<long long> blk_off, row0;
-    std::vector<int> blk_cap, blk_stride;
-  };
   // Sweep depth: steps served by one pass over a block's history.  Deeper
   // sweeps divide the history traffic, but the newest lags of each step (up
   // to depth + 1 of them) are summed by the mode items.  A lane holds the 10
@@ -655,8 +663,8 @@ int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, vo
   // their kernel rows), windows of 64 lags or more so that the deep sweep pays, and
   // (outside the two-plane float32 forms) more than kQuadMinLags modes x lags per
   // plane and the windows of tiled_window: measured on gfx950 against the vector sweep, us
-  // per step, 128 x 64 two-material float64 W = 150: 45 against 86; 512 x 128 two-material float32
-  // W = 250: 58 against 103; 512^2 x 2 float64 W = 1000: 207 against 352; one plane
+  // per step, 128 x 64 two-material float64 W = 150: 45 against 86; 512 x 128 two-material
+  // float32 W = 250: 58 against 103; 512^2 x 2 float64 W = 1000: 207 against 352; one plane
   // 256^2 float32 W = 300, forward and adjoint: 33 against 38.
   const int np0 = h->g[0].np;  // (planes per group: the same for every group)
   const bool pair32 = !h->fp64 && np0 == 2;
@@ -667,47 +675,65 @@ int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, vo
   const bool vector = kind && std::strcmp(kind, "valu") == 0, matrix = kind && std::strcmp(kind, "mfma") == 0;
   RowSharing rows{4, 0};
   if (able && !in_order && !vector && (wbar >= 64 || matrix)) rows = row_sharing(order);
-  h->mfma = able && !vector &&
-            (matrix || (wbar >= 64 &&
-                        (pair32 || (static_cast<double>(h->nh) * c.window_cap > kQuadMinLags &&
-                                    c.window_cap >= tiled_window(c, np0, rows)))));
+  const bool mfma = able && !vector &&
+                    (matrix || (wbar >= 64 &&
+                                (pair32 || (static_cast<double>(h->nh) * c.window_cap > kQuadMinLags &&
+                                            c.window_cap >= tiled_window(c, np0, rows)))));
   int want_depth = 0;
   if (const char *env = std::getenv("SBIM_SWEEP_DEPTH")) want_depth = std::atoi(env);  // tuning override
-  const auto vector_depth = [&]() {
+  sbim::Form f;
+  if (!mfma) {
     if (want_depth == 1 || want_depth == 2 || want_depth == 4 || want_depth == 6 ||
         want_depth == 8 || want_depth == 12 || want_depth == 16)
-      return want_depth;
-    return wbar < 64 ? 6 : (h->comp || h->fp64 || wbar >= 1500 ? 12 : 8);
-  };
-  h->tiled = h->mfma && !in_order;
-  h->quad_modes = 4;
-  if (h->tiled && !(np0 == 2 && want_depth == 16)) h->quad_modes = rows.quad;
-  if (!h->mfma)
-    h->depth = vector_depth();
-  else if (np0 == 2 && want_depth == 16)
-    h->depth = 16;
-  else
-    h->depth = h->quad_modes == 2 && np0 == 1 ? 64 : 32;
-  std::vector<HostPlan> plan(h->ngroups);
-  auto plan_groups = [&]() {
-    for (int i = 0; i < h->ngroups; ++i)
-      plan_group(c, order, form_of(h), h->g[i], plan[i].geom, plan[i].blk_off, plan[i].blk_cap,
-                 plan[i].blk_stride, plan[i].cls_q);
-  };
-  plan_groups();
-  if (h->mfma && !h->tiled) {
-    // The in-order form addresses a block's history with 32-bit byte offsets from
-    // its slot 0: every block's capacity times its slot stride must stay below 2^30
-    // floats, else the vector sweep plans the group instead.
-    for (long long b = 0; b < h->g[0].nblocks && h->mfma; ++b)
-      if (static_cast<long long>(plan[0].blk_cap[b]) * plan[0].blk_stride[b] * 2 * 3 * sbim::kLanes * 2 >=
-          (1LL << 30))
-        h->mfma = false;
-    if (!h->mfma) {
-      h->depth = wbar < 64 ? 6 : (h->comp || wbar >= 1500 ? 12 : 8);
-      plan_groups();
-    }
+      f.depth = want_depth;
+    else
+      f.depth = wbar < 64 ? 6 : (h->comp || h->fp64 || wbar >= 1500 ? 12 : 8);
+    return f;
   }
+  const bool short_depth = np0 == 2 && want_depth == 16;
+  f.tiled = !in_order;
+  f.quad = f.tiled && !short_depth ? rows.quad : 4;
+  f.depth = short_depth ? 16 : f.quad == 2 && np0 == 1 ? 64 : 32;
+  if (!f.tiled) {
+    // The in-order form addresses a block's history with 32-bit byte offsets from
+    // its slot 0: every block's capacity times its slot stride (the blocks of its phase)
+    // must stay below 2^30 floats, else the vector sweep plans the group instead.
+    const std::vector<int> count = modes_per_q(order);
+    long long padded = 0;
+    for (size_t r = 1; r < count.size(); ++r) padded += (count[r] + 3) / 4 * 4;
+    const long long blocks = (padded + sbim::kLanes - 1) / sbim::kLanes;
+    if (c.window_cap * ((blocks + f.depth - 1) / f.depth) * 2LL * 3 * sbim::kLanes * 2 >= (1LL << 30))
+      return {wbar < 64 ? 6 : (h->comp || wbar >= 1500 ? 12 : 8), 0, false, false};
+  }
+  return f;
+}
+
+// The plan of a handle's material groups (sweep form, mode order) and their device
+// memory, tables and cleared state; `extra` more bytes are needed beside them.  With
+// `in_order` the float32 history sums keep the lag order of the vector and in-order
+// forms.  `tables` (or null): kernel tables of an earlier plan of the same fixed
+// windows, whose classes and rows are the same; the groups take them over.  Errors are
+// reported on `eh` (null: for sbim_last_error(NULL)); the caller frees the groups then.
+int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, void **tables) {
+  const sbim_config &c = h->cfg;
+  hipError_t e;
+  h->ready = false;
+  make_groups(h);
+  const WaveOrder order = wave_order(c);
+  struct HostPlan {
+    std::vector<double> geom, cls_q;
+    std::vector<long long> blk_off, row0;
+    std::vector<int> blk_cap, blk_stride;
+  };
+  const sbim::Form form = choose_form(h, order, in_order);
+  h->depth = form.depth;
+  h->mfma = form.quad != 0;
+  h->tiled = form.tiled;
+  h->quad_modes = form.quad ? form.quad : 4;
+  std::vector<HostPlan> plan(h->ngroups);
+  for (int i = 0; i < h->ngroups; ++i)
+    plan_group(c, order, form, h->g[i], plan[i].geom, plan[i].blk_off, plan[i].blk_cap,
+               plan[i].blk_stride, plan[i].cls_q);
   if (h->mfma) {
     if (h->tiled) {
       // Lag ranges per quad, one wavefront each: one for fewer than 4 rounds of 32 lags,
@@ -748,20 +774,12 @@ int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, vo
     if (!(tables && tables[i])) need += table_bytes(h, g);
     need += g.M * (4 * 2 + 8 + 32) + g.nblocks * 16 + g.nclasses * 20;
   }
-  size_t free_b = 0, total_b = 0;
-  e = hipMemGetInfo(&free_b, &total_b);
+  size_t free_b = 0;
+  e = free_memory(&free_b);
   if (e != hipSuccess) return fail(eh, SBIM_E_DEVICE, "hipMemGetInfo: %s", hipGetErrorString(e));
-  if (h->tiled) {
-    // The time-tiled form holds more sums per mode (and again for the adjoint): where
-    // both would not fit, plan the forms that hold less.
-    size_t adjoint = 0;
-    for (int i = 0; i < h->ngroups; ++i)
-      adjoint += ring_bytes(h, h->g[i]) + 2 * state_bytes_g(h->g[i]) + pending_bytes(h, h->g[i]);
-    if (need + adjoint + out_spec_bytes(h) > free_b) {
-      for (int i = 0; i < h->ngroups; ++i) free_group(h->g[i]);
-      return plan_handle(h, true, extra, eh);
-    }
-  }
+  // The time-tiled form holds more sums per mode: without room for it, the forms that hold
+  // less.  (Its adjoint's room is looked at when an adjoint is asked for: ensure_adjoint.)
+  if (h->tiled && need > free_b) return plan_handle(h, true, extra, eh, tables);
   if (need > free_b)
     return fail(eh, SBIM_E_OOM, "needs %zu bytes of device memory, %zu free", need, free_b);
 

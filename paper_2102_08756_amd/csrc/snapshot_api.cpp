@@ -188,6 +188,18 @@ int move_group(sbim_handle *h, const Group &g, const Form &f, const Layout &from
 
 namespace sbim_api {
 
+bool adjoint_fits_in_order(const sbim_handle *h, size_t free_b) {
+  const Form f = choose_form(h, wave_order(h->cfg), true);
+  const std::vector<Layout> to = lay_out(h, f);
+  long long need = h->out_adj ? 0 : out_spec_bytes(h), have = static_cast<long long>(free_b);
+  for (int i = 0; i < h->ngroups; ++i) {
+    const Group &a = to[i].g, &b = h->g[i];
+    need += 2 * (ring_bytes(f, a, h->rsize) + pending_bytes(f, a, h->rsize)) + 3 * state_bytes_g(a) + a.M * 48;
+    have += ring_bytes(h, b) + pending_bytes(h, b) + state_bytes_g(b) + b.M * 48;
+  }
+  return need <= have;
+}
+
 // The histories wait in host memory meanwhile, which the moves read directly: both forms
 // need not fit the device together.
 int replan_in_order(sbim_handle *h) {

@@ -26,6 +26,7 @@ hipError_t dev_alloc(T **p, size_t count) {
 hipError_t dev_alloc_bytes(void **p, size_t bytes);
 hipError_t upload(void *dst, const void *src, size_t bytes, hipStream_t st);
 int check_ptr(sbim_handle *h, const void *p, const char *name);
+int check_ready(sbim_handle *h);  // the groups hold their buffers (a failed plan leaves none)
 
 // The distinct wavenumbers q of a configuration's modes, ascending, and each bin's place
 // among them.

@@ -175,6 +175,7 @@ int sbim_mode_kernel(sbim_handle *h, int p, int i1, int i3, double *host_out, in
   if (p < 0 || p >= h->cfg.nplanes || i1 < 0 || i1 >= h->n1 || i3 < 0 || i3 >= h->h3 ||
       max_lags < 0 || (max_lags > 0 && !host_out))
     return fail(h, SBIM_E_INVALID, "bad arguments to sbim_mode_kernel");
+  if (int rc = check_ready(h)) return rc;
   const Group *gp = nullptr;
   for (int i = 0; i < h->ngroups; ++i)
     for (int k = 0; k < h->g[i].np; ++k)

@@ -523,6 +523,11 @@ int check_ptr(sbim_handle *h, const void *p, const char *name) {
   return SBIM_OK;
 }
 
+int check_ready(sbim_handle *h) {
+  if (h->ready) return SBIM_OK;
+  return fail(h, SBIM_E_STATE, "the handle has no history buffers: planning it again failed");
+}
+
 // Forward real 2-D FFT of a [P][3][n1][n3] field into `spec`.
 hipError_t fft_forward(sbim_handle *h, const void *field, void *spec) {
   return sbim::launch_fft_forward(h->fp64, field, spec, h->cfg.nplanes * 3, h->n1, h->n3,
@@ -889,7 +894,7 @@ int keep_sum_order(sbim_handle *h) {
 // One forward step: transform u (and v for VEL_INPUT), then the step launch of
 // every material group with the given rule for the damping term's velocity.
 int push_fields(sbim_handle *h, const void *u, const void *v, int vel_rule) {
-  if (!h->ready) return fail(h, SBIM_E_STATE, "the handle has no history buffers");
+  if (int rc = check_ready(h)) return rc;
   hipError_t e = fft_forward(h, u, h->spec);
   if (e != hipSuccess) return hip_fail(h, e, "forward FFT of u");
   if (vel_rule == sbim::VEL_INPUT) {
@@ -1016,7 +1021,8 @@ int sbim_backward(sbim_handle *h, const void *g_tau, void *du, void *dv) {
   if (rc) return rc;
   rc = check_ptr(h, du, "dL_du");
   if (rc) return rc;
-  if (!h->ready) return fail(h, SBIM_E_STATE, "the handle has no history buffers");
+  rc = check_ready(h);
+  if (rc) return rc;
   rc = ensure_adjoint(h);
   if (rc) return rc;
   hipError_t e = fft_forward(h, g_tau, h->spec);
@@ -1054,6 +1060,7 @@ int sbim_backward(sbim_handle *h, const void *g_tau, void *du, void *dv) {
 
 int sbim_backward_reset(sbim_handle *h) {
   if (!h) return fail(nullptr, SBIM_E_INVALID, "handle is NULL");
+  if (int rc = check_ready(h)) return rc;
   for (int i = 0; i < h->ngroups; ++i) {
     Group &g = h->g[i];
     if (!g.state_adj) continue;
@@ -1070,6 +1077,7 @@ int sbim_backward_reset(sbim_handle *h) {
 
 int sbim_reset(sbim_handle *h) {
   if (!h) return fail(nullptr, SBIM_E_INVALID, "handle is NULL");
+  if (int rc = check_ready(h)) return rc;
   for (int i = 0; i < h->ngroups; ++i) {
     Group &g = h->g[i];
     hipError_t e = hipSuccess;

@@ -295,6 +295,7 @@ long long sbim_snapshot_bytes(sbim_handle *h, const void *src, int running) {
 int sbim_save_state(sbim_handle *h, void *dst) {
   if (!h) return fail(nullptr, SBIM_E_INVALID, "handle is NULL");
   int rc = check_ptr(h, dst, "dst");
+  if (!rc) rc = check_ready(h);
   if (rc) return rc;
   char *d = static_cast<char *>(dst);
   hipError_t e = save_header(h, d, own_bytes(h, false));
@@ -320,6 +321,7 @@ int sbim_save_state(sbim_handle *h, void *dst) {
 int sbim_load_state(sbim_handle *h, const void *src) {
   if (!h) return fail(nullptr, SBIM_E_INVALID, "handle is NULL");
   int rc = check_ptr(h, src, "src");
+  if (!rc) rc = check_ready(h);
   if (rc) return rc;
   const char *s = static_cast<const char *>(src);
   SnapshotHeader hd{};
@@ -356,6 +358,7 @@ int sbim_load_state(sbim_handle *h, const void *src) {
 int sbim_save_running_state(sbim_handle *h, void *dst) {
   if (!h) return fail(nullptr, SBIM_E_INVALID, "handle is NULL");
   int rc = check_ptr(h, dst, "dst");
+  if (!rc) rc = check_ready(h);
   if (rc) return rc;
   char *d = static_cast<char *>(dst);
   hipError_t e = save_header(h, d, own_bytes(h, true));
@@ -372,6 +375,7 @@ int sbim_save_running_state(sbim_handle *h, void *dst) {
 int sbim_load_running_state(sbim_handle *h, const void *src) {
   if (!h) return fail(nullptr, SBIM_E_INVALID, "handle is NULL");
   int rc = check_ptr(h, src, "src");
+  if (!rc) rc = check_ready(h);
   if (rc) return rc;
   const char *s = static_cast<const char *>(src);
   SnapshotHeader hd{};

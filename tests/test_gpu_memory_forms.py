@@ -4,7 +4,7 @@ out by the first adjoint."""
 import pytest
 import torch
 
-from paper_2102_08756_amd import SBIM, Config, SBIMError
+from paper_2102_08756_amd import SBIM, Config, Fault, SBIMError
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -99,3 +99,23 @@ def test_without_room_for_any_form(monkeypatch):
     assert torch.equal(sb.backward(u[0]), own.backward(u[0]))
     sb.close()
     own.close()
+
+
+def test_handle_without_buffers_refuses_every_call(monkeypatch):
+    """Planned again for a fault without memory for any form: the calls say so."""
+    sb = handle(monkeypatch, "fp32")
+    u, snap, light = sb.new_field(), sb.save_state(), sb.save_running_state()
+    prm = [torch.full((3, 128, 128), -1.0, dtype=torch.float64, device=DEV)]
+    prm += [torch.full((128, 128), v, dtype=torch.float64, device=DEV) for v in (0.6, 0.5, 0.4)]
+    monkeypatch.setenv("SBIM_MEMORY_LIMIT", "1")
+    with pytest.raises(SBIMError, match="SBIM_E_OOM"):
+        Fault(sb, *prm)
+    monkeypatch.delenv("SBIM_MEMORY_LIMIT")
+    for call in (lambda: sb.push(u), lambda: sb.backward(u), lambda: sb.save_state(snap),
+                 lambda: sb.load_state(snap), lambda: sb.save_running_state(light),
+                 lambda: sb.load_running_state(light), sb.reset, sb.backward_reset,
+                 lambda: sb.mode_kernel(0, 1, 1, 4)):
+        with pytest.raises(SBIMError, match="SBIM_E_STATE.*no history buffers"):
+            call()
+    sb.info(), sb.state_bytes(), sb.step_work(3)
+    sb.close()

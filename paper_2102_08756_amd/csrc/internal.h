@@ -64,8 +64,8 @@ struct Group {
   void *ring = nullptr;           // [ring_records][np][3][64] complex (matrix-core form: in
                                   // tiles, then the recent ring [kRecent][nblocks][np][3][64])
   double *state = nullptr;        // [np][3][M] complex double (rotated frame, sorted)
-  void *pending = nullptr;        // [depth+1][np][5][M] complex: history sums of coming steps,
-                                  // then [kMidPeriod+1][np][5][M]: the middle level's, if any
+  void *pending = nullptr;        // [depth+1][np][5][M] complex: history sums of coming steps
+                                  // (float64 vector form: [depth+1][np][10][M] real), then [kMidPeriod+1][np][5][M]: the middle level's, if any
   // adjoint (allocated on first use)
   void *ring_adj = nullptr;
   void *pending_adj = nullptr;

@@ -218,7 +218,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs &a, long long kb, int
   using W = typename W4<R>::T;
   const cplx<R> *__restrict__ ring = static_cast<const cplx<R> *>(a.ring);
   const W *__restrict__ table = static_cast<const W *>(a.table);
-  cplx<R> *__restrict__ pending = static_cast<cplx<R> *>(a.pending);
+  void *const pending = a.pending;
   const long long M = a.M, step = a.step;
   const int np = a.np;
   constexpr int LG = sweep_lag_groups<R, S, T, COMP>();
@@ -361,8 +361,8 @@ __device__ __forceinline__ void sweep_item(const SweepArgs &a, long long kb, int
     if (wave == 0 && lg == 0 && valid) {
 #pragma unroll
       for (int t = 0; t < 5; ++t)
-        pending[((slot * np + p) * 5 + t) * M + sm] =
-            cplx<R>{acc[s][2 * t].value(), acc[s][2 * t + 1].value()};
+        store_sum<R, false>(pending, (slot * np + p) * 5LL, t, M, sm,
+                            cplx<R>{acc[s][2 * t].value(), acc[s][2 * t + 1].value()});
     }
   }
 }

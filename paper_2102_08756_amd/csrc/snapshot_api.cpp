@@ -19,7 +19,7 @@ namespace {
 // order of the modes, the padding of their classes, the size of its reals, the sweep depth
 // (which blocks lie together, how many pending sums); and its size.  Two earlier kinds
 // are told by their second word: one that names the order alone, and one without a mark,
-// in lag order (by q also where one lag is all) with its pending sums as real arrays.
+// in lag order (by q also where one lag is all); their pending sums lay in other ways.
 struct SnapshotHeader {
   long long step, mark, bytes;
   int order, quad, real, depth;
@@ -93,11 +93,9 @@ int snapshot_form(sbim_handle *h, const SnapshotHeader &hd, bool running, Form &
     const bool marked = std::find(std::begin(kOrderMark), std::end(kOrderMark), hd.mark) != std::end(kOrderMark);
     if (marked ? hd.mark != kOrderMark[order_of(h)] : h->tiled)
       return fail(h, SBIM_E_INVALID, "snapshot orders the modes in another way than this handle");
-    if (!marked) {
-      own = running && !is_static;  // (its pending sums are formed again)
-      f.by_q = is_static;
-      if (!own) from = lay_out(h, f);
-    }
+    f.by_q = is_static && !marked;
+    own = running && !f.by_q;  // (its pending sums are formed again)
+    if (!own) from = lay_out(h, f);
     return SBIM_OK;
   }
   f.depth = running ? mine.depth : hd.depth;

@@ -146,6 +146,31 @@ __device__ __forceinline__ void load_tile(typename RingTile<R>::V (&h)[3][2],
   }
 }
 
+// Pending sum t of position s: one complex array per sum, [slot][plane][5][M], or beside the
+// float64 vector sweep two real ones, [slot][plane][10][M] (1024 x 512 x 2, 128 lags: a launch
+// 173.3 us with complex sums, 168.1 so; float32 1024 x 512 x 2, 5 lags, 51.3 and 52.3).
+// `row`: 5 (slot planes + plane).
+template <typename R, bool TILED> constexpr bool kRealSums = sizeof(R) == 8 && !TILED;
+template <typename R, bool TILED>
+__device__ __forceinline__ void store_sum(void *pending, long long row, int t, long long M, long long s, cplx<R> v) {
+  if constexpr (kRealSums<R, TILED>) {
+    R *q = static_cast<R *>(pending) + (row + t) * 2 * M + s;
+    q[0] = v.x;
+    q[M] = v.y;
+  } else {
+    static_cast<cplx<R> *>(pending)[(row + t) * M + s] = v;
+  }
+}
+template <typename R, bool TILED>
+__device__ __forceinline__ cplx<R> load_sum(const void *pending, long long row, int t, long long M, long long s) {
+  if constexpr (kRealSums<R, TILED>) {
+    const R *q = static_cast<const R *>(pending) + (row + t) * 2 * M + s;
+    return cplx<R>{q[0], q[M]};
+  } else {
+    return static_cast<const cplx<R> *>(pending)[(row + t) * M + s];
+  }
+}
+
 // Mode item of step n for one (mode, plane): the push, then the traction of
 // the same step from the same registers.
 //   push:    rotate the new spectrum into the wavevector frame, update the
@@ -212,10 +237,9 @@ __device__ __forceinline__ void mode_step(const ModeArgs &a, int p, long long s)
 #pragma unroll
     for (int t = 0; t < 5; ++t) pend[t] = midv[t] = cplx<R>{R(0), R(0)};
     if (swept && (wl > 0 || !TILED)) {
-      const cplx<R> *__restrict__ q = static_cast<const cplx<R> *>(a.pending) +
-                                      (mod_step(step, S + 1) * np + p) * 5LL * M + s;
+      const long long row = (mod_step(step, S + 1) * np + p) * 5LL;
 #pragma unroll
-      for (int t = 0; t < 5; ++t) pend[t] = q[t * M];
+      for (int t = 0; t < 5; ++t) pend[t] = load_sum<R, TILED>(a.pending, row, t, M, s);
     }
     if (mids && wl > 0) {
       const cplx<R> *__restrict__ q = static_cast<const cplx<R> *>(a.mid) +

@@ -553,12 +553,12 @@ __global__ __launch_bounds__(kWholeThreads) void ifft_whole_kernel(
   const RowSlots rows{S, logNh};
   const ColumnSlots cols{S, logn1};
   const cplx<R> *src = spec + static_cast<long long>(blockIdx.x) * n1 * S;
-  cplx<R> v[kWholePerThread + 1];
+  cplx<R> v[kWholePerThread];
 #pragma unroll
-  for (int i = 0; i <= kWholePerThread; ++i)
+  for (int i = 0; i < kWholePerThread; ++i)
     v[i] = src[min(static_cast<int>(threadIdx.x) + i * kWholeThreads, n1 * S - 1)];
 #pragma unroll
-  for (int i = 0; i <= kWholePerThread; ++i)
+  for (int i = 0; i < kWholePerThread; ++i)
     buf[cols(min(static_cast<int>(threadIdx.x) + i * kWholeThreads, n1 * S - 1))] = v[i];
   __syncthreads();
   lds_fft<R, kWholeThreads, kWholePerThread>(buf, n1, logn1, S, +1, q, logL, cols);

@@ -454,7 +454,7 @@ __device__ __forceinline__ void mid_item(const SweepArgs &a, int item) {
 // mode items (one per wavefront).  LDS (dynamic) holds the partial sums of
 // wavefronts 1 .. LG-1 of a quad.
 template <typename R, bool COMP, int NP, int CM, int G, int TW, int WAVES>
-__global__ __launch_bounds__(8 * kLanes) __attribute__((amdgpu_waves_per_eu(WAVES))) void
+__global__ __launch_bounds__(4 * kLanes) __attribute__((amdgpu_waves_per_eu(WAVES))) void
 step_kernel_mfma(SweepArgs sa, ModeArgs ma, long long sweep_wgs, long long mid_wgs, int mid_items,
                  long long nblocks, int LG, int QW, unsigned spread) {
   extern __shared__ __align__(16) unsigned char quad_lds[];
@@ -542,7 +542,7 @@ hipError_t step_launch_q(const sbim_handle *h, const Group &g, const SweepArgs &
 template <typename R, bool COMP>
 hipError_t step_launch_quads(const sbim_handle *h, const Group &g, const SweepArgs &sa,
                              const ModeArgs &ma, long long mode_blocks, hipEvent_t ev0, hipEvent_t ev1) {
-  if (h->lag_chunks < 1 || h->sweep_quads < 1 || h->lag_chunks * h->sweep_quads > 8)
+  if (h->lag_chunks < 1 || h->sweep_quads < 1 || h->lag_chunks * h->sweep_quads > 4)
     return hipErrorInvalidValue;
   if (g.np == 2 && h->quad_modes == 4) {
     if (h->depth == 16) return step_launch_q<R, COMP, 2, 4, 1, 1>(h, g, sa, ma, mode_blocks, ev0, ev1);

@@ -759,7 +759,7 @@ int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, vo
     }
     if (const char *env = std::getenv("SBIM_SWEEP_CHUNKS")) {  // tuning override
       const int v = std::atoi(env);
-      if (v == 1 || v == 2 || v == 4 || (v == 8 && h->tiled)) h->lag_chunks = v;
+      if (v == 1 || v == 2 || v == 4) h->lag_chunks = v;
     }
     // Quads per work-group.  Time-tiled form: one, its history tiles are whole cache
     // lines (two quads measured within 2%, either way).  In-order form: two for the
@@ -768,8 +768,7 @@ int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, vo
     h->sweep_quads = !h->tiled && h->comp && h->lag_chunks <= 2 ? 2 : 1;
     if (const char *env = std::getenv("SBIM_SWEEP_QUADS")) {  // tuning override
       const int v = std::atoi(env);
-      if ((v == 1 || v == 2 || v == 4) && v * h->lag_chunks <= (h->tiled ? 8 : 4))
-        h->sweep_quads = v;
+      if ((v == 1 || v == 2 || v == 4) && v * h->lag_chunks <= 4) h->sweep_quads = v;
     }
   }
   size_t need = extra;

@@ -746,12 +746,15 @@ int plan_handle(sbim_handle *h, bool in_order, size_t extra, sbim_handle *eh, vo
       // ranges: W = 150 float64 rupture 128 x 64 238 / 222 / 232; W = 250 float32
       // 512 x 128 65 / 59 / 60; W = 1000 float64 512^2 with the sweep spread among the
       // other work - / 219 / 211, compensated - / 136 / 133; eight are slower there).
-      // Plain float32 sums a range without a break: from 3 and 8 rounds, so that its chains
-      // are no longer than the vector sweep's four or the in-order form's (error against
-      // float64, 64^2 x 2 at 470 lags: 2.31e-7 with two ranges, 1.99e-7 in order).
+      // Plain float32 sums a range without a break: two from 3 rounds and four from 8 (two
+      // planes) or 11, so that its error is that of the vector sweep's four ranges or of
+      // the in-order form (against float64, 64^2 x 2 at 470 lags: 2.31e-7 with two ranges,
+      // 1.84e-7 with four, 1.99e-7 in order; 128^2 one plane at 300 1.95e-7 with two,
+      // 2.05e-7 in the vector sweep).
       const int rounds = (c.window_cap + 31) / 32;
       const bool plain = !h->fp64 && !h->comp;
-      h->lag_chunks = rounds < (plain ? 3 : 4) ? 1 : rounds < (plain ? 8 : 16) ? 2 : 4;
+      const int two = plain ? 3 : 4, four = !plain ? 16 : h->g[0].np == 2 ? 8 : 11;
+      h->lag_chunks = rounds < two ? 1 : rounds < four ? 2 : 4;
     } else {
       // in-order form: as many as fit at least 16 blocks of 4 lags, up to two for the
       // compensated form (its registers allow three wavefronts per SIMD), four for

@@ -184,27 +184,30 @@ __device__ __forceinline__ cplx<R> load_sum(const void *pending, long long row, 
 template <typename R, bool COMP, bool TILED>
 __device__ __forceinline__ void mode_step(const ModeArgs &a, int p, long long s) {
   using W = typename W4<R>::T;
+  constexpr bool EARLY = TILED || COMP;  // (below)
   const double2 *__restrict__ spec = static_cast<const double2 *>(a.spec);
   const double2 *__restrict__ spec_v = static_cast<const double2 *>(a.spec_v);
   cplx<R> *__restrict__ ring = static_cast<cplx<R> *>(a.ring);
   double2 *__restrict__ state = a.state;
   const long long M = a.M, nh = a.nh, step = a.step;
   const int np = a.np;
-  // What a step reads beside the spectrum and the state (window, kernel rows, sums)
-  // is asked for at once in the matrix-core forms; beside the vector sweep, after the
-  // push: its chains of dependent loads are the launch's length, and the fewer loads
-  // the mode items have in flight the shorter they are (float64 512^2, two materials,
-  // 40 lags: the launch 30.0 and 29.2 us, the mode items alone 18.0 and 19.2).
+  // What a step reads beside the spectrum and the state (window, kernel rows, sums) is
+  // asked for at once in the matrix-core and compensated forms (2048^2 x 2, windows per
+  // mode, compensated, us a step: 769 so, 782 after the push); beside the plain vector
+  // sweeps, after the push: their chains of dependent loads are the launch's length, and
+  // the fewer loads the mode items have in flight the shorter they are (a launch at once /
+  // after: float64 512^2, two materials, 40 lags, 30.0 / 29.2; float32 512^2 x 2, 5 lags,
+  // 25.7 / 24.3).
   const int natural = a.nat[s];
-  if (!TILED && natural < 0) return;  // a padding position of the matrix-core layout: no mode
+  if (!EARLY && natural < 0) return;  // a padding position of the matrix-core layout: no mode
   int wl = 0;
   long long row0 = 0;
-  if constexpr (TILED) {
+  if constexpr (EARLY) {
     wl = a.win[s];
     row0 = a.row0[s];
   }
   const double4 geom = *reinterpret_cast<const double4 *>(a.geom + 4 * s);
-  const int b = TILED ? __builtin_amdgcn_readfirstlane(static_cast<int>(s >> 6)) : static_cast<int>(s >> 6);
+  const int b = EARLY ? __builtin_amdgcn_readfirstlane(static_cast<int>(s >> 6)) : static_cast<int>(s >> 6);
   const int lane = static_cast<int>(s & 63);
   const int cap = a.blk_cap[b];
   const long long base = a.blk_off[b];
@@ -248,8 +251,8 @@ __device__ __forceinline__ void mode_step(const ModeArgs &a, int p, long long s)
       for (int t = 0; t < 5; ++t) midv[t] = q[t * M];
     }
   };
-  if constexpr (TILED) load_sums();
-  if (TILED && natural < 0) return;
+  if constexpr (EARLY) load_sums();
+  if (EARLY && natural < 0) return;
   const double q = geom.x, kh1 = geom.y, kh3 = geom.z;
 
   // record of one step: of the block's ring, or of the recent ring
@@ -310,7 +313,7 @@ __device__ __forceinline__ void mode_step(const ModeArgs &a, int p, long long s)
   }
 
   // ---- history sums of step n
-  if constexpr (!TILED) {
+  if constexpr (!EARLY) {
     wl = a.win[s];
     load_sums();
   }
@@ -329,7 +332,7 @@ __device__ __forceinline__ void mode_step(const ModeArgs &a, int p, long long s)
     if (fresh > 0) {
       // the newest lags: plain products (the compensated form folds their sum,
       // at most depth + 1 or kMidPeriod + 1 lags, into the pending sum once)
-      const W *__restrict__ rowp = static_cast<const W *>(a.table) + (TILED ? row0 : a.row0[s]);
+      const W *__restrict__ rowp = static_cast<const W *>(a.table) + (EARLY ? row0 : a.row0[s]);
       R part[kSums];
 #pragma unroll
       for (int k = 0; k < kSums; ++k) part[k] = COMP ? R(0) : acc[k].s;

@@ -128,8 +128,8 @@ typedef struct {
                                   (one window for every mode, of 64 lags or more; and
                                   either a float32 form with two planes of one material or
                                   more than 2^18 modes x lags per plane and, on grids that
-                                  fill the chip, longer windows); float32 handles
-                                  that drive a fault or a strip sum their lags in order,
+                                  fill the chip, longer windows); handles that
+                                  drive a strip, or a fault in float32, sum their lags in order,
                                   with two planes of one material on the matrix cores too.
                                   Without device memory for the time-tiled matrix-core form
                                   (which holds 42 to 74 pending sums per mode, the others
@@ -520,8 +520,8 @@ typedef struct {
 /*
  * sbim_strip_create: a strip on handle h (one plane of side +1, or planes of
  * sides +1, -1 when layers_below > 0; dx1 == dx3; at step 0) with the fault parameters of
- * sbim_fault_params (copied and checked on the device; synchronises the stream).  A float32
- * handle is planned again with its sums in order as by sbim_fault_create.
+ * sbim_fault_params (copied and checked on the device; synchronises the stream).  A handle
+ * of any precision is planned with its sums in order as by sbim_fault_create.
  */
 int sbim_strip_create(sbim_handle *h, const sbim_strip_config *cfg, const sbim_fault_params *prm,
                       sbim_strip **out);

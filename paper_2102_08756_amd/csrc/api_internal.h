@@ -67,8 +67,8 @@ int ensure_adjoint(sbim_handle *h);
 int replan_in_order(sbim_handle *h);
 // Whether that plan and its adjoint fit what is free and what the present plan holds.
 bool adjoint_fits_in_order(const sbim_handle *h, size_t free_b);
-// Plan a float32 handle with its history sums in lag order (fault, strip).
-int keep_sum_order(sbim_handle *h);
+// Plan a handle of a strip, or a float32 handle of a fault, with its sums in lag order.
+int keep_sum_order(sbim_handle *h, bool strip);
 // One forward step: transform u (and v for VEL_INPUT), then the step launch of
 // every material group with the given rule for the damping term's velocity.
 int push_fields(sbim_handle *h, const void *u, const void *v, int vel_rule);

@@ -125,7 +125,7 @@ int sbim_fault_create(sbim_handle *h, const sbim_fault_params *prm, sbim_fault *
                 "0 <= mu_k <= mu_s",
                 cell / h->n3, cell % h->n3);
   }
-  int rc = keep_sum_order(h);
+  int rc = keep_sum_order(h, false);
   if (!rc) rc = fault_clear(f);
   if (rc) {
     free_fault(f);

@@ -105,7 +105,7 @@ struct sbim_handle {
   long long step = 0;             // pushes done
   long long bstep = 0;            // backward calls done
   int depth = 1;                  // sweep depth: steps served by one pass over a block's history
-  bool in_order = false;          // drives a fault or strip in float32: sums and transforms keep their rounding
+  bool in_order = false;          // drives a strip, or a fault in float32: sums and transforms keep their rounding
   bool mfma = false;              // history sweep on the matrix cores (quads of one class)
   bool tiled = false;             // ... in the time-tiled form (quads.hip), else in lag order (pairs.hip)
   int quad_modes = 4;             // time-tiled form: sorted positions that share a kernel row (2 or 4)

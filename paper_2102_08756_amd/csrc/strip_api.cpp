@@ -264,7 +264,7 @@ int sbim_strip_create(sbim_handle *h, const sbim_strip_config *sc, const sbim_fa
                 "0 <= mu_k <= mu_s",
                 cell / h->n3, cell % h->n3);
   }
-  int rc = keep_sum_order(h);
+  int rc = keep_sum_order(h, true);
   if (!rc) rc = strip_clear(s);
   if (rc) {
     free_strip(s);

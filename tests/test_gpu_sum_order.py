@@ -1,4 +1,4 @@
-"""GPU: float32 handles that drive a fault or a strip sum their lags in order.
+"""GPU: handles that drive a strip, or a fault in float32, sum their lags in order.
 
 Two planes of one material and a window of 64 lags or more run the in-order matrix-core sweep
 (pairs.hip); it is compared with the oracle on random pushes to a handle that a fault was opened on
@@ -172,6 +172,33 @@ def test_fault_after_an_adjoint_that_was_reset():
         f.close()
         sb.close()
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("window,n", [(20, 16), (64, 128)])
+def test_float64_strip_sums_as_the_vector_sweep(window, n, monkeypatch):
+    """Also where the handle alone would be in the time-tiled form: the steps of the vector
+    sweep, bit for bit."""
+    wl = workloads.TPV3
+    mat = (wl["rho"], wl["cp"], wl["cs"])
+    plane = dict(side=1, mu=wl["rho"] * wl["cs"] ** 2, cs=wl["cs"], cp=wl["cp"])
+    gen = torch.Generator().manual_seed(4)
+    tau0 = torch.stack([65e6 + 20e6 * torch.rand(n, n, generator=gen, dtype=torch.float64),
+                        torch.full((n, n), -120e6, dtype=torch.float64), torch.zeros(n, n, dtype=torch.float64)])
+    prm = [tau0.to(DEV)] + [torch.full((n, n), v, dtype=torch.float64, device=DEV) for v in (0.677, 0.525, 0.4)]
+    out = []
+    for kind in (None, "valu"):
+        if kind:
+            monkeypatch.setenv("SBIM_SWEEP_KIND", kind)
+        sb = handle(dict(n1=n, n3=n, dx1=100.0, dx3=100.0, dt=0.3 * 100.0 / wl["cp"], window_cap=window,
+                         planes=[plane]), "fp64")
+        assert sb.info()["sweep_matrix_cores"] == (1 if window == 64 and not kind else 0)
+        s = Strip(sb, [mat], *prm)
+        assert sb.info()["sweep_matrix_cores"] == 0
+        out.append(s.run(window + 20) + (s.read("displacement"),))
+        s.close()
+        sb.close()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
 
 
 def test_two_sided_strip_in_order(monkeypatch):

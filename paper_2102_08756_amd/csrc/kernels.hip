@@ -625,7 +625,7 @@ hipError_t step_launch_s(const sbim_handle *h, const Group &g, const SweepArgs &
   // 34.5 at 42) and above one lag of the longest window per 2500 modes and planes (compensated, unsplit against split: 2048^2 x 2 at 400 lags 763 and
   // 830 us a step, 2048^2 x 2 at 2000 913 and 829, 1024^2 at 300 184 and 125); with one
   // window, while the sweep has at most a wavefront per CU (float64: 256^2 at 60 lags 49
-  // and 37 us, 512^2 at 40 65 and 65) and lags enough so far (256 x 64: float32 at 20 lags
+  // and 37 us, 512^2 at 40 61 and 65) and lags enough so far (256 x 64: float32 at 20 lags
   // 26.5 and 25.7, compensated at 28 29.2 and 30.7, at 34 31.5 and 31.0).
   // A handle that sums in order keeps its chains whole.
   if constexpr (S == 6 || (S * T == 8 && sizeof(R) == 4 && !COMP)) {
